@@ -53,29 +53,60 @@ __device__ __forceinline__ bool in_scope(const int32_t *comp, int32_t label, int
   return label < 0 || comp[x] == label;
 }
 
-__global__ void uf_init_kernel(int32_t *parent, const int32_t *comp, int32_t label, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride)
-    if (in_scope(comp, label, x)) parent[x] = (int32_t)x;
-}
-
-// Sampling phase (the Afforest strategy of Sutton, Ben-Nun and Barak, 2018):
-// every vertex in scope first unites with the first kSampleLinks entries of
-// its row, which on skewed graphs already joins almost every vertex of the
-// largest component into one tree.
+// Hooking phase: the first unions, without an atomic.  Every lower vertex
+// takes the first live entry of its row as parent (rows are ascending and
+// upper ids precede lower ones: its smallest upper neighbour), then every
+// upper vertex the smallest of the parents of its first kSampleLinks live
+// entries, if smaller than itself.  Each thread writes only its own vertex's
+// parent, and each parent is a smaller id of the same component, so the
+// result is a forest for the union-find below; a hub's smallest neighbour
+// has a very small id, so on skewed graphs almost every vertex ends in one
+// tree.  (The Afforest strategy of Sutton, Ben-Nun and Barak, 2018, samples
+// the first neighbours too, but unites them: here every neighbour of a hub
+// then contended for the same few roots: a relabelling of 1.5 M vertices of
+// 2e7 skewed edges took 2.3 to 5.2 ms by the graph's seed, all but 0.05 ms of
+// it those unions; hooks and merges take 0.24 ms.)
 constexpr int kSampleLinks = 2;
+// Entries looked at for a live one; a vertex with none there stays a root.
+constexpr int kHookProbe = 16;
 
-__global__ void uf_sample_link_kernel(const int64_t *__restrict__ off,
-                                      const int32_t *__restrict__ cols, const int32_t *comp,
-                                      int32_t label, int32_t *parent, int64_t n) {
+__global__ void uf_hook_lower_kernel(const int64_t *__restrict__ off,
+                                     const int32_t *__restrict__ cols, const int32_t *comp,
+                                     int32_t label, int32_t *parent, int64_t nU, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
     if (!in_scope(comp, label, x)) continue;
-    const int64_t s = off[x], e = off[x + 1];
-    for (int64_t j = s; j < e && j < s + kSampleLinks; ++j) {
-      const int32_t w = cols[j];
-      if (w >= 0) uf_union(parent, (int32_t)x, w);
+    int32_t p = (int32_t)x;
+    if (x >= nU) {
+      const int64_t s = off[x], e = min(off[x + 1], s + kHookProbe);
+      for (int64_t j = s; j < e; ++j) {
+        const int32_t w = cols[j];
+        if (w >= 0) {
+          p = w;
+          break;
+        }
+      }
     }
+    parent[x] = p;
+  }
+}
+
+__global__ void uf_hook_upper_kernel(const int64_t *__restrict__ off,
+                                     const int32_t *__restrict__ cols, const int32_t *comp,
+                                     int32_t label, int32_t *parent, int64_t nU) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < nU; x += stride) {
+    if (!in_scope(comp, label, x)) continue;
+    int32_t p = (int32_t)x;
+    const int64_t s = off[x], e = min(off[x + 1], s + kHookProbe);
+    int links = 0;
+    for (int64_t j = s; j < e && links < kSampleLinks; ++j) {
+      const int32_t w = cols[j];
+      if (w < 0) continue;
+      p = min(p, parent[w]);  // a lower vertex's, final since the last launch
+      ++links;
+    }
+    parent[x] = p;
   }
 }
 
@@ -86,15 +117,102 @@ __global__ void uf_compress_kernel(int32_t *parent, const int32_t *comp, int32_t
     if (in_scope(comp, label, x)) astore(&parent[x], uf_find(parent, (int32_t)x));
 }
 
-// Roots of kRootSamples evenly spaced vertices (-1 when out of scope).
-constexpr int kRootSamples = 1024;
+// Merging phase: the roots at the two ends of two more edges of every upper
+// vertex, from the middle of its row, are joined by lowering the larger
+// root's parent to the smaller root.  A minimum may overwrite another join,
+// which is then not made: trees hold vertices of one component all the same,
+// and the completion below walks every vertex outside the largest tree.  On
+// 1.5 M vertices and 2e7 skewed edges the hooks leave 15,205 trees, the
+// largest of 13% of the vertices, and a first launch two or one that hold
+// 99% (90% and 9%, or 99%, by the seed): no join between two low roots need
+// have been kept.  A second launch over every kMergeEvery-th vertex (kFind:
+// roots looked up, since the trees are not compressed in between) joins
+// those, and leaves 10,700 vertices of a few thousand entries outside.
+//
+// Nearly all joins lower one of a few dozen large roots, and same-address
+// atomics (and stores) queue: each workgroup first takes the minimum per root
+// in a small direct-mapped LDS table and adds each to memory once (a join
+// whose slot another root holds goes to memory).  340 us without the table,
+// 665 with plain stores in place of the minimum.
+constexpr int kMergeBlock = 1024;
+constexpr int kMergeSlots = 2048;
+constexpr int kMergeEvery = 16;
 
-__global__ void uf_sample_roots_kernel(const int32_t *parent, const int32_t *comp, int32_t label,
-                                       int64_t n, int32_t *roots) {
+template <bool kFind>
+__global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ cols, const int32_t *comp,
+    int32_t label, int32_t *parent, int64_t nU) {
+  __shared__ int32_t key[kMergeSlots], low[kMergeSlots];
+  for (int i = threadIdx.x; i < kMergeSlots; i += kMergeBlock) {
+    key[i] = -1;
+    low[i] = INT32_MAX;
+  }
+  __syncthreads();
+  const int64_t stride = (int64_t)gridDim.x * kMergeBlock;
+  for (int64_t i = (int64_t)blockIdx.x * kMergeBlock + threadIdx.x;; i += stride) {
+    const int64_t x = kFind ? i * kMergeEvery : i;
+    if (x >= nU) break;
+    if (!in_scope(comp, label, x)) continue;
+    const int64_t s = off[x], d = off[x + 1] - s;
+    if (d == 0) continue;
+    const int32_t w[2] = {cols[s + d / 3], cols[s + 2 * d / 3]};
+    // (a parent lowered meanwhile may be read old or new: both are in the
+    // vertex's component)
+    const int32_t rx = kFind ? uf_find(parent, (int32_t)x) : parent[x];
+    int32_t rw[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      rw[k] = w[k] < 0 ? rx : kFind ? uf_find(parent, w[k]) : parent[w[k]];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int32_t lo = min(rx, rw[k]), hi = max(rx, rw[k]);
+      if (lo == hi) continue;
+      const int slot = (int)(((uint32_t)hi * 2654435761u) >> 21);
+      static_assert(kMergeSlots == 1 << 11, "slot hash");
+      int32_t held = __hip_atomic_load(&key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (held < 0) {
+        const int32_t old = atomicCAS(&key[slot], -1, hi);
+        held = old < 0 ? hi : old;
+      }
+      if (held != hi)
+        atomicMin(&parent[hi], lo);
+      else if (__hip_atomic_load(&low[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > lo)
+        atomicMin(&low[slot], lo);
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kMergeSlots; i += kMergeBlock)
+    if (key[i] >= 0) atomicMin(&parent[key[i]], low[i]);
+}
+
+// The most frequent root among kRootSamples evenly spaced vertices into
+// *big (-1 when none of them is in scope): one workgroup, every thread
+// counting its own sample among all of them in LDS, so that the choice
+// needs no host.
+constexpr int kRootSamples = 256;
+
+__global__ __launch_bounds__(kRootSamples) void uf_big_root_kernel(const int32_t *parent,
+                                                                   const int32_t *comp,
+                                                                   int32_t label, int64_t n,
+                                                                   int32_t *big) {
+  __shared__ __align__(16) int32_t roots[kRootSamples];
+  __shared__ unsigned long long best;
   const int i = threadIdx.x;
-  if (i >= kRootSamples) return;
   const int64_t x = (n * i) / kRootSamples;
-  roots[i] = (x < n && in_scope(comp, label, x)) ? aload(&parent[x]) : -1;
+  const int32_t mine = (x < n && in_scope(comp, label, x)) ? aload(&parent[x]) : -1;
+  roots[i] = mine;
+  if (i == 0) best = 0;
+  __syncthreads();
+  int c = 0;
+  for (int j = 0; j < kRootSamples; j += 4) {
+    const int4 r = *reinterpret_cast<const int4 *>(&roots[j]);
+    c += (r.x == mine) + (r.y == mine) + (r.z == mine) + (r.w == mine);
+  }
+  // (the count in the high word decides, then the smaller root)
+  if (mine >= 0)
+    atomicMax(&best, ((unsigned long long)c << 32) | (uint32_t)(0x7FFFFFFF - mine));
+  __syncthreads();
+  if (i == 0) *big = best != 0 ? 0x7FFFFFFF - (int32_t)(uint32_t)best : -1;
 }
 
 // Completion: every vertex in scope outside the tree of root `big` unites
@@ -103,7 +221,8 @@ __global__ void uf_sample_roots_kernel(const int32_t *parent, const int32_t *com
 __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
     const int64_t *__restrict__ off, const int32_t *__restrict__ cols, const int32_t *comp,
     int32_t label, int32_t *parent, const int32_t *ins_head, const int32_t *ins_next,
-    const int32_t *ins_other, int64_t n, int32_t big) {
+    const int32_t *ins_other, int64_t n, const int32_t *big_root) {
+  const int32_t big = *big_root;
   const int gw = blockIdx.x * kWavesPerBlock + wave_in_block();
   const int nw = gridDim.x * kWavesPerBlock;
   for (int64_t b = (int64_t)gw * kWave; b < n; b += (int64_t)nw * kWave) {
@@ -393,40 +512,29 @@ int small_grid(const Graph &g, int64_t items) {
 
 // Component labels for the whole graph (label < 0) or re-labelling of the
 // vertices currently labelled `label` (deletion may split that component).
-// Synchronises the stream once (the largest tree's root is read on the
-// host); uses the partial-sum buffers as scratch (they are reset before every
-// computation).
+// Stream-ordered; the root of the largest tree sits in the partial-sum
+// buffer (reset before every computation).
 hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
-  static_assert(kRootSamples * sizeof(int32_t) <= kMaxBlocks * kPartFields * sizeof(int64_t),
-                "root samples must fit the partial-sum buffer");
   const int32_t *head = g.delta.count > 0 ? g.delta.head : nullptr;
-  int32_t *d_roots = reinterpret_cast<int32_t *>(g.part);
-  int32_t *h_roots = reinterpret_cast<int32_t *>(g.h_part);
-  uf_init_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
-  uf_sample_link_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, g.comp, label,
-                                                           g.parent, g.n);
+  int32_t *d_big = reinterpret_cast<int32_t *>(g.part);
+  uf_hook_lower_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, g.comp, label, g.parent,
+                                                          g.nU, g.n);
+  uf_hook_upper_kernel<<<small_grid(g, g.nU), 256, 0, s>>>(g.off, g.cols, g.comp, label,
+                                                           g.parent, g.nU);
   uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
-  uf_sample_roots_kernel<<<1, kRootSamples, 0, s>>>(g.parent, g.comp, label, g.n, d_roots);
-  hipError_t e = hipMemcpyAsync(h_roots, d_roots, sizeof(int32_t) * kRootSamples,
-                                hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return e;
-  std::vector<int32_t> r(h_roots, h_roots + kRootSamples);
-  std::sort(r.begin(), r.end());
-  int32_t big = -1;
-  int best = 0;
-  for (size_t i = 0; i < r.size();) {
-    size_t j = i;
-    while (j < r.size() && r[j] == r[i]) ++j;
-    if (r[i] >= 0 && (int)(j - i) > best) {
-      best = (int)(j - i);
-      big = r[i];
-    }
-    i = j;
-  }
+  auto merge_grid = [&](int64_t items) {
+    return (int)std::max<int64_t>(
+        1, std::min<int64_t>((items + kMergeBlock - 1) / kMergeBlock, g.cu_count));
+  };
+  uf_merge_kernel<false><<<merge_grid(g.nU), kMergeBlock, 0, s>>>(g.off, g.cols, g.comp, label,
+                                                                  g.parent, g.nU);
+  uf_merge_kernel<true><<<merge_grid(g.nU / kMergeEvery + 1), kMergeBlock, 0, s>>>(
+      g.off, g.cols, g.comp, label, g.parent, g.nU);
+  uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
+  uf_big_root_kernel<<<1, kRootSamples, 0, s>>>(g.parent, g.comp, label, g.n, d_big);
   uf_rest_link_kernel<<<wide_grid(g), kBlock, 0, s>>>(g.off, g.cols, g.comp, label, g.parent,
                                                       head, g.delta.next, g.delta.other, g.n,
-                                                      big);
+                                                      d_big);
   uf_label_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
   return hipGetLastError();
 }

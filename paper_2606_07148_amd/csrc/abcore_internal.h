@@ -282,6 +282,9 @@ struct Graph {
   uint32_t *probe_bits = nullptr;  // ceil(n/32) words: results of offset probes
   int32_t *comp = nullptr;  // component labels
   bool comp_valid = false;
+  // no served deletion since the labels were computed (serving only merges
+  // labels, so after one a label may cover several components)
+  bool comp_exact = false;
   int32_t *parent = nullptr; // union-find scratch
   Delta delta;
   int version = 0;

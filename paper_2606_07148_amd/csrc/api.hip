@@ -537,6 +537,7 @@ abcore_status compute_components(Graph &g, hipStream_t s) {
   if (g.n > 0) CHK(launch_cc(g, -1, s));
   CHK(hipStreamSynchronize(s));
   g.comp_valid = true;
+  g.comp_exact = true;
   return ABCORE_OK;
 }
 
@@ -1642,10 +1643,10 @@ static abcore_status query_impl(Graph *g, abcore_edge_update upd, uint32_t alpha
   const int32_t cu = g->h_state->aux0, cv = g->h_state->aux1;
   const int32_t x = upd.u, y = g->nU + upd.v;
   // 2. component maintenance (Sec. V): merge on insertion, re-label the old
-  //    component on deletion
+  //    component on deletion (unless the update kernel settled its labels)
   if (upd.op > 0) {
     if (cu != cv) CHK(launch_relabel(*g, std::max(cu, cv), std::min(cu, cv), s));
-  } else {
+  } else if (ustat != 2) {
     CHK(launch_cc(*g, cu, s));
   }
   // 3. scoped peel: Algorithm 1 on the component(s) of u and v only

@@ -297,15 +297,15 @@ __device__ int64_t row_find(const int32_t *cols, int64_t a, int64_t b, int32_t t
   return a;
 }
 
-// Applies one update on a single thread.  Validation precedes every write,
+// Applies one update (one thread).  Validation precedes every write,
 // so a rejected update leaves the graph untouched.  st->status: 0 applied,
 // 1 applied using the new delta slot `slot`, -5 present (insertion),
 // -4 absent (deletion).  aux0/aux1 receive the labels of u and v before the
 // update.
-__global__ void update_kernel(int64_t *off, int32_t *cols, int64_t m_csr, int32_t *deg0,
-                              const int32_t *comp, int32_t *ins_head, int32_t *ins_next,
-                              int32_t *ins_other, int64_t slot, int32_t nU, int32_t u,
-                              int32_t v, int32_t op, PeelState *st) {
+__device__ void apply_update(const int64_t *off, int32_t *cols, int32_t *deg0,
+                             const int32_t *comp, int32_t *ins_head, int32_t *ins_next,
+                             int32_t *ins_other, int64_t slot, int32_t nU, int32_t u, int32_t v,
+                             int32_t op, PeelState *st) {
   const int32_t x = u, y = nU + v;
   st->aux0 = comp != nullptr ? comp[x] : -1;
   st->aux1 = comp != nullptr ? comp[y] : -1;
@@ -376,7 +376,88 @@ __global__ void update_kernel(int64_t *off, int32_t *cols, int64_t m_csr, int32_
     deg0[y] -= 1;
     st->status = 0;
   }
-  (void)m_csr;
+}
+
+// The update (thread 0), and after a deletion on exact labels (settle) the
+// common cases in which it splits nothing that needs a search: an endpoint
+// left without edges becomes its own component (unless it was the label of
+// vertices that stay), and endpoints still joined by a path of length three
+// x - v' - u' - y leave every label as it is.  status 2: the labels are
+// settled; 0: the component has to be labelled again (0.24 ms at 1.5 M
+// vertices, and growing with them).  The path is looked for in bounded work,
+// so not finding one proves nothing: the first kSettleRow entries of x's row
+// in LDS, against the first kSettleScan entries of the rows of the first
+// kSettleCand neighbours of y, one row per wave at a time.  Inserted edges
+// take no part.  Measured at 2e7 edges: 11 us with the path found, against
+// 5 us for the update alone.
+constexpr int kSettleBlock = 1024;
+constexpr int kSettleRow = 8192;
+constexpr int kSettleCand = 64;
+constexpr int kSettleScan = 1024;
+
+__global__ __launch_bounds__(kSettleBlock) void update_kernel(
+    const int64_t *off, int32_t *cols, int32_t *deg0, int32_t *comp, int32_t *ins_head,
+    int32_t *ins_next, int32_t *ins_other, int64_t slot, int32_t nU, int32_t u, int32_t v,
+    int32_t op, int settle, PeelState *st) {
+  __shared__ int32_t row[kSettleRow];
+  __shared__ int s_found;
+  if (threadIdx.x == 0) {
+    s_found = 0;
+    apply_update(off, cols, deg0, comp, ins_head, ins_next, ins_other, slot, nU, u, v, op, st);
+  }
+  if (op > 0 || !settle) return;
+  __syncthreads();  // the deletion is visible to the workgroup
+  if (st->status != 0) return;
+  const int32_t x = u, y = nU + v;
+  const int32_t dx = deg0[x], dy = deg0[y];
+  __syncthreads();  // (status is rewritten below)
+  if (dx == 0 || dy == 0) {
+    if (threadIdx.x != 0) return;
+    // y, a lower vertex, labels no vertex but itself
+    if (dy == 0) comp[y] = y;
+    if (dy == 0 || comp[x] != x) {
+      if (dx == 0) comp[x] = x;
+      st->status = 2;
+    }
+    return;
+  }
+  const int64_t xa = off[x];
+  const int nrow = (int)min(off[x + 1] - xa, (int64_t)kSettleRow);
+  for (int i = threadIdx.x; i < nrow; i += kSettleBlock) row[i] = cols[xa + i];
+  __syncthreads();
+  const int64_t ya = off[y];
+  const int ncand = (int)min(off[y + 1] - ya, (int64_t)kSettleCand);
+  for (int c = wave_in_block(); c < ncand; c += kSettleBlock / kWave) {
+    if (__hip_atomic_load(&s_found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
+    const int32_t w = cols[ya + c];
+    if (w < 0) continue;  // deleted, x among them
+    const int64_t ra = off[w], rb = min(off[w + 1], ra + kSettleScan);
+    for (int64_t j0 = ra; j0 < rb; j0 += kWave) {
+      const int64_t j = j0 + lane_id();
+      const int32_t z = j < rb ? cols[j] : -1;
+      bool hit = false;
+      if (z >= 0) {
+        // rows are ascending once tombstones ~c are decoded
+        int lo = 0, hi = nrow;
+        while (lo < hi) {
+          const int mid = (lo + hi) / 2;
+          const int32_t r = row[mid];
+          if ((r < 0 ? ~r : r) < z)
+            lo = mid + 1;
+          else
+            hi = mid;
+        }
+        hit = lo < nrow && row[lo] == z;
+      }
+      if (__ballot(hit)) {
+        if (lane_id() == 0)
+          __hip_atomic_store(&s_found, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        break;
+      }
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && s_found) st->status = 2;
 }
 
 // A window of served updates, applied in order on a single thread (the order
@@ -546,9 +627,10 @@ hipError_t launch_relabel(Graph &g, int32_t from, int32_t to, hipStream_t s) {
 
 hipError_t launch_update(Graph &g, int32_t u, int32_t v, int32_t op, int64_t slot,
                          hipStream_t s) {
-  update_kernel<<<1, 1, 0, s>>>(g.off, g.cols, g.m_csr, g.deg0, g.comp_valid ? g.comp : nullptr,
-                                g.delta.head, g.delta.next, g.delta.other, slot, g.nU, u, v, op,
-                                g.state);
+  const bool settle = op < 0 && g.comp_valid && g.comp_exact;
+  update_kernel<<<1, settle ? kSettleBlock : kWave, 0, s>>>(
+      g.off, g.cols, g.deg0, g.comp_valid ? g.comp : nullptr, g.delta.head, g.delta.next,
+      g.delta.other, slot, g.nU, u, v, op, settle ? 1 : 0, g.state);
   return hipGetLastError();
 }
 

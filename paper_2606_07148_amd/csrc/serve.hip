@@ -297,6 +297,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     g.m += win[i].op;
     g.upd_version = r.version;
     g.delta.count = r.pairs_after;
+    if (win[i].op < 0) g.comp_exact = false;
     if (win[i].op > 0) {
       int32_t a = find(r.label_u), b = find(r.label_v);
       if (a != b) {

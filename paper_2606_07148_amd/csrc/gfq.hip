@@ -551,31 +551,160 @@ __global__ void answer_kernel(const int32_t *deg, int32_t x, int32_t y, int32_t 
   st->aux0 = bits;
 }
 
-// Current-graph CSR export: degrees -> offsets are computed by the caller;
-// each thread copies one row (live base entries, then inserted entries kept
-// in ascending order by insertion).
-__global__ void export_rows_kernel(const int64_t *off, const int32_t *cols,
-                                   const int32_t *ins_head, const int32_t *ins_next,
-                                   const int32_t *ins_other, const int64_t *out_off,
-                                   int32_t *out_cols, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    int64_t o = out_off[x];
-    const int64_t o0 = o;
-    for (int64_t j = off[x]; j < off[x + 1]; ++j)
-      if (cols[j] >= 0) out_cols[o++] = cols[j];
-    if (ins_head != nullptr) {
-      for (int32_t e = ins_head[x]; e >= 0; e = ins_next[e]) {
-        const int32_t w = ins_other[e];
-        if (w < 0) continue;
-        int64_t p = o++;
-        while (p > o0 && out_cols[p - 1] > w) {
-          out_cols[p] = out_cols[p - 1];
+// Current-graph CSR export, rows ascending: live base entries merged with
+// the live inserted ones.  Rows that the updates left alone (full degree, no
+// inserted list) are copied, 64 rows of at most kPiece entries or 64 pieces
+// of longer rows per wave, entry by entry across the lanes whatever the
+// degree mix: an entry moves by one shift per row.  The other rows follow one
+// per wave: an entry's position is the live entries before it (ballots) plus
+// the inserted ones below it (a short list in LDS).  (A thread per row copied
+// hubs of 50,000 entries serially, 8.7 ms at 2e7 edges.)
+constexpr int kExportIns = 64;  // inserted entries of a row held in LDS
+
+// Copies d entries from s to s + shift (per lane; d <= kPiece).
+__device__ __forceinline__ void copy_rows(const int32_t *__restrict__ cols,
+                                          int32_t *__restrict__ out, int64_t s, int d,
+                                          int64_t shift) {
+  constexpr int kU = 4;  // copies in flight per lane
+  const int incl = wave_incl_scan(d);
+  const int total = __shfl(incl, kWave - 1, kWave);
+  const int64_t from = s - (incl - d);  // position of the batch's entry 0, by this row
+  for (int base = 0; base < total; base += kU * kWave) {
+    int32_t w[kU];
+    int64_t to[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int k = base + u * kWave + lane_id();
+      const int kk = min(k, total - 1);
+      int j = 0;
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (__shfl(incl, j + step - 1, kWave) <= kk) j += step;
+      const int64_t pos = __shfl(from, j, kWave) + kk;
+      to[u] = pos + __shfl(shift, j, kWave);
+      w[u] = cols[pos];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (base + u * kWave + lane_id() < total) out[to[u]] = w[u];
+  }
+}
+
+// One changed row: base entries [s, s + d), output from o0; ins (kExportIns
+// ints of LDS) and the wave are its own.
+__device__ __forceinline__ void export_changed_row(const int32_t *__restrict__ cols, int64_t s,
+                                                   int64_t d, int head,
+                                                   const int32_t *__restrict__ ins_next,
+                                                   const int32_t *__restrict__ ins_other,
+                                                   int64_t o0, int32_t *__restrict__ out,
+                                                   int32_t *ins) {
+  constexpr int kU = 4;
+  int all = 0;
+  if (lane_id() == 0) {
+    // the live inserted entries, ascending; a list that does not fit is
+    // merged entry by entry below
+    for (int e = head; e >= 0; e = ins_next[e]) {
+      const int32_t v = ins_other[e];
+      if (v < 0) continue;
+      if (all < kExportIns) {
+        int p = all;
+        while (p > 0 && ins[p - 1] > v) {
+          ins[p] = ins[p - 1];
           --p;
         }
-        out_cols[p] = w;
+        ins[p] = v;
       }
+      ++all;
     }
+  }
+  all = __shfl(all, 0, kWave);
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int c = all <= kExportIns ? all : 0;
+  int64_t live = 0, before = 0;  // before: live entries below lane i's inserted one
+  for (int64_t k0 = 0; k0 < d; k0 += kU * kWave) {
+    int32_t w[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t k = k0 + u * kWave + lane_id();
+      w[u] = k < d ? cols[s + k] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const uint64_t mask = __ballot(w[u] >= 0);
+      int below = 0;
+      for (int i = 0; i < c; ++i) {
+        const bool less = w[u] >= 0 && w[u] < ins[i];
+        if (!less && w[u] >= 0) ++below;
+        const int cnt = __popcll(__ballot(less));
+        if (lane_id() == i) before += cnt;
+      }
+      if (w[u] >= 0) out[o0 + live + __popcll(mask & lanemask_lt()) + below] = w[u];
+      live += __popcll(mask);
+    }
+  }
+  if (lane_id() < c) out[o0 + before + lane_id()] = ins[lane_id()];
+  if (all > kExportIns && lane_id() == 0) {
+    int64_t o = o0 + live;
+    for (int e = head; e >= 0; e = ins_next[e]) {
+      const int32_t v = ins_other[e];
+      if (v < 0) continue;
+      int64_t p = o++;
+      while (p > o0 && out[p - 1] > v) {
+        out[p] = out[p - 1];
+        --p;
+      }
+      out[p] = v;
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(kBlock) void export_rows_kernel(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ cols,
+    const int32_t *__restrict__ deg0, const int32_t *__restrict__ ins_head,
+    const int32_t *__restrict__ ins_next, const int32_t *__restrict__ ins_other,
+    const int32_t *__restrict__ piece_row, const int64_t *__restrict__ piece_start,
+    const int64_t *__restrict__ out_off, int32_t *__restrict__ out_cols, int64_t n,
+    int64_t npieces) {
+  __shared__ int32_t s_ins[kWavesPerBlock][kExportIns];
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block();
+  const int64_t nw = (int64_t)gridDim.x * kWavesPerBlock;
+  auto unchanged = [&](int64_t x, int64_t d) {
+    return deg0[x] == d && (ins_head == nullptr || ins_head[x] < 0);
+  };
+  for (int64_t b = gw * kWave; b < n; b += nw * kWave) {
+    const int64_t x = b + lane_id();
+    int64_t s = 0, shift = 0, d = 0;
+    bool same = true;
+    if (x < n) {
+      s = off[x];
+      d = off[x + 1] - s;
+      shift = out_off[x] - s;
+      same = unchanged(x, d);
+    }
+    copy_rows(cols, out_cols, s, same && d <= kPiece ? (int)d : 0, shift);
+    for (uint64_t rows = __ballot(!same); rows != 0; rows &= rows - 1) {
+      const int j = __ffsll((unsigned long long)rows) - 1;
+      const int64_t rs = __shfl(s, j, kWave);
+      export_changed_row(cols, rs, __shfl(d, j, kWave),
+                         ins_head != nullptr ? ins_head[b + j] : -1, ins_next, ins_other,
+                         rs + __shfl(shift, j, kWave), out_cols, s_ins[wave_in_block()]);
+    }
+  }
+  for (int64_t b = gw * kWave; b < npieces; b += nw * kWave) {
+    const int64_t p = b + lane_id();
+    int64_t s = 0, shift = 0;
+    int d = 0;
+    if (p < npieces) {
+      const int32_t x = piece_row[p];
+      s = piece_start[p];
+      const int64_t rs = off[x], re = off[x + 1];
+      shift = out_off[x] - rs;
+      if (unchanged(x, re - rs)) d = (int)(min(s + kPiece, re) - s);
+    }
+    copy_rows(cols, out_cols, s, d, shift);
   }
 }
 
@@ -654,8 +783,18 @@ hipError_t launch_update_window(Graph &g, const int32_t *d_upd, int w, WindowRec
   return hipGetLastError();
 }
 
-// Writes the current CSR (n+1 offsets, 2m entries) to caller buffers.
+// Writes the current CSR (n+1 offsets, 2m entries) to caller buffers: on a
+// graph unchanged since its build the handle's own arrays (0.06 ms at 2e7
+// edges), else the rows with their updates.
 hipError_t launch_export(Graph &g, int64_t *out_off, int32_t *out_cols, hipStream_t s) {
+  if (g.version == 0 && g.delta.count == 0) {
+    hipError_t e = hipMemcpyAsync(out_off, g.off, sizeof(int64_t) * (g.n + 1),
+                                  hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess && out_cols != nullptr && g.m_csr > 0)
+      e = hipMemcpyAsync(out_cols, g.cols, sizeof(int32_t) * 2 * g.m_csr,
+                         hipMemcpyDeviceToDevice, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  }
   int64_t *tmp64 = nullptr;
   void *temp = nullptr;
   size_t temp_bytes = 0;
@@ -668,9 +807,9 @@ hipError_t launch_export(Graph &g, int64_t *out_off, int32_t *out_cols, hipStrea
     e = prim::exclusive_sum(temp, temp_bytes, tmp64, out_off, (size_t)(g.n + 1), s);
   if (e == hipSuccess && out_cols != nullptr) {
     const int32_t *head = g.delta.count > 0 ? g.delta.head : nullptr;
-    export_rows_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, head, g.delta.next,
-                                                          g.delta.other, out_off, out_cols,
-                                                          g.n);
+    export_rows_kernel<<<wide_grid(g), kBlock, 0, s>>>(
+        g.off, g.cols, g.deg0, head, g.delta.next, g.delta.other, g.piece_row, g.piece_start,
+        out_off, out_cols, g.n, g.npieces);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);

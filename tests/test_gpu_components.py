@@ -85,3 +85,31 @@ def test_labels_after_deletions_match_oracle(name, seed):
         want = oracle.components(oracle.Graph(nU, nL, cur[:, 0].copy(), cur[:, 1].copy()))
         assert np.array_equal(pkg.abcore_components(g).cpu().numpy(), want), (op, u, v)
     g.destroy()
+
+
+@pytest.mark.parametrize("inserted", [0, 1, 64, 65, 200])
+def test_export_after_updates(inserted):
+    """The exported CSR of an updated graph: rows of both sides of the piece
+    length (64) and a hub of 3,000 entries, tombstones in some, and `inserted`
+    new edges of one row (its list held in LDS up to 64)."""
+    r = np.random.RandomState(inserted)
+    nU, nL = 300, 4000
+    rows = {0: 3000, 1: 64, 2: 65, 3: 1, 5: 63, 6: 128, 7: 129}
+    eu = np.concatenate([np.full(d, u) for u, d in rows.items()] + [r.randint(8, nU, 2000)])
+    ev = np.concatenate([r.permutation(3700)[:d] for d in rows.values()] +
+                        [r.randint(0, 3700, 2000)])
+    left = set(zip(eu.tolist(), ev.tolist()))
+    g = pkg.abcore_build_csr(nU, nL, to_dev(eu), to_dev(ev))
+    gone = [e for u in (0, 2, 3, 6) for e in sorted(x for x in left if x[0] == u)[::40]]
+    # (lower ids from 3700 on have no edges yet; the smaller ones interleave)
+    new = [(0, v) for v in range(4000) if (0, v) not in left][::3][:inserted]
+    for op, (u, v) in [(-1, e) for e in gone] + [(1, e) for e in new]:
+        pkg.abcore_query(g, u, v, op, 2, 2)
+        (left.discard if op < 0 else left.add)((u, v))
+    off, cols = [t.cpu().numpy() for t in pkg.abcore_export_csr(g)]
+    pairs = sorted(left)
+    deg = np.bincount([u for u, _ in pairs] + [nU + v for _, v in pairs], minlength=nU + nL)
+    assert np.array_equal(off, np.concatenate([[0], np.cumsum(deg)]))
+    want = [nU + v for _, v in pairs] + [u for u, v in sorted(pairs, key=lambda e: (e[1], e[0]))]
+    assert np.array_equal(cols, np.array(want, np.int32))
+    g.destroy()

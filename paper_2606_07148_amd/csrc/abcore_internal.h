@@ -540,10 +540,25 @@ hipError_t launch_kcore_steps(Graph &g, int steps, hipStream_t s);
 hipError_t launch_kcore_levels(Graph &g, int levels, hipStream_t s);
 hipError_t launch_cc(Graph &g, int32_t only_label, hipStream_t s);
 hipError_t query_persistent_grids(Graph &g);
-abcore_status build_pieces(Graph &g, hipStream_t s);
+// Temporaries of a build, one stream-ordered allocation shared by its phases:
+// two key buffers of `words` 64-bit words (the edges, or 2 (n + 1) counts),
+// one of n + 1, and the primitives' storage (grown on demand).
+struct BuildScratch {
+  explicit BuildScratch(hipStream_t stream) : s(stream) {}
+  ~BuildScratch();
+  hipError_t reserve(int64_t m, int64_t n);
+  hipError_t reserve_temp(size_t bytes);
+  hipStream_t s;
+  uint64_t *k0 = nullptr, *k1 = nullptr;
+  int64_t *c = nullptr;       // n + 1
+  int32_t *flags = nullptr;   // 2 small counters
+  void *block = nullptr, *temp = nullptr;
+  size_t temp_bytes = 0;
+};
+abcore_status build_pieces(Graph &g, BuildScratch &w, hipStream_t s);
 // Degree ranks and the rank-sorted adjacency copy (Graph::rank, rcols); on
 // an allocation failure it leaves them null and succeeds.
-abcore_status build_ranks(Graph &g, hipStream_t s);
+abcore_status build_ranks(Graph &g, BuildScratch &w, hipStream_t s);
 hipError_t launch_answer_view(const PeelArgs &a, int32_t x, int32_t y, hipStream_t s);
 // After a peel scoped to the components of vx and vy: the survivors of that
 // scope, or with `connected` those reachable from vx or vy through

@@ -141,8 +141,8 @@ void set_error(const char *fmt, ...) {
   va_end(ap);
 }
 
-abcore_status build_csr_device(Graph &g, const int32_t *eu, const int32_t *ev, int64_t m,
-                               hipStream_t s);
+abcore_status build_csr_device(Graph &g, BuildScratch &w, const int32_t *eu, const int32_t *ev,
+                               int64_t m, hipStream_t s);
 hipError_t launch_relabel(Graph &g, int32_t from, int32_t to, hipStream_t s);
 hipError_t launch_update(Graph &g, int32_t u, int32_t v, int32_t op, int64_t slot,
                          hipStream_t s);
@@ -918,18 +918,19 @@ abcore_status abcore_build_csr(int32_t n_upper, int32_t n_lower, const int32_t *
     auto ms_since = [&](std::chrono::steady_clock::time_point t) {
       return std::chrono::duration<double, std::milli>(now() - t).count();
     };
+    BuildScratch scratch_keys(s);
     auto t0 = now();
-    st = build_csr_device(*g, d_eu, d_ev, m, s);
+    st = build_csr_device(*g, scratch_keys, d_eu, d_ev, m, s);
     if (st == ABCORE_OK && hipStreamSynchronize(s) != hipSuccess) st = ABCORE_EDEVICE;
     if (st != ABCORE_OK) break;
     g->build_ms[0] = ms_since(t0);
     t0 = now();
-    st = build_pieces(*g, s);
+    st = build_pieces(*g, scratch_keys, s);
     if (st == ABCORE_OK && hipStreamSynchronize(s) != hipSuccess) st = ABCORE_EDEVICE;
     if (st != ABCORE_OK) break;
     g->build_ms[1] = ms_since(t0);
     t0 = now();
-    st = build_ranks(*g, s);
+    st = build_ranks(*g, scratch_keys, s);
     if (st == ABCORE_OK && hipStreamSynchronize(s) != hipSuccess) st = ABCORE_EDEVICE;
     if (st != ABCORE_OK) break;
     g->build_ms[2] = ms_since(t0);

@@ -1,35 +1,34 @@
 // Device construction of the unified CSR (Sec. III: CSR storage; Sec. IV-A:
-// contiguous ids, upper first).  Pairs are keyed (u*nL + v), radix-sorted
-// and deduplicated (E is a set); the sorted keys give the upper rows
-// directly, a second sort on (v*nU + u) gives the lower rows.  Both sorts are
-// rocPRIM's device radix sort, called directly (prim.h); the build is
-// preprocessing and is not part of the timed peel.
+// contiguous ids, upper first).  Pairs are keyed (u, v) in two bit fields,
+// radix-sorted and deduplicated (E is a set); the sorted keys give the upper
+// rows directly.  The sort is stable, so sorting them again by v's field
+// alone gives the lower rows.  The sorts are rocPRIM's device radix sort,
+// called directly (prim.h) between two buffers; the build is preprocessing
+// and is not part of the timed peel.
 #include "prim.h"
 
 #include <algorithm>
 
 #include "abcore_internal.h"
+#include "wave.h"
 
 namespace abc {
 
 namespace {
 
-__global__ void validate_kernel(const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
-                                int64_t m, int32_t nU, int32_t nL, int32_t *bad) {
+// Keys (u << vbits) | v, and *bad set if an endpoint is out of range (its key
+// then means nothing and the build ends after the sort).
+__global__ void make_keys_kernel(const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
+                                 int64_t m, int32_t nU, int32_t nL, int vbits,
+                                 uint64_t *__restrict__ keys, int32_t *bad) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int found = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
     const int32_t u = eu[i], v = ev[i];
     found |= (u < 0 || u >= nU || v < 0 || v >= nL);
+    keys[i] = ((uint64_t)(uint32_t)u << vbits) | (uint64_t)(uint32_t)v;
   }
   if (__ballot(found) != 0 && (threadIdx.x & 63) == 0) atomicOr(bad, 1);
-}
-
-__global__ void make_keys_kernel(const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
-                                 int64_t m, int32_t nL, uint64_t *__restrict__ keys) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride)
-    keys[i] = (uint64_t)(uint32_t)eu[i] * (uint64_t)nL + (uint64_t)(uint32_t)ev[i];
 }
 
 // Counts one per valid lane into deg[row] where the lanes of a wave hold
@@ -48,11 +47,12 @@ __device__ __forceinline__ void add_row_runs(int32_t *deg, int32_t row, bool ok)
   }
 }
 
-// Upper side: unique key i = (u, v) -> cols[i] = nU + v; upper degrees; and
-// the transposed key (v*nU + u) for the lower rows.  (Wave-uniform loop.)
+// Upper side: unique key i = (u, v) -> cols[i] = nU + v; upper degrees.
+// (Wave-uniform loop.)
 __global__ void upper_rows_kernel(const uint64_t *__restrict__ ukeys, int64_t md, int32_t nU,
-                                  int32_t nL, int32_t *__restrict__ cols,
-                                  int32_t *__restrict__ deg, uint64_t *__restrict__ tkeys) {
+                                  int vbits, int32_t *__restrict__ cols,
+                                  int32_t *__restrict__ deg) {
+  const uint64_t vmask = (1ull << vbits) - 1;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x / kWave) * kWave; b < md;
        b += stride) {
@@ -61,18 +61,18 @@ __global__ void upper_rows_kernel(const uint64_t *__restrict__ ukeys, int64_t md
     int32_t u = 0;
     if (ok) {
       const uint64_t k = ukeys[i];
-      u = (int32_t)(k / (uint64_t)nL);
-      const int32_t v = (int32_t)(k % (uint64_t)nL);
-      cols[i] = nU + v;
-      tkeys[i] = (uint64_t)(uint32_t)v * (uint64_t)nU + (uint64_t)(uint32_t)u;
+      u = (int32_t)(k >> vbits);
+      cols[i] = nU + (int32_t)(k & vmask);
     }
     add_row_runs(deg, u, ok);
   }
 }
 
-// Lower side: keys sorted by (v, u) -> cols[md + i] = u; lower degrees.
+// Lower side: the keys in (v, u) order -> cols[md + i] = u; lower degrees.
 __global__ void lower_rows_kernel(const uint64_t *__restrict__ lkeys, int64_t md, int32_t nU,
-                                  int32_t *__restrict__ cols, int32_t *__restrict__ deg) {
+                                  int vbits, int32_t *__restrict__ cols,
+                                  int32_t *__restrict__ deg) {
+  const uint64_t vmask = (1ull << vbits) - 1;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x / kWave) * kWave; b < md;
        b += stride) {
@@ -81,8 +81,8 @@ __global__ void lower_rows_kernel(const uint64_t *__restrict__ lkeys, int64_t md
     int32_t v = 0;
     if (ok) {
       const uint64_t k = lkeys[i];
-      cols[md + i] = (int32_t)(k % (uint64_t)nU);
-      v = (int32_t)(k / (uint64_t)nU);
+      cols[md + i] = (int32_t)(k >> vbits);
+      v = (int32_t)(k & vmask);
     }
     add_row_runs(deg + nU, v, ok);
   }
@@ -122,7 +122,7 @@ __global__ void fill_pieces_kernel(const int64_t *__restrict__ off, int64_t n,
       const int64_t f = first[x];
       const int64_t np = (d + kPiece - 1) / kPiece;
       piece_first[x] = (int32_t)f;
-      heavy_rows[hfirst[x]] = (int32_t)x;
+      if (heavy_rows != nullptr) heavy_rows[hfirst[x]] = (int32_t)x;
       for (int64_t k = 0; k < np; ++k) {
         piece_row[f + k] = (int32_t)x;
         piece_start[f + k] = off[x] + k * kPiece;
@@ -175,126 +175,131 @@ int bits_for(uint64_t maxkey) {
 
 }  // namespace
 
+BuildScratch::~BuildScratch() {
+  if (temp) (void)dev_free_async(temp, s);
+  if (block) (void)dev_free_async(block, s);
+}
+
+hipError_t BuildScratch::reserve(int64_t m, int64_t n) {
+  const int64_t words = std::max<int64_t>(m, 2 * (n + 1));
+  const hipError_t e = dev_malloc_async(&block, sizeof(uint64_t) * (2 * words + n + 2), s);
+  if (e != hipSuccess) return e;
+  k0 = static_cast<uint64_t *>(block);
+  k1 = k0 + words;
+  c = reinterpret_cast<int64_t *>(k1 + words);
+  flags = reinterpret_cast<int32_t *>(c + n + 1);
+  return hipSuccess;
+}
+
+hipError_t BuildScratch::reserve_temp(size_t bytes) {
+  if (temp != nullptr && bytes <= temp_bytes) return hipSuccess;
+  if (temp) (void)dev_free_async(temp, s);
+  temp = nullptr;
+  temp_bytes = 0;
+  const hipError_t e = dev_malloc_async(&temp, std::max<size_t>(bytes, 16), s);
+  if (e == hipSuccess) temp_bytes = std::max<size_t>(bytes, 16);
+  return e;
+}
+
 // Builds off/cols/deg0 of g (already sized: g.nU, g.nL, g.n set; arrays not
 // yet allocated).  Returns a status and sets the error message.
-abcore_status build_csr_device(Graph &g, const int32_t *eu, const int32_t *ev, int64_t m,
-                               hipStream_t s) {
+abcore_status build_csr_device(Graph &g, BuildScratch &w, const int32_t *eu, const int32_t *ev,
+                               int64_t m, hipStream_t s) {
 #define BCHK(x)                                                                     \
   do {                                                                              \
     hipError_t e_ = (x);                                                            \
     if (e_ != hipSuccess) {                                                         \
       set_error("CSR build: %s failed: %s", #x, hipGetErrorString(e_));             \
-      status = (e_ == hipErrorOutOfMemory) ? ABCORE_ENOMEM : ABCORE_EDEVICE;        \
-      goto done;                                                                    \
+      return (e_ == hipErrorOutOfMemory) ? ABCORE_ENOMEM : ABCORE_EDEVICE;          \
     }                                                                               \
   } while (0)
-  abcore_status status = ABCORE_OK;
   const int grid = std::max(1, std::min(g.cu_count * 8, (int)((m + 255) / 256)));
-  int32_t *d_bad = nullptr;
-  uint64_t *k0 = nullptr, *k1 = nullptr;
-  int *d_nsel = nullptr;
-  void *temp = nullptr;
-  size_t temp_bytes = 0, need = 0;
-  int64_t *deg64 = nullptr;
-  int32_t h_bad = 0;
-  int h_nsel = 0;
+  size_t need = 0, most = 0;
   int64_t md = 0;
-  const int ubits = bits_for((uint64_t)std::max(g.nU, 1) * (uint64_t)std::max(g.nL, 1) - 1);
-  const int lbits = ubits;
+  const int vbits = bits_for((uint64_t)std::max(g.nL, 1) - 1);
+  const int ubits = bits_for((uint64_t)std::max(g.nU, 1) - 1);
 
   BCHK(dev_malloc(&g.off, sizeof(int64_t) * (g.n + 1)));
   BCHK(dev_malloc(&g.deg0, sizeof(int32_t) * std::max<int64_t>(g.n, 1)));
+  BCHK(w.reserve(m, g.n));
   BCHK(hipMemsetAsync(g.deg0, 0, sizeof(int32_t) * std::max<int64_t>(g.n, 1), s));
   if (m > 0) {
-    BCHK(dev_malloc_async(&d_bad, sizeof(int32_t), s));
-    BCHK(hipMemsetAsync(d_bad, 0, sizeof(int32_t), s));
-    validate_kernel<<<grid, 256, 0, s>>>(eu, ev, m, g.nU, g.nL, d_bad);
+    uint64_t *cur = w.k0, *alt = w.k1;
+    BCHK(hipMemsetAsync(w.flags, 0, 2 * sizeof(int32_t), s));
+    make_keys_kernel<<<grid, 256, 0, s>>>(eu, ev, m, g.nU, g.nL, vbits, cur, w.flags);
     BCHK(hipGetLastError());
-    BCHK(hipMemcpyAsync(&h_bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    // temporary storage large enough for the sort and the unique selection
+    BCHK(prim::sort_keys_two(nullptr, need, cur, alt, (size_t)m, 0, ubits + vbits, s));
+    most = need;
+    BCHK(prim::unique(nullptr, need, cur, alt, w.flags + 1, (size_t)m, s));
+    BCHK(w.reserve_temp(std::max(most, need)));
+    need = w.temp_bytes;
+    BCHK(prim::sort_keys_two(w.temp, need, cur, alt, (size_t)m, 0, ubits + vbits, s));
+    need = w.temp_bytes;
+    BCHK(prim::unique(w.temp, need, cur, alt, w.flags + 1, (size_t)m, s));
+    int32_t h_flags[2] = {0, 0};
+    BCHK(hipMemcpyAsync(h_flags, w.flags, sizeof(h_flags), hipMemcpyDeviceToHost, s));
     BCHK(hipStreamSynchronize(s));
-    if (h_bad) {
+    if (h_flags[0] != 0) {
       set_error("abcore_build_csr: edge endpoint out of range");
-      status = ABCORE_EINVAL;
-      goto done;
+      return ABCORE_EINVAL;
     }
-    BCHK(dev_malloc_async(&k0, sizeof(uint64_t) * m, s));
-    BCHK(dev_malloc_async(&k1, sizeof(uint64_t) * m, s));
-    BCHK(dev_malloc_async(&d_nsel, sizeof(int), s));
-    make_keys_kernel<<<grid, 256, 0, s>>>(eu, ev, m, g.nL, k0);
-    BCHK(hipGetLastError());
-    // temp storage large enough for the sort and the unique selection
-    BCHK(prim::sort_keys(nullptr, need, k0, k1, (size_t)m, 0, ubits, s));
-    temp_bytes = std::max(temp_bytes, need);
-    BCHK(prim::unique(nullptr, need, k1, k0, d_nsel, (size_t)m, s));
-    temp_bytes = std::max(temp_bytes, need);
-    BCHK(dev_malloc_async(&temp, std::max<size_t>(temp_bytes, 16), s));
-    BCHK(prim::sort_keys(temp, temp_bytes, k0, k1, (size_t)m, 0, ubits, s));
-    BCHK(prim::unique(temp, temp_bytes, k1, k0, d_nsel, (size_t)m, s));
-    BCHK(hipMemcpyAsync(&h_nsel, d_nsel, sizeof(int), hipMemcpyDeviceToHost, s));
-    BCHK(hipStreamSynchronize(s));
-    md = h_nsel;
+    md = h_flags[1];
+    w.k0 = alt;  // the unique keys
+    w.k1 = cur;
   }
   g.m_csr = md;
   g.m = md;
   BCHK(dev_malloc(&g.cols, sizeof(int32_t) * std::max<int64_t>(2 * md, 1)));
   if (md > 0) {
     const int gridm = std::max(1, std::min(g.cu_count * 8, (int)((md + 255) / 256)));
-    upper_rows_kernel<<<gridm, 256, 0, s>>>(k0, md, g.nU, g.nL, g.cols, g.deg0, k1);
-    BCHK(hipGetLastError());
-    BCHK(prim::sort_keys(temp, temp_bytes, k1, k0, (size_t)md, 0, lbits, s));
-    lower_rows_kernel<<<gridm, 256, 0, s>>>(k0, md, g.nU, g.cols, g.deg0);
-    BCHK(hipGetLastError());
-  }
-  BCHK(dev_malloc_async(&deg64, sizeof(int64_t) * (g.n + 1), s));
-  {
-    const int gridn = std::max(1, std::min(g.cu_count * 8, (int)((g.n + 256) / 256)));
-    widen_kernel<<<gridn, 256, 0, s>>>(g.deg0, g.n, deg64);
+    upper_rows_kernel<<<gridm, 256, 0, s>>>(w.k0, md, g.nU, vbits, g.cols, g.deg0);
     BCHK(hipGetLastError());
     need = 0;
-    BCHK(prim::exclusive_sum(nullptr, need, deg64, g.off, (size_t)(g.n + 1), s));
-    if (need > temp_bytes) {
-      BCHK(dev_free_async(temp, s));
-      temp = nullptr;
-      temp_bytes = need;
-      BCHK(dev_malloc_async(&temp, temp_bytes, s));
-    }
-    BCHK(prim::exclusive_sum(temp, temp_bytes, deg64, g.off, (size_t)(g.n + 1), s));
+    BCHK(prim::sort_keys_two(nullptr, need, w.k0, w.k1, (size_t)md, 0, vbits, s));
+    BCHK(w.reserve_temp(need));
+    need = w.temp_bytes;
+    BCHK(prim::sort_keys_two(w.temp, need, w.k0, w.k1, (size_t)md, 0, vbits, s));
+    lower_rows_kernel<<<gridm, 256, 0, s>>>(w.k0, md, g.nU, vbits, g.cols, g.deg0);
+    BCHK(hipGetLastError());
   }
-  BCHK(hipStreamSynchronize(s));
-done:
-  for (void *p : {(void *)d_bad, (void *)k0, (void *)k1, (void *)d_nsel, temp, (void *)deg64})
-    if (p) (void)dev_free_async(p, s);
-  return status;
+  {
+    const int gridn = std::max(1, std::min(g.cu_count * 8, (int)((g.n + 256) / 256)));
+    widen_kernel<<<gridn, 256, 0, s>>>(g.deg0, g.n, w.c);
+    BCHK(hipGetLastError());
+    need = 0;
+    BCHK(prim::exclusive_sum(nullptr, need, w.c, g.off, (size_t)(g.n + 1), s));
+    BCHK(w.reserve_temp(need));
+    need = w.temp_bytes;
+    BCHK(prim::exclusive_sum(w.temp, need, w.c, g.off, (size_t)(g.n + 1), s));
+  }
+  return ABCORE_OK;
 #undef BCHK
 }
 
 // Splits rows longer than kPiece entries into pieces (see Graph).
-abcore_status build_pieces(Graph &g, hipStream_t s) {
+abcore_status build_pieces(Graph &g, BuildScratch &w, hipStream_t s) {
 #define PCHK(x)                                                                     \
   do {                                                                              \
     hipError_t e_ = (x);                                                            \
     if (e_ != hipSuccess) {                                                         \
       set_error("piece build: %s failed: %s", #x, hipGetErrorString(e_));           \
-      status = (e_ == hipErrorOutOfMemory) ? ABCORE_ENOMEM : ABCORE_EDEVICE;        \
-      goto done;                                                                    \
+      return (e_ == hipErrorOutOfMemory) ? ABCORE_ENOMEM : ABCORE_EDEVICE;          \
     }                                                                               \
   } while (0)
-  abcore_status status = ABCORE_OK;
-  int64_t *np = nullptr, *hv = nullptr, *first = nullptr, *hfirst = nullptr;
-  void *temp = nullptr;
-  size_t temp_bytes = 0;
+  int64_t *np = reinterpret_cast<int64_t *>(w.k0), *hv = np + (g.n + 1);
+  int64_t *first = reinterpret_cast<int64_t *>(w.k1), *hfirst = first + (g.n + 1);
+  size_t need = 0;
   int64_t h_tot[4] = {0, 0, 0, 0};
   const int grid = std::max(1, std::min(g.cu_count * 8, (int)((g.n + 256) / 256)));
-  PCHK(dev_malloc_async(&np, sizeof(int64_t) * (g.n + 1), s));
-  PCHK(dev_malloc_async(&hv, sizeof(int64_t) * (g.n + 1), s));
-  PCHK(dev_malloc_async(&first, sizeof(int64_t) * (g.n + 1), s));
-  PCHK(dev_malloc_async(&hfirst, sizeof(int64_t) * (g.n + 1), s));
   count_pieces_kernel<<<grid, 256, 0, s>>>(g.off, g.n, np, hv);
   PCHK(hipGetLastError());
-  PCHK(prim::exclusive_sum(nullptr, temp_bytes, np, first, (size_t)(g.n + 1), s));
-  PCHK(dev_malloc_async(&temp, std::max<size_t>(temp_bytes, 16), s));
-  PCHK(prim::exclusive_sum(temp, temp_bytes, np, first, (size_t)(g.n + 1), s));
-  PCHK(prim::exclusive_sum(temp, temp_bytes, hv, hfirst, (size_t)(g.n + 1), s));
+  PCHK(prim::exclusive_sum(nullptr, need, np, first, (size_t)(g.n + 1), s));
+  PCHK(w.reserve_temp(need));
+  need = w.temp_bytes;
+  PCHK(prim::exclusive_sum(w.temp, need, np, first, (size_t)(g.n + 1), s));
+  need = w.temp_bytes;
+  PCHK(prim::exclusive_sum(w.temp, need, hv, hfirst, (size_t)(g.n + 1), s));
   PCHK(hipMemcpyAsync(&h_tot[0], first + g.n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   PCHK(hipMemcpyAsync(&h_tot[1], first + g.nU, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   PCHK(hipMemcpyAsync(&h_tot[2], hfirst + g.n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -317,71 +322,127 @@ abcore_status build_pieces(Graph &g, hipStream_t s) {
   PCHK(dev_malloc(&g.pull_bounds, sizeof(int32_t) * 2 * (g.pull_bounds_grid + 1)));
   row_weight_kernel<<<grid, 256, 0, s>>>(g.off, g.n, np);
   PCHK(hipGetLastError());
-  PCHK(prim::exclusive_sum(temp, temp_bytes, np, hv, (size_t)(g.n + 1), s));
+  need = w.temp_bytes;
+  PCHK(prim::exclusive_sum(w.temp, need, np, hv, (size_t)(g.n + 1), s));
   pull_bounds_kernel<<<(2 * (g.pull_bounds_grid + 1) + 255) / 256, 256, 0, s>>>(
       hv, g.nU, g.n, g.pull_bounds_grid, g.pull_bounds);
   PCHK(hipGetLastError());
-  PCHK(hipStreamSynchronize(s));
-done:
-  for (void *p : {(void *)np, (void *)hv, (void *)first, (void *)hfirst, temp})
-    if (p) (void)dev_free_async(p, s);
-  return status;
+  return ABCORE_OK;
 #undef PCHK
 }
 
 namespace {
 
-// (layer-local key) decreasing degree, then id: 64-bit keys whose order is
-// the rank order of one layer.
-__global__ void rank_keys_kernel(const int64_t *__restrict__ off, int64_t lo, int64_t hi,
-                                 uint64_t *__restrict__ keys) {
+// Sort keys of the rank order: layer, then decreasing degree, above the id.
+// The ids start in order and the sort is stable, so it takes the upper field
+// alone (dbits of degree and the layer's bit; top is no smaller than any
+// degree).
+__global__ void rank_keys_kernel(const int64_t *__restrict__ off, int64_t nU, int64_t n,
+                                 int64_t top, int dbits, uint64_t *__restrict__ keys) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = lo + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < hi; x += stride) {
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
     const uint64_t d = (uint64_t)(off[x + 1] - off[x]);
-    keys[x - lo] = ((0x7FFFFFFFull - d) << 32) | (uint64_t)(x - lo);
+    keys[x] = ((((uint64_t)(x >= nU) << dbits) | ((uint64_t)top - d)) << 32) | (uint64_t)x;
   }
 }
 
-__global__ void rank_scatter_kernel(const uint64_t *__restrict__ sorted, int64_t cnt, int64_t lo,
+__global__ void rank_scatter_kernel(const uint64_t *__restrict__ sorted, int64_t nU, int64_t n,
                                     const int64_t *__restrict__ off, int32_t *__restrict__ rank,
                                     int32_t *__restrict__ rank_vtx, int64_t *__restrict__ rdeg) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += stride) {
-    const int64_t x = lo + (int64_t)(uint32_t)sorted[i];
-    rank[x] = (int32_t)i;
-    rank_vtx[lo + i] = (int32_t)x;
-    rdeg[lo + i] = off[x + 1] - off[x];
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const int64_t x = (int64_t)(uint32_t)sorted[i];
+    rank[x] = (int32_t)(i - (i < nU ? 0 : nU));
+    rank_vtx[i] = (int32_t)x;
+    rdeg[i] = off[x + 1] - off[x];
   }
 }
 
-// Entry keys (global rank of the row, neighbour's rank): sorted, the rows
-// come out in rank order and each row's ranks ascending.  A wave per row
-// (rows in turn), its lanes over the row's entries, so that hubs do not
-// serialise on one thread.
-__global__ void entry_keys_kernel(const int64_t *__restrict__ off, const int32_t *__restrict__ cols,
-                                  const int32_t *__restrict__ rank, int64_t n, int64_t nU, int rbits,
-                                  uint64_t *__restrict__ keys) {
-  const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-  const int64_t w0 = (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int lane = (int)(threadIdx.x % kWave);
-  for (int64_t x = w0; x < n; x += waves) {
-    const uint64_t r = (uint64_t)rank[x] + (x < nU ? 0 : (uint64_t)nU);
-    const int64_t e1 = off[x + 1];
-    for (int64_t e = off[x] + lane; e < e1; e += kWave)
-      keys[e] = (r << rbits) | (uint64_t)rank[cols[e]];
+// Entry keys (rank of the upper end << lbits) | rank of the lower end, in
+// order of the lower end's rank: the lower rows, taken in rank order.  A
+// stable sort by the upper field then gives the upper rows in rank order with
+// ascending neighbours, and one more by the lower field the lower rows: two
+// sorts of m keys on one layer's bits each, where keying both directions
+// with (row, neighbour) sorted 2 m keys on both (at 2e7 edges 2.3 ms of sorts
+// against 0.9).  A wave takes 64 rows of at most kPiece entries, or 64
+// pieces of longer rows, entry-balanced; bound by the random rank lookups.
+__device__ __forceinline__ void emit_entry_keys(const int32_t *__restrict__ cols,
+                                                const int32_t *__restrict__ rank, int64_t s,
+                                                int d, int64_t shift, int32_t r, int lbits,
+                                                uint64_t *__restrict__ keys) {
+  constexpr int kU = 4;  // entries in flight per lane
+  const int incl = wave_incl_scan(d);
+  const int total = __shfl(incl, kWave - 1, kWave);
+  const int64_t from = s - (incl - d);
+  for (int base = 0; base < total; base += kU * kWave) {
+    int32_t w[kU], row[kU];
+    int64_t to[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int kk = min(base + u * kWave + lane_id(), total - 1);
+      int j = 0;
+#pragma unroll
+      for (int step = 32; step > 0; step >>= 1)
+        if (__shfl(incl, j + step - 1, kWave) <= kk) j += step;
+      const int64_t pos = __shfl(from, j, kWave) + kk;
+      to[u] = pos + __shfl(shift, j, kWave);
+      row[u] = __shfl(r, j, kWave);
+      w[u] = cols[pos];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) w[u] = rank[w[u]];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (base + u * kWave + lane_id() < total)
+        keys[to[u]] = ((uint64_t)(uint32_t)w[u] << lbits) | (uint64_t)(uint32_t)row[u];
   }
 }
 
-// The neighbour's global rank: a lower neighbour (of an upper row) is its
-// layer rank past nU, so that the rank rows form a CSR graph of their own.
-__global__ void entry_unkey_kernel(const uint64_t *__restrict__ keys, int64_t cnt, int rbits,
-                                   int64_t nU, int32_t *__restrict__ rcols) {
-  const uint64_t mask = (1ull << rbits) - 1;
+__global__ __launch_bounds__(kBlock) void entry_keys_kernel(
+    const int64_t *__restrict__ off, const int32_t *__restrict__ cols,
+    const int32_t *__restrict__ rank, const int32_t *__restrict__ rank_vtx,
+    const int64_t *__restrict__ roff, const int32_t *__restrict__ rp_row,
+    const int64_t *__restrict__ rp_start, int64_t nU, int64_t n, int64_t m, int64_t p0, int64_t p1,
+    int lbits, uint64_t *__restrict__ keys) {
+  const int64_t gw = (int64_t)blockIdx.x * kWavesPerBlock + wave_in_block();
+  const int64_t nw = (int64_t)gridDim.x * kWavesPerBlock;
+  // (the lower rows' entries are the last m of the rank rows)
+  for (int64_t b = p0 + gw * kWave; b < p1; b += nw * kWave) {
+    const int64_t p = b + lane_id();
+    int64_t s = 0, shift = 0;
+    int32_t row = 0;
+    int d = 0;
+    if (p < p1) {
+      row = rp_row[p];
+      const int64_t t = rp_start[p], rs = roff[row];
+      s = off[rank_vtx[row]] + (t - rs);
+      shift = t - m - s;
+      d = (int)(min(t + kPiece, roff[row + 1]) - t);
+    }
+    emit_entry_keys(cols, rank, s, d, shift, row - (int32_t)nU, lbits, keys);
+  }
+  for (int64_t b = nU + gw * kWave; b < n; b += nw * kWave) {
+    const int64_t row = b + lane_id();
+    int64_t s = 0, shift = 0;
+    int d = 0;
+    if (row < n) {
+      const int64_t t = roff[row], len = roff[row + 1] - t;
+      s = off[rank_vtx[row]];
+      shift = t - m - s;
+      d = len <= kPiece ? (int)len : 0;
+    }
+    emit_entry_keys(cols, rank, s, d, shift, (int32_t)(row - nU), lbits, keys);
+  }
+}
+
+// The rank rows' entries: global ranks (a lower neighbour of an upper row is
+// its layer rank past nU, so that the rank rows form a CSR graph of their
+// own).
+__global__ void entry_unkey_kernel(const uint64_t *__restrict__ keys, int64_t m, int shift,
+                                   uint64_t mask, int32_t base, int32_t *__restrict__ out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += stride) {
-    const bool upper_row = (int64_t)(keys[i] >> rbits) < nU;
-    rcols[i] = (int32_t)((int64_t)(keys[i] & mask) + (upper_row ? nU : 0));
-  }
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride)
+    out[i] = (int32_t)((keys[i] >> shift) & mask) + base;
 }
 
 // Degree counts by threshold, from the rank order (degrees decrease along a
@@ -402,23 +463,39 @@ __global__ void rank_table_kernel(const int64_t *__restrict__ roff, int64_t lo, 
 
 }  // namespace
 
-abcore_status build_ranks(Graph &g, hipStream_t s) {
-  const int64_t ent = 2 * g.m_csr;
+abcore_status build_ranks(Graph &g, BuildScratch &w, hipStream_t s) {
+  const int64_t m = g.m_csr, ent = 2 * m;
   if (g.n == 0) return ABCORE_OK;
-  // 2^31 items is the sort's limit; larger graphs keep the bitmap pull
+  // row positions are kept in 31 bits elsewhere; larger graphs keep the
+  // bitmap pull
   if (ent >= 0x7FFFFFFFLL) return ABCORE_OK;
-  uint64_t *k0 = nullptr, *k1 = nullptr;
-  void *temp = nullptr;
-  size_t temp_bytes = 0, need = 0;
+  uint64_t *k0 = w.k0, *k1 = w.k1;
   bool ok = true;
   const int grid = std::max(1, std::min(g.cu_count * 8, (int)((g.n + 255) / 256)));
-  const int64_t nmax = std::max<int64_t>(std::max<int64_t>(g.nU, g.nL), 1);
-  const int rbits = bits_for((uint64_t)nmax - 1);
+  const int64_t top = std::max<int64_t>(std::max<int64_t>(g.nU, g.nL), 1);  // >= any degree
+  const int dbits = bits_for((uint64_t)top);
+  const int ubits = bits_for((uint64_t)std::max(g.nU, 1) - 1);
+  const int lbits = bits_for((uint64_t)std::max(g.nL, 1) - 1);
   const int xbits = bits_for((uint64_t)std::max<int64_t>(g.n, 1) - 1);
-  const int64_t items = std::max<int64_t>(ent, nmax);
   auto fail = [&](hipError_t e) {
     if (e != hipSuccess) ok = false;
     return e != hipSuccess;
+  };
+  auto sort_bits = [&](int64_t count, int begin, int end) {
+    size_t need = 0;
+    hipError_t e = prim::sort_keys_two(nullptr, need, k0, k1, (size_t)count, begin, end, s);
+    if (e == hipSuccess) e = w.reserve_temp(need);
+    need = w.temp_bytes;
+    return e == hipSuccess
+               ? prim::sort_keys_two(w.temp, need, k0, k1, (size_t)count, begin, end, s)
+               : e;
+  };
+  auto sum = [&](const int64_t *in, int64_t *out) {
+    size_t need = 0;
+    hipError_t e = prim::exclusive_sum(nullptr, need, in, out, (size_t)(g.n + 1), s);
+    if (e == hipSuccess) e = w.reserve_temp(need);
+    need = w.temp_bytes;
+    return e == hipSuccess ? prim::exclusive_sum(w.temp, need, in, out, (size_t)(g.n + 1), s) : e;
   };
   do {
     if (fail(dev_malloc(&g.rank, sizeof(int32_t) * g.n))) break;
@@ -427,83 +504,41 @@ abcore_status build_ranks(Graph &g, hipStream_t s) {
     if (fail(dev_malloc(&g.rcols, sizeof(int32_t) * std::max<int64_t>(ent, 1)))) break;
     g.rdeg_mask = (uint32_t)((1ull << xbits) - 1);
     if (fail(dev_malloc(&g.rdeg, sizeof(int32_t) * ((size_t)g.rdeg_mask + 1)))) break;
-    // k0 also holds the degrees by rank (n + 1 values after n + 1 slots)
-    if (fail(dev_malloc_async(&k0, sizeof(uint64_t) * std::max<int64_t>(items, 2 * (g.n + 1)), s))) break;
-    if (fail(dev_malloc_async(&k1, sizeof(uint64_t) * items, s))) break;
-    // temporary storage for the largest sort, and the offsets' scan
-    if (fail(prim::sort_keys(nullptr, need, k0, k1, (size_t)items, 0, 64, s)))
-      break;
-    temp_bytes = std::max<size_t>(need, 16);
-    need = 0;
-    if (fail(prim::exclusive_sum(nullptr, need, reinterpret_cast<int64_t *>(k0),
-                                              g.roff, (size_t)(g.n + 1), s)))
-      break;
-    temp_bytes = std::max(temp_bytes, need);
-    if (fail(dev_malloc_async(&temp, temp_bytes, s))) break;
-    // ranks, one layer at a time
-    for (int layer = 0; layer < 2 && ok; ++layer) {
-      const int64_t lo = layer == 0 ? 0 : g.nU, hi = layer == 0 ? g.nU : g.n;
-      if (hi <= lo) continue;
-      rank_keys_kernel<<<grid, 256, 0, s>>>(g.off, lo, hi, k0);
-      if (fail(hipGetLastError())) break;
-      size_t tb = temp_bytes;
-      if (fail(prim::sort_keys(temp, tb, k0, k1, (size_t)(hi - lo), 0, 64, s)))
-        break;
-      // (k0 holds no keys any more past the sort: its tail collects the
-      // degrees by rank, the offsets' scan input)
-      rank_scatter_kernel<<<grid, 256, 0, s>>>(k1, hi - lo, lo, g.off, g.rank, g.rank_vtx,
-                                               reinterpret_cast<int64_t *>(k0) + g.n + 1);
-      if (fail(hipGetLastError())) break;
-    }
-    if (!ok) break;
-    {
-      int64_t *rdeg = reinterpret_cast<int64_t *>(k0) + g.n + 1;
-      if (fail(hipMemsetAsync(rdeg + g.n, 0, sizeof(int64_t), s))) break;
-      size_t tb = temp_bytes;
-      if (fail(prim::exclusive_sum(temp, tb, rdeg, g.roff, (size_t)(g.n + 1), s))) break;
-    }
-    if (ent > 0) {
-      entry_keys_kernel<<<grid, 256, 0, s>>>(g.off, g.cols, g.rank, g.n, g.nU, rbits, k0);
-      if (fail(hipGetLastError())) break;
-      size_t tb = temp_bytes;
-      if (fail(prim::sort_keys(temp, tb, k0, k1, (size_t)ent, 0, rbits + xbits, s)))
-        break;
-      entry_unkey_kernel<<<grid, 256, 0, s>>>(k1, ent, rbits, g.nU, g.rcols);
-      if (fail(hipGetLastError())) break;
-    }
+    if (fail(dev_malloc(&g.rp_row, sizeof(int32_t) * std::max<int64_t>(g.npieces, 1)))) break;
+    if (fail(dev_malloc(&g.rp_start, sizeof(int64_t) * std::max<int64_t>(g.npieces, 1)))) break;
+    if (fail(dev_malloc(&g.rp_first, sizeof(int32_t) * g.n))) break;
+    // ranks, both layers at once; their degrees place the rank rows
+    rank_keys_kernel<<<grid, 256, 0, s>>>(g.off, g.nU, g.n, top, dbits, k0);
+    if (fail(hipGetLastError())) break;
+    if (fail(sort_bits(g.n, 32, 32 + dbits + 1))) break;
+    rank_scatter_kernel<<<grid, 256, 0, s>>>(k0, g.nU, g.n, g.off, g.rank, g.rank_vtx, w.c);
+    if (fail(hipGetLastError())) break;
+    if (fail(hipMemsetAsync(w.c + g.n, 0, sizeof(int64_t), s))) break;
+    if (fail(sum(w.c, g.roff))) break;
     // the rank rows' pieces (the same lengths as the vertex rows', in rank
-    // order; k0 and k1 serve as the counts and their scans)
+    // order; the key buffers serve as the counts and their scans)
     {
       int64_t *np = reinterpret_cast<int64_t *>(k0), *hv = np + (g.n + 1);
-      int64_t *hfirst = nullptr;
-      if (fail(dev_malloc_async(&hfirst, sizeof(int64_t) * 2 * (g.n + 1), s))) break;
-      int32_t *hrows = nullptr;
-      bool pok = false;
-      do {
-        int64_t *fcopy = hfirst + (g.n + 1);
-        count_pieces_kernel<<<grid, 256, 0, s>>>(g.roff, g.n, np, hv);
-        if (fail(hipGetLastError())) break;
-        size_t tb = temp_bytes;
-        if (fail(prim::exclusive_sum(temp, tb, np, fcopy, (size_t)(g.n + 1), s))) break;
-        tb = temp_bytes;
-        if (fail(prim::exclusive_sum(temp, tb, hv, hfirst, (size_t)(g.n + 1), s))) break;
-        if (fail(dev_malloc(&g.rp_row, sizeof(int32_t) * std::max<int64_t>(g.npieces, 1)))) break;
-        if (fail(dev_malloc(&g.rp_start, sizeof(int64_t) * std::max<int64_t>(g.npieces, 1))))
-          break;
-        if (fail(dev_malloc(&g.rp_first, sizeof(int32_t) * g.n))) break;
-        if (fail(dev_malloc_async(&hrows, sizeof(int32_t) * std::max<int64_t>(g.nheavy, 1), s))) break;
-        fill_pieces_kernel<<<grid, 256, 0, s>>>(g.roff, g.n, fcopy, hfirst, g.rp_row, g.rp_start,
-                                                g.rp_first, hrows);
-        if (fail(hipGetLastError())) break;
-        pok = true;
-      } while (0);
-      if (fail(hipStreamSynchronize(s))) pok = false;
-      if (hrows) (void)dev_free_async(hrows, s);
-      (void)dev_free_async(hfirst, s);
-      if (!pok) {
-        ok = false;
-        break;
-      }
+      int64_t *first = reinterpret_cast<int64_t *>(k1);
+      count_pieces_kernel<<<grid, 256, 0, s>>>(g.roff, g.n, np, hv);
+      if (fail(hipGetLastError())) break;
+      if (fail(sum(np, first))) break;
+      fill_pieces_kernel<<<grid, 256, 0, s>>>(g.roff, g.n, first, nullptr, g.rp_row, g.rp_start,
+                                              g.rp_first, nullptr);
+      if (fail(hipGetLastError())) break;
+    }
+    if (m > 0) {
+      entry_keys_kernel<<<wide_grid(g), kBlock, 0, s>>>(
+          g.off, g.cols, g.rank, g.rank_vtx, g.roff, g.rp_row, g.rp_start, g.nU, g.n, m,
+          g.npieces_upper, g.npieces, lbits, k0);
+      if (fail(hipGetLastError())) break;
+      if (fail(sort_bits(m, lbits, lbits + ubits))) break;
+      const int gridm = std::max(1, std::min(g.cu_count * 8, (int)((m + 255) / 256)));
+      entry_unkey_kernel<<<gridm, 256, 0, s>>>(k0, m, 0, (1ull << lbits) - 1, g.nU, g.rcols);
+      if (fail(hipGetLastError())) break;
+      if (fail(sort_bits(m, 0, lbits))) break;
+      entry_unkey_kernel<<<gridm, 256, 0, s>>>(k0, m, lbits, (1ull << ubits) - 1, 0, g.rcols + m);
+      if (fail(hipGetLastError())) break;
     }
     // per layer and threshold t: the vertices of degree >= t (ranks [0, K))
     // and their entries, kept on the host
@@ -546,8 +581,8 @@ abcore_status build_ranks(Graph &g, hipStream_t s) {
     if (!ok) break;
     if (fail(hipStreamSynchronize(s))) break;
   } while (0);
-  for (void *p : {(void *)k0, (void *)k1, temp})
-    if (p) (void)dev_free_async(p, s);
+  w.k0 = k0;
+  w.k1 = k1;
   if (!ok) {
     (void)hipGetLastError();
     if (g.rank) (void)dev_free(g.rank);

@@ -11,6 +11,7 @@
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/device/device_select.hpp>
+#include <rocprim/types/double_buffer.hpp>
 
 namespace abc {
 namespace prim {
@@ -19,6 +20,19 @@ namespace prim {
 inline hipError_t sort_keys(void *temp, size_t &bytes, const uint64_t *in, uint64_t *out,
                             size_t n, int begin, int end, hipStream_t s) {
   return rocprim::radix_sort_keys(temp, bytes, in, out, n, (unsigned)begin, (unsigned)end, s);
+}
+
+// The same between two buffers: `cur` holds the keys before and after, `alt`
+// is the other buffer (they may change places).  Needs no third buffer of n
+// keys, as the form above does.
+inline hipError_t sort_keys_two(void *temp, size_t &bytes, uint64_t *&cur, uint64_t *&alt,
+                                size_t n, int begin, int end, hipStream_t s) {
+  rocprim::double_buffer<uint64_t> keys(cur, alt);
+  const hipError_t e =
+      rocprim::radix_sort_keys(temp, bytes, keys, n, (unsigned)begin, (unsigned)end, s);
+  cur = keys.current();
+  alt = keys.alternate();
+  return e;
 }
 
 // The first key of every run of equal keys, in order; *count their number.

@@ -539,6 +539,8 @@ hipError_t launch_kcore_persistent(Graph &g, hipStream_t s);
 hipError_t launch_kcore_steps(Graph &g, int steps, hipStream_t s);
 hipError_t launch_kcore_levels(Graph &g, int levels, hipStream_t s);
 hipError_t launch_cc(Graph &g, int32_t only_label, hipStream_t s);
+hipError_t launch_reached(Graph &g, const uint32_t *member, int32_t vx, int32_t vy,
+                          uint32_t *bits, unsigned long long *count, hipStream_t s);
 hipError_t query_persistent_grids(Graph &g);
 // Temporaries of a build, one stream-ordered allocation shared by its phases:
 // two key buffers of `words` 64-bit words (the edges, or 2 (n + 1) counts),
@@ -563,7 +565,7 @@ hipError_t launch_answer_view(const PeelArgs &a, int32_t x, int32_t y, hipStream
 // After a peel scoped to the components of vx and vy: the survivors of that
 // scope, or with `connected` those reachable from vx or vy through
 // survivors, into d_bits (every word); *count (nullable) their number.
-// Synchronous.  Needs g.list and g.list2 for `connected`.
+// Synchronous.  Needs g.parent for `connected`.
 abcore_status scoped_set(Graph &g, int32_t vx, int32_t vy, int32_t thrU, int32_t thrL,
                          bool connected, uint32_t *d_bits, int64_t *count, hipStream_t s);
 // Largest deg0 over ids [lo, hi); set bits of a ceil(n/32)-word bitmask.

@@ -1620,10 +1620,7 @@ static abcore_status query_impl(Graph *g, abcore_edge_update upd, uint32_t alpha
   hipStream_t s = as_stream(stream);
   TRY(compute_components(*g, s));
   TRY(ensure_delta(*g, s));
-  if (d_set != nullptr && connected) {
-    TRY(ensure(&g->list, g->n));
-    TRY(ensure(&g->list2, g->n));
-  }
+  if (d_set != nullptr && connected) TRY(ensure(&g->parent, g->n));
   // 1. apply the update (validated on the device before any write)
   CHK(launch_init_state(*g, s));
   CHK(launch_update(*g, upd.u, upd.v, upd.op, g->delta.count, s));
@@ -1784,10 +1781,7 @@ abcore_status abcore_community(abcore_graph h, int32_t q, uint32_t alpha, uint32
   TRY(check_abort(*g));
   hipStream_t s = as_stream(stream);
   TRY(compute_components(*g, s));
-  if (connected) {
-    TRY(ensure(&g->list, g->n));
-    TRY(ensure(&g->list2, g->n));
-  }
+  if (connected) TRY(ensure(&g->parent, g->n));
   // Algorithm 1 on q's connected component only, as GFQ scopes its peel
   const int32_t thrU = clamp_thr(alpha), thrL = clamp_thr(beta);
   int64_t launches = 0;

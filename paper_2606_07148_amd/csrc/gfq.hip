@@ -49,9 +49,32 @@ __device__ void uf_union(int32_t *parent, int32_t a, int32_t b) {
   }
 }
 
-__device__ __forceinline__ bool in_scope(const int32_t *comp, int32_t label, int64_t x) {
-  return label < 0 || comp[x] == label;
-}
+// The vertices a search for connected parts covers: those labelled `label`
+// (all when it is negative; a row's live entries stay inside), or the members
+// of a bitmap (a row's entries are tested too).
+struct LabelScope {
+  const int32_t *comp;
+  int32_t label;
+  __device__ __forceinline__ bool in(int64_t x) const { return label < 0 || comp[x] == label; }
+  __device__ __forceinline__ bool near(int32_t w) const { return w >= 0; }
+  // a vertex at or after sample i of k, or -1
+  __device__ __forceinline__ int64_t sample(int i, int k, int64_t n) const {
+    const int64_t x = (n * i) / k;
+    return x < n && in(x) ? x : -1;
+  }
+};
+struct MemberScope {
+  const uint32_t *bits;
+  __device__ __forceinline__ bool in(int64_t x) const { return (bits[x >> 5] >> (x & 31)) & 1u; }
+  __device__ __forceinline__ bool near(int32_t w) const { return w >= 0 && in(w); }
+  // (members may be few: the first one in the 64 words from the sample on)
+  __device__ __forceinline__ int64_t sample(int i, int k, int64_t n) const {
+    const int64_t words = (n + 31) / 32, w0 = (words * i) / k;
+    for (int64_t w = w0; w < min(words, w0 + 64); ++w)
+      if (bits[w] != 0) return 32 * w + (__ffs((int)bits[w]) - 1);
+    return -1;
+  }
+};
 
 // Hooking phase: the first unions, without an atomic.  Every lower vertex
 // takes the first live entry of its row as parent (rows are ascending and
@@ -70,18 +93,19 @@ constexpr int kSampleLinks = 2;
 // Entries looked at for a live one; a vertex with none there stays a root.
 constexpr int kHookProbe = 16;
 
+template <class Scope>
 __global__ void uf_hook_lower_kernel(const int64_t *__restrict__ off,
-                                     const int32_t *__restrict__ cols, const int32_t *comp,
-                                     int32_t label, int32_t *parent, int64_t nU, int64_t n) {
+                                     const int32_t *__restrict__ cols, Scope scope,
+                                     int32_t *parent, int64_t nU, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
-    if (!in_scope(comp, label, x)) continue;
+    if (!scope.in(x)) continue;
     int32_t p = (int32_t)x;
     if (x >= nU) {
       const int64_t s = off[x], e = min(off[x + 1], s + kHookProbe);
       for (int64_t j = s; j < e; ++j) {
         const int32_t w = cols[j];
-        if (w >= 0) {
+        if (scope.near(w)) {
           p = w;
           break;
         }
@@ -91,18 +115,19 @@ __global__ void uf_hook_lower_kernel(const int64_t *__restrict__ off,
   }
 }
 
+template <class Scope>
 __global__ void uf_hook_upper_kernel(const int64_t *__restrict__ off,
-                                     const int32_t *__restrict__ cols, const int32_t *comp,
-                                     int32_t label, int32_t *parent, int64_t nU) {
+                                     const int32_t *__restrict__ cols, Scope scope,
+                                     int32_t *parent, int64_t nU) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < nU; x += stride) {
-    if (!in_scope(comp, label, x)) continue;
+    if (!scope.in(x)) continue;
     int32_t p = (int32_t)x;
     const int64_t s = off[x], e = min(off[x + 1], s + kHookProbe);
     int links = 0;
     for (int64_t j = s; j < e && links < kSampleLinks; ++j) {
       const int32_t w = cols[j];
-      if (w < 0) continue;
+      if (!scope.near(w)) continue;
       p = min(p, parent[w]);  // a lower vertex's, final since the last launch
       ++links;
     }
@@ -110,11 +135,11 @@ __global__ void uf_hook_upper_kernel(const int64_t *__restrict__ off,
   }
 }
 
-__global__ void uf_compress_kernel(int32_t *parent, const int32_t *comp, int32_t label,
-                                   int64_t n) {
+template <class Scope>
+__global__ void uf_compress_kernel(int32_t *parent, Scope scope, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride)
-    if (in_scope(comp, label, x)) astore(&parent[x], uf_find(parent, (int32_t)x));
+    if (scope.in(x)) astore(&parent[x], uf_find(parent, (int32_t)x));
 }
 
 // Merging phase: the roots at the two ends of two more edges of every upper
@@ -138,10 +163,10 @@ constexpr int kMergeBlock = 1024;
 constexpr int kMergeSlots = 2048;
 constexpr int kMergeEvery = 16;
 
-template <bool kFind>
+template <bool kFind, class Scope>
 __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
-    const int64_t *__restrict__ off, const int32_t *__restrict__ cols, const int32_t *comp,
-    int32_t label, int32_t *parent, int64_t nU) {
+    const int64_t *__restrict__ off, const int32_t *__restrict__ cols, Scope scope,
+    int32_t *parent, int64_t nU) {
   __shared__ int32_t key[kMergeSlots], low[kMergeSlots];
   for (int i = threadIdx.x; i < kMergeSlots; i += kMergeBlock) {
     key[i] = -1;
@@ -152,7 +177,7 @@ __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
   for (int64_t i = (int64_t)blockIdx.x * kMergeBlock + threadIdx.x;; i += stride) {
     const int64_t x = kFind ? i * kMergeEvery : i;
     if (x >= nU) break;
-    if (!in_scope(comp, label, x)) continue;
+    if (!scope.in(x)) continue;
     const int64_t s = off[x], d = off[x + 1] - s;
     if (d == 0) continue;
     const int32_t w[2] = {cols[s + d / 3], cols[s + 2 * d / 3]};
@@ -162,7 +187,7 @@ __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
     int32_t rw[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      rw[k] = w[k] < 0 ? rx : kFind ? uf_find(parent, w[k]) : parent[w[k]];
+      rw[k] = !scope.near(w[k]) ? rx : kFind ? uf_find(parent, w[k]) : parent[w[k]];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int32_t lo = min(rx, rw[k]), hi = max(rx, rw[k]);
@@ -191,15 +216,15 @@ __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
 // needs no host.
 constexpr int kRootSamples = 256;
 
+template <class Scope>
 __global__ __launch_bounds__(kRootSamples) void uf_big_root_kernel(const int32_t *parent,
-                                                                   const int32_t *comp,
-                                                                   int32_t label, int64_t n,
+                                                                   Scope scope, int64_t n,
                                                                    int32_t *big) {
   __shared__ __align__(16) int32_t roots[kRootSamples];
   __shared__ unsigned long long best;
   const int i = threadIdx.x;
-  const int64_t x = (n * i) / kRootSamples;
-  const int32_t mine = (x < n && in_scope(comp, label, x)) ? aload(&parent[x]) : -1;
+  const int64_t x = scope.sample(i, kRootSamples, n);
+  const int32_t mine = x >= 0 ? aload(&parent[x]) : -1;
   roots[i] = mine;
   if (i == 0) best = 0;
   __syncthreads();
@@ -218,9 +243,10 @@ __global__ __launch_bounds__(kRootSamples) void uf_big_root_kernel(const int32_t
 // Completion: every vertex in scope outside the tree of root `big` unites
 // with all of its neighbours (both layers' rows and inserted edges).  Edges
 // with both ends in that tree need nothing: they are joined already.
+template <class Scope>
 __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
-    const int64_t *__restrict__ off, const int32_t *__restrict__ cols, const int32_t *comp,
-    int32_t label, int32_t *parent, const int32_t *ins_head, const int32_t *ins_next,
+    const int64_t *__restrict__ off, const int32_t *__restrict__ cols, Scope scope,
+    int32_t *parent, const int32_t *ins_head, const int32_t *ins_next,
     const int32_t *ins_other, int64_t n, const int32_t *big_root) {
   const int32_t big = *big_root;
   const int gw = blockIdx.x * kWavesPerBlock + wave_in_block();
@@ -228,7 +254,7 @@ __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
   for (int64_t b = (int64_t)gw * kWave; b < n; b += (int64_t)nw * kWave) {
     const int64_t xi = b + lane_id();
     int32_t x = -1;
-    if (xi < n && in_scope(comp, label, xi) && (big < 0 || uf_find(parent, (int32_t)xi) != big))
+    if (xi < n && scope.in(xi) && (big < 0 || uf_find(parent, (int32_t)xi) != big))
       x = (int32_t)xi;
     int64_t s = 0;
     int d = 0;
@@ -257,13 +283,13 @@ __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
       const int64_t start = (int64_t)(((uint64_t)hi32 << 32) | lo32);
       if (k < total) {
         const int32_t w = cols[start + (kk - ex)];
-        if (w >= 0) uf_union(parent, owner, w);
+        if (scope.near(w)) uf_union(parent, owner, w);
       }
     }
     if (ins_head != nullptr && x >= 0) {
       for (int e = ins_head[x]; e >= 0; e = ins_next[e]) {
         const int32_t w = ins_other[e];
-        if (w >= 0) uf_union(parent, x, w);
+        if (scope.near(w)) uf_union(parent, x, w);
       }
     }
   }
@@ -272,7 +298,45 @@ __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
 __global__ void uf_label_kernel(int32_t *parent, int32_t *comp, int32_t label, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride)
-    if (in_scope(comp, label, x)) comp[x] = uf_find(parent, (int32_t)x);
+    if (LabelScope{comp, label}.in(x)) comp[x] = uf_find(parent, (int32_t)x);
+}
+
+// The members in the trees of vx and vy (each only if a member itself) into
+// bits, every word, and their number added to *count.
+__global__ __launch_bounds__(kBlock) void uf_reached_kernel(const uint32_t *__restrict__ member,
+                                                            int32_t *parent, int32_t vx,
+                                                            int32_t vy, int64_t n,
+                                                            uint32_t *__restrict__ bits,
+                                                            int64_t nwords,
+                                                            unsigned long long *count) {
+  const MemberScope scope{member};
+  // (a root is the vertex itself or smaller: -1 is no member's root)
+  const int32_t r1 = scope.in(vx) ? uf_find(parent, vx) : -1;
+  const int32_t r2 = scope.in(vy) ? uf_find(parent, vy) : -1;
+  const int64_t stride = (int64_t)gridDim.x * kBlock;
+  unsigned long long c = 0;
+  for (int64_t base = ((int64_t)blockIdx.x * kWavesPerBlock + wave_in_block()) * kWave;
+       base < nwords * 32; base += stride) {
+    const int64_t x = base + lane_id();
+    bool p = false;
+    if (x < n && scope.in(x)) {
+      const int32_t r = uf_find(parent, (int32_t)x);
+      p = r == r1 || r == r2;
+    }
+    const uint64_t mask = __ballot(p);
+    const int64_t w0 = base / 32;
+    if (lane_id() == 0) {
+      bits[w0] = (uint32_t)mask;
+      c += __popcll(mask);
+    }
+    if (lane_id() == 1 && w0 + 1 < nwords) bits[w0 + 1] = (uint32_t)(mask >> 32);
+  }
+  __shared__ unsigned long long s;
+  if (threadIdx.x == 0) s = 0;
+  __syncthreads();
+  if (c != 0) atomicAdd(&s, c);
+  __syncthreads();
+  if (threadIdx.x == 0 && s != 0) atomicAdd(count, s);
 }
 
 __global__ void relabel_kernel(int32_t *comp, int64_t n, int32_t from, int32_t to) {
@@ -720,32 +784,48 @@ int small_grid(const Graph &g, int64_t items) {
 
 }  // namespace
 
-// Component labels for the whole graph (label < 0) or re-labelling of the
-// vertices currently labelled `label` (deletion may split that component).
-// Stream-ordered; the root of the largest tree sits in the partial-sum
-// buffer (reset before every computation).
-hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
+// The forest of connected parts of a scope in g.parent: vertices of one part
+// have one root, the smallest id in it.  Stream-ordered; the root of the
+// largest tree sits in the partial-sum buffer (reset before every
+// computation).
+template <class Scope>
+static void launch_parts(Graph &g, Scope scope, hipStream_t s) {
   const int32_t *head = g.delta.count > 0 ? g.delta.head : nullptr;
   int32_t *d_big = reinterpret_cast<int32_t *>(g.part);
-  uf_hook_lower_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, g.comp, label, g.parent,
-                                                          g.nU, g.n);
-  uf_hook_upper_kernel<<<small_grid(g, g.nU), 256, 0, s>>>(g.off, g.cols, g.comp, label,
-                                                           g.parent, g.nU);
-  uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
+  uf_hook_lower_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, scope, g.parent, g.nU,
+                                                          g.n);
+  uf_hook_upper_kernel<<<small_grid(g, g.nU), 256, 0, s>>>(g.off, g.cols, scope, g.parent, g.nU);
+  uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, scope, g.n);
   auto merge_grid = [&](int64_t items) {
     return (int)std::max<int64_t>(
         1, std::min<int64_t>((items + kMergeBlock - 1) / kMergeBlock, g.cu_count));
   };
-  uf_merge_kernel<false><<<merge_grid(g.nU), kMergeBlock, 0, s>>>(g.off, g.cols, g.comp, label,
-                                                                  g.parent, g.nU);
+  uf_merge_kernel<false><<<merge_grid(g.nU), kMergeBlock, 0, s>>>(g.off, g.cols, scope, g.parent,
+                                                                  g.nU);
   uf_merge_kernel<true><<<merge_grid(g.nU / kMergeEvery + 1), kMergeBlock, 0, s>>>(
-      g.off, g.cols, g.comp, label, g.parent, g.nU);
-  uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
-  uf_big_root_kernel<<<1, kRootSamples, 0, s>>>(g.parent, g.comp, label, g.n, d_big);
-  uf_rest_link_kernel<<<wide_grid(g), kBlock, 0, s>>>(g.off, g.cols, g.comp, label, g.parent,
-                                                      head, g.delta.next, g.delta.other, g.n,
-                                                      d_big);
+      g.off, g.cols, scope, g.parent, g.nU);
+  uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, scope, g.n);
+  uf_big_root_kernel<<<1, kRootSamples, 0, s>>>(g.parent, scope, g.n, d_big);
+  uf_rest_link_kernel<<<wide_grid(g), kBlock, 0, s>>>(g.off, g.cols, scope, g.parent, head,
+                                                      g.delta.next, g.delta.other, g.n, d_big);
+}
+
+// Component labels for the whole graph (label < 0) or re-labelling of the
+// vertices currently labelled `label` (deletion may split that component).
+hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
+  launch_parts(g, LabelScope{g.comp, label}, s);
   uf_label_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
+  return hipGetLastError();
+}
+
+// The members (a bitmap) connected to vx or vy through members.  One forest of
+// all members' parts: a fixed number of launches, whatever the distances.
+hipError_t launch_reached(Graph &g, const uint32_t *member, int32_t vx, int32_t vy,
+                          uint32_t *bits, unsigned long long *count, hipStream_t s) {
+  const int64_t nwords = (g.n + 31) / 32;
+  launch_parts(g, MemberScope{member}, s);
+  uf_reached_kernel<<<small_grid(g, g.n), kBlock, 0, s>>>(member, g.parent, vx, vy, g.n, bits,
+                                                          nwords, count);
   return hipGetLastError();
 }
 

@@ -113,3 +113,29 @@ def test_export_after_updates(inserted):
     want = [nU + v for _, v in pairs] + [u for u, v in sorted(pairs, key=lambda e: (e[1], e[0]))]
     assert np.array_equal(cols, np.array(want, np.int32))
     g.destroy()
+
+
+@pytest.mark.parametrize("a,b", [(1, 1), (2, 1), (1, 2), (2, 2)])
+@pytest.mark.parametrize("name", ["path", "pairs", "stars", "sparse", "skewed", "edge"])
+def test_connected_part_of_a_core(name, a, b):
+    """The connected part of a core around members and non-members, on parts
+    of every size (long chains of members among them), before and after
+    deletions."""
+    nU, nL, eu, ev = _shape(name)
+    g = pkg.abcore_build_csr(nU, nL, to_dev(eu), to_dev(ev))
+    r = np.random.RandomState(8)
+    left = sorted(set(zip(eu.tolist(), ev.tolist())))
+    for step in range(2):
+        cur = np.array(left, np.int32).reshape(-1, 2)
+        ref = oracle.Graph(nU, nL, cur[:, 0].copy(), cur[:, 1].copy())
+        for q in [0, nU] + r.randint(0, nU + nL, 4).tolist():
+            say("connected part", name, a, b, q)
+            want = oracle.community(ref, q, a, b, True)
+            bits, size = pkg.abcore_community(g, q, a, b, connected=True)
+            w = oracle.pack(want)
+            assert np.array_equal(bits.cpu().numpy().view(np.uint32)[: len(w)], w), q
+            assert size == int(want.sum())
+        for u, v in left[1::97]:
+            pkg.abcore_query(g, u, v, -1, a, b)
+        left = [e for i, e in enumerate(left) if i % 97 != 1]
+    g.destroy()

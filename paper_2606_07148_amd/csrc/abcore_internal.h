@@ -110,9 +110,7 @@ struct PeelState {
   int32_t aux0, aux1;   // small results (uncertain count, labels, answer bits)
   int32_t pulled;       // first round ran in pull form
   int32_t abort_flag;   // a grid barrier exceeded its spin limit
-  int32_t dead;         // core decomposition: alive-list entries found removed by a scan
   int32_t live;         // core decomposition: live entries of the alive list after a scan
-  int32_t pad0;
   int64_t launches;     // launches that did work
   // arrival counters of the workspace reset only (never zeroed: that kernel
   // always completes, so they always return to zero)
@@ -130,6 +128,7 @@ enum PartField : int {
   kPartRest = 6,      // nested scan: entries of the rows that survive it
   kPartAliveU = 7,    // GCC scan: upper vertices that survive it
   kPartAliveL = 8,    // GCC scan: lower vertices that survive it
+  kPartDead = 9,      // core decomposition: list entries a scan found removed
   kPartFields = 10
 };
 

@@ -71,35 +71,67 @@ constexpr int kUnrollBlock = ABC_TOP_UNROLL_BLOCK;  // the same for those walks
 // of a target per row, far fewer rows than 65536 per workgroup and half)
 constexpr int kAgg = 2 * (kHalfBlock / kWave - 1) * (kFine + kCoarse);
 
+// Positions of this thread's `mine` items in two appends of the workgroup to
+// the lists counted by ctr[0] and ctr[1]: one atomic per list and workgroup
+// (same-address atomics queue at about 11 ns each: one per wave cost 0.27 ms
+// at 750,000 vertices).  s: 2 ints of LDS per wave and 2 more.  Whole
+// workgroup.
+template <int kWaves>
+__device__ __forceinline__ int2 block_append(int2 mine, int32_t *ctr, int (*s)[2]) {
+  const int i0 = wave_incl_scan(mine.x), i1 = wave_incl_scan(mine.y);
+  if (lane_id() == kWave - 1) {
+    s[wave_in_block()][0] = i0;
+    s[wave_in_block()][1] = i1;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    int total = 0;
+    for (int w = 0; w < kWaves; ++w) total += s[w][threadIdx.x];
+    s[kWaves][threadIdx.x] = total > 0 ? atomicAdd(&ctr[threadIdx.x], total) : 0;
+  }
+  __syncthreads();
+  int2 at = make_int2(s[kWaves][0] + i0 - mine.x, s[kWaves][1] + i1 - mine.y);
+  for (int w = 0; w < wave_in_block(); ++w) {
+    at.x += s[w][0];
+    at.y += s[w][1];
+  }
+  __syncthreads();  // the words are free again
+  return at;
+}
+
 // Live vertices of the alive list (core < 0) into hv and their bits into
 // live; count[0] receives their number, count[1] the number in the upper
-// layer.  One append counter increment per wave.
-__global__ __launch_bounds__(kBlock) void top_select_kernel(const int32_t *__restrict__ alive,
-                                                            int64_t cnt,
-                                                            const int32_t *__restrict__ core,
-                                                            int32_t nU, int32_t *__restrict__ hv,
-                                                            uint32_t *__restrict__ live,
-                                                            int32_t *count) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < cnt; base += stride) {
-    const int64_t i = base + threadIdx.x;
-    int32_t x = -1;
-    bool on = false;
-    if (i < cnt) {
-      x = alive[i];
-      on = core[x] < 0;
+// layer.
+constexpr int kListBlock = 1024;
+constexpr int kListWaves = kListBlock / kWave;
+constexpr int kListSpan = 4;  // entries per thread
+
+__global__ __launch_bounds__(kListBlock) void top_select_kernel(
+    const int32_t *__restrict__ alive, int64_t cnt, const int32_t *__restrict__ core, int32_t nU,
+    int32_t *__restrict__ hv, uint32_t *__restrict__ live, int32_t *count) {
+  __shared__ int s[kListWaves + 1][2];
+  const int64_t stride = (int64_t)gridDim.x * kListBlock * kListSpan;
+  for (int64_t base = (int64_t)blockIdx.x * kListBlock * kListSpan; base < cnt; base += stride) {
+    int32_t x[kListSpan], c[kListSpan];
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      const int64_t i = base + u * kListBlock + threadIdx.x;
+      x[u] = i < cnt ? alive[i] : -1;
     }
-    const uint64_t mask = __ballot(on);
-    const uint64_t upper = __ballot(on && x < nU);
-    int at = 0;
-    if (lane_id() == 0 && mask) {
-      at = atomicAdd(&count[0], (int)__popcll(mask));
-      if (upper) atomicAdd(&count[1], (int)__popcll(upper));
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) c[u] = x[u] >= 0 ? core[x[u]] : 0;
+    int2 mine = make_int2(0, 0);
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      mine.x += c[u] < 0 ? 1 : 0;
+      mine.y += c[u] < 0 && x[u] < nU ? 1 : 0;
     }
-    at = __shfl(at, 0, kWave);
-    if (on) {
-      hv[at + (int)__popcll(mask & lanemask_lt())] = x;
-      atomicOr(&live[x >> 5], 1u << (x & 31));
+    int at = block_append<kListWaves>(mine, count, s).x;
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      if (c[u] >= 0) continue;
+      hv[at++] = x[u];
+      atomicOr(&live[x[u] >> 5], 1u << (x[u] & 31));
     }
   }
 }
@@ -588,8 +620,16 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
   const int64_t n_short = a.len_in[0], n_long = a.len_in[1];
   if (blockIdx.x >= n_long && (int64_t)blockIdx.x * kHalfWaves >= n_short) return;  // idle
   const int kc = min(kCache, a.tgt_cnt);
-  for (int i = threadIdx.x; i < kc; i += blockDim.x)
-    cache[i] = (uint16_t)min(a.est[a.tgt_base + i] - a.k0, 65535);
+  // (kFill loads in flight per thread: the fill is most of a late half)
+  constexpr int kFill = 16;
+  for (int i0 = threadIdx.x; i0 < kc; i0 += kFill * kHalfBlock) {
+    int32_t v[kFill];
+#pragma unroll
+    for (int u = 0; u < kFill; ++u) v[u] = a.est[a.tgt_base + min(i0 + u * kHalfBlock, kc - 1)];
+#pragma unroll
+    for (int u = 0; u < kFill; ++u)
+      if (i0 + u * kHalfBlock < kc) cache[i0 + u * kHalfBlock] = (uint16_t)min(v[u] - a.k0, 65535);
+  }
   lds_barrier();
   const int32_t k0 = a.k0;
   // cached values are offsets from k0 saturated at 65535: exact for every
@@ -738,32 +778,44 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
 // are due (c(x) < est(x); c starts at 0, so the first half of each layer
 // takes all), short rows from the front of the layer's buffer, long rows
 // from its back; len[0] and len[1] receive their numbers.
-__global__ __launch_bounds__(kBlock) void top_due_kernel(const int32_t *__restrict__ est,
-                                                         const int32_t *__restrict__ cnt,
-                                                         const int32_t *__restrict__ hlen,
-                                                         int32_t base, int32_t count,
-                                                         int32_t *__restrict__ list,
-                                                         int32_t *len) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t o = (int64_t)blockIdx.x * blockDim.x; o < count; o += stride) {
-    const int64_t i = o + threadIdx.x;
-    const int32_t j = base + (int32_t)i;
-    const bool due = i < count && cnt[j] < est[j];
-    const bool lg = due && hlen[j] > kLongRow;
-    const uint64_t ms = __ballot(due && !lg), ml = __ballot(lg);
-    int bs = 0, bl = 0;
-    if (lane_id() == 0) {
-      if (ms) bs = atomicAdd(&len[0], (int)__popcll(ms));
-      if (ml) bl = atomicAdd(&len[1], (int)__popcll(ml));
+__global__ __launch_bounds__(kListBlock) void top_due_kernel(const int32_t *__restrict__ est,
+                                                             const int32_t *__restrict__ cnt,
+                                                             const int32_t *__restrict__ hlen,
+                                                             int32_t base, int32_t count,
+                                                             int32_t *__restrict__ list,
+                                                             int32_t *len) {
+  __shared__ int s[kListWaves + 1][2];
+  const int64_t stride = (int64_t)gridDim.x * kListBlock * kListSpan;
+  for (int64_t o = (int64_t)blockIdx.x * kListBlock * kListSpan; o < count; o += stride) {
+    int32_t c[kListSpan], e[kListSpan];
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      const int64_t i = o + u * kListBlock + threadIdx.x;
+      c[u] = i < count ? cnt[base + i] : 0;
+      e[u] = i < count ? est[base + i] : 0;
     }
-    bs = __shfl(bs, 0, kWave);
-    bl = __shfl(bl, 0, kWave);
-    if (due) {
+    int2 mine = make_int2(0, 0);
+    uint32_t lg = 0;
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      if (c[u] >= e[u]) continue;
+      if (hlen[base + o + u * kListBlock + threadIdx.x] > kLongRow) {
+        lg |= 1u << u;
+        ++mine.y;
+      } else {
+        ++mine.x;
+      }
+    }
+    int2 at = block_append<kListWaves>(mine, len, s);
+#pragma unroll
+    for (int u = 0; u < kListSpan; ++u) {
+      if (c[u] >= e[u]) continue;
+      const int32_t j = base + (int32_t)(o + u * kListBlock + threadIdx.x);
       // the two ends never meet: at most count vertices are due
-      if (lg)
-        list[count - 1 - (bl + (int)__popcll(ml & lanemask_lt()))] = j;
+      if ((lg >> u) & 1u)
+        list[count - 1 - at.y++] = j;
       else
-        list[bs + (int)__popcll(ms & lanemask_lt())] = j;
+        list[at.x++] = j;
     }
   }
 }
@@ -863,8 +915,8 @@ abcore_status kcore_top(Graph &g, const int32_t *alive, int64_t cnt, int32_t k0,
         !ok(hipMemsetAsync(live, 0, sizeof(uint32_t) * std::max<int64_t>(words, 1), s)))
       break;
     if (cnt > 0) {
-      top_select_kernel<<<grid_of(g, cnt, kBlock), kBlock, 0, s>>>(alive, cnt, g.core, g.nU,
-                                                                   hv, live, ctr);
+      top_select_kernel<<<grid_of(g, cnt, kListBlock * kListSpan), kListBlock, 0, s>>>(
+          alive, cnt, g.core, g.nU, hv, live, ctr);
       if (!ok(hipGetLastError())) break;
     }
     if (!ok(hipMemcpyAsync(hc, ctr, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, s)) ||
@@ -967,7 +1019,7 @@ abcore_status kcore_top(Graph &g, const int32_t *alive, int64_t cnt, int32_t k0,
       for (int r = 0; r < halves_per_check && t < max_halves; ++r, ++t) {
         const bool upper = (t % 2) == 0;
         const int32_t self_base = upper ? 0 : hU, self_cnt = upper ? hU : hL;
-        top_due_kernel<<<grid_of(g, self_cnt, kBlock), kBlock, 0, s>>>(
+        top_due_kernel<<<grid_of(g, self_cnt, kListBlock * kListSpan), kListBlock, 0, s>>>(
             est, cntv, hlen, self_base, self_cnt, lists + self_base, list_len + 2 * t);
         HalfArgs a{};
         a.hoff = hoff;
@@ -1016,7 +1068,9 @@ abcore_status kcore_top(Graph &g, const int32_t *alive, int64_t cnt, int32_t k0,
     int32_t *dmax = ctr + 3;
     int32_t hmax = 0;
     if (h > 0) {
-      top_write_kernel<<<grid_of(g, h, kBlock), kBlock, 0, s>>>(hv, est, h, g.core, dmax);
+      // (one same-address maximum per workgroup: few of them)
+      top_write_kernel<<<std::min(grid_of(g, h, kBlock), g.cu_count), kBlock, 0, s>>>(
+          hv, est, h, g.core, dmax);
       if (!ok(hipGetLastError())) break;
     }
     if (!ok(hipMemcpyAsync(&hmax, dmax, sizeof(int32_t), hipMemcpyDeviceToHost, s)) ||

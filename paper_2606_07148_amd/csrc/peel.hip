@@ -2737,21 +2737,47 @@ __global__ __launch_bounds__(kScanBlock) void kcore_level_scan_kernel(PeelArgs a
     atomicAdd(&s_dead, dead_here);
   }
   __syncthreads();
-  if (!compact && threadIdx.x == 0 && s_kept > 0) atomicAdd(&st->kept, s_kept);
-  if (threadIdx.x == 0 && s_dead > 0) atomicAdd(&st->dead, s_dead);
-  if (threadIdx.x == 0) a.part[(int64_t)blockIdx.x * kPartFields + kPartMin] = s_min;
+  // this workgroup's counts, in its own slots: counters shared by all of
+  // them took one atomic each, which queued (20 us of a scan of any length)
+  const int active = (int)min((int64_t)gridDim.x, ((int64_t)cur + kScanChunk - 1) / kScanChunk);
+  if (threadIdx.x == 0 && (int)blockIdx.x < active) {
+    int64_t *slot = a.part + (int64_t)blockIdx.x * kPartFields;
+    st_agent(reinterpret_cast<int32_t *>(&slot[kPartMin]), s_min);
+    st_agent(reinterpret_cast<int32_t *>(&slot[kPartKept]), s_kept);
+    st_agent(reinterpret_cast<int32_t *>(&slot[kPartDead]), s_dead);
+    __builtin_amdgcn_s_waitcnt(0);  // written before this thread's arrival
+  }
   if (last_block_done<false>(st)) {
     const int lane = lane_id();
     int32_t after = 0;
     if (lane < kSub) after = phys_tail(st, lane, a.qcap) - ld_agent(&st->hi[lane]);
     after = wave_sum(after);
-    const int32_t gmin =
-        (int32_t)wave_min_strided(a.part + kPartMin, (int)gridDim.x, kPartFields, 0x7FFFFFFF);
+    int32_t gmin = 0x7FFFFFFF, sum_kept = 0, dead_n = 0;
+    constexpr int kU = 4;
+    for (int i0 = lane; i0 < active; i0 += kU * kWave) {
+      int32_t v[kU][3];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        int64_t *slot = a.part + (int64_t)min(i0 + u * kWave, active - 1) * kPartFields;
+        v[u][0] = ld_agent(reinterpret_cast<int32_t *>(&slot[kPartMin]));
+        v[u][1] = ld_agent(reinterpret_cast<int32_t *>(&slot[kPartKept]));
+        v[u][2] = ld_agent(reinterpret_cast<int32_t *>(&slot[kPartDead]));
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        if (i0 + u * kWave >= active) continue;
+        gmin = min(gmin, v[u][0]);
+        sum_kept += v[u][1];
+        dead_n += v[u][2];
+      }
+    }
+    gmin = wave_min(gmin);
+    sum_kept = wave_sum(sum_kept);
+    dead_n = wave_sum(dead_n);
     advance_round_wave(st, a.qcap);  // the queued vertices start the level's peel
     if (lane < kGroups) st->fin[lane][0] = 0;  // the level's peel detects its own end
     if (lane == 0) {
-      const int32_t kept_n = ld_agent(&st->kept);  // live entries
-      const int32_t dead_n = ld_agent(&st->dead);
+      const int32_t kept_n = sum_kept;  // live entries
       st->k = kn;
       if (after > 0) st->max_core = kn;
       st->next_k = after > 0 ? kn + 1 : max(kn + 1, gmin);
@@ -2764,7 +2790,6 @@ __global__ __launch_bounds__(kScanBlock) void kcore_level_scan_kernel(PeelArgs a
       st->compact = (int64_t)(compact ? 0 : dead_n) * 4 > len ? 1 : 0;
       st->live = kept_n;
       st->kept = 0;
-      st->dead = 0;
       if (kept_n == 0) st->done = 1;
       atomicAdd((unsigned long long *)&st->launches, 1ull);
     }

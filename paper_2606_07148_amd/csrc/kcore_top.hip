@@ -67,9 +67,9 @@ constexpr int kUnroll = ABC_TOP_UNROLL;             // row entries in flight per
 constexpr int kLongRow = ABC_TOP_LONG_ROW;          // longer rows: walked by a whole workgroup
 constexpr int kUnrollBlock = ABC_TOP_UNROLL_BLOCK;  // the same for those walks
 // summed decrement targets: 16-bit sums, two to a word, in the bins of
-// waves 1..15 (a sum counts rows of one workgroup: at most one decrement
+// waves 2..15 (a sum counts rows of one workgroup: at most one decrement
 // of a target per row, far fewer rows than 65536 per workgroup and half)
-constexpr int kAgg = 2 * (kHalfBlock / kWave - 1) * (kFine + kCoarse);
+constexpr int kAgg = 2 * (kHalfBlock / kWave - 2) * (kFine + kCoarse);
 
 // Positions of this thread's `mine` items in two appends of the workgroup to
 // the lists counted by ctr[0] and ctr[1]: one atomic per list and workgroup
@@ -381,6 +381,7 @@ struct HalfArgs {
   int32_t cap_in;
   int propagate;  // lowered vertices decrement their neighbours' counts
   int spec;       // every listed vertex is due (it drops): see hindex_wave
+  int narrow;     // most drops are short: see Pass
 };
 
 #ifndef ABC_TOP_LDS_BARRIER
@@ -428,28 +429,34 @@ __device__ __forceinline__ void uncount(const Dec &dec, int32_t w, int32_t v, in
 
 // One pass of the binned h-index search over [lo, hi]: values above hi are
 // counted, the kFine integers just below hi get one bin each, the rest of
-// the range [lo, fine_lo) kCoarse equal-width bins.
+// the range [lo, fine_lo) kCoarse bins of 2^shift values each (a shift: the
+// division by an arbitrary width was a third of a pass).  A narrow pass
+// leaves the coarse bins out: past the first halves most drops are short and
+// most values lie far below them, crowding into a few coarse bins.
 struct Pass {
-  int32_t lo, hi, fine_lo, width;
+  int32_t lo, hi, fine_lo;
+  int shift;
   int nb;
 };
 
-__device__ __forceinline__ Pass pass_of(int32_t lo, int32_t hi) {
+__device__ __forceinline__ Pass pass_of(int32_t lo, int32_t hi, bool narrow) {
   Pass p;
   p.lo = lo;
   p.hi = hi;
   p.fine_lo = max(lo, hi - kFine + 1);
-  const int64_t nco = (int64_t)p.fine_lo - lo;
-  p.width = nco > 0 ? (int32_t)((nco + kCoarse - 1) / kCoarse) : 1;
-  p.nb = nco > 0 ? (int)((nco + p.width - 1) / p.width) : 0;
+  const uint32_t nco = (uint32_t)(p.fine_lo - lo);
+  // the smallest shift with nco >> shift < kCoarse (kCoarse = 2^8)
+  p.shift = nco > 0 ? max(0, 32 - (int)__builtin_clz(nco) - 8) : 0;
+  p.nb = nco > 0 && !narrow ? (int)((nco - 1) >> p.shift) + 1 : 0;
   return p;
 }
+static_assert(kCoarse == 256, "shift of the coarse bins");
 
 __device__ __forceinline__ void bin_value(const Pass &p, int32_t v, uint32_t *bins) {
   if (v <= p.hi && v >= p.fine_lo)
     atomicAdd(&bins[v - p.fine_lo], 1u);
-  else if (v < p.fine_lo && v >= p.lo)
-    atomicAdd(&bins[kFine + (v - p.lo) / p.width], 1u);
+  else if (p.nb > 0 && v < p.fine_lo && v >= p.lo)
+    atomicAdd(&bins[kFine + ((v - p.lo) >> p.shift)], 1u);
 }
 
 // After a pass (one wave): true and *res = the largest h in [lo, hi] with
@@ -457,21 +464,21 @@ __device__ __forceinline__ void bin_value(const Pass &p, int32_t v, uint32_t *bi
 // highest coarse bin whose lower edge e has count_ge(e) >= e: the answer's
 // range [*res, *nhi] for the next pass (count_ge(lo) >= lo must hold, which
 // makes some bin qualify).  *c receives count_ge(*res).
-__device__ bool scan_bins(const Pass &p, const uint32_t *bins, int64_t above, int32_t *res,
-                          int32_t *nhi, int64_t *c) {
+__device__ bool scan_bins(const Pass &p, const uint32_t *bins, int32_t above, int32_t *res,
+                          int32_t *nhi, int32_t *c) {
   const uint32_t *fine = bins, *coarse = bins + kFine;
   // unit bins from hi down: lane L at t = top - L; counts by an inclusive
   // wave scan; the first t (from the top) with count >= t wins
-  int64_t acc = above;
+  int32_t acc = above;
   for (int32_t top = p.hi; top >= p.fine_lo; top -= kWave) {
     const int32_t t = top - lane_id();
-    int64_t incl = t >= p.fine_lo ? (int64_t)fine[t - p.fine_lo] : 0;
+    int32_t incl = t >= p.fine_lo ? (int32_t)fine[t - p.fine_lo] : 0;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-      const int64_t y = __shfl_up(incl, o, kWave);
+      const int32_t y = __shfl_up(incl, o, kWave);
       if (lane_id() >= o) incl += y;
     }
-    const uint64_t ok = __ballot(t >= p.fine_lo && acc + incl >= (int64_t)t);
+    const uint64_t ok = __ballot(t >= p.fine_lo && acc + incl >= t);
     if (ok) {
       const int l = __ffsll((unsigned long long)ok) - 1;
       *res = top - l;
@@ -481,46 +488,50 @@ __device__ bool scan_bins(const Pass &p, const uint32_t *bins, int64_t above, in
     }
     acc += __shfl(incl, kWave - 1, kWave);
   }
-  // coarse bins from the top: bin i covers [lo + i * width, lo + (i + 1) * width)
+  // coarse bins from the top: bin i covers 2^shift values from lo + (i << shift)
   for (int topb = p.nb - 1; topb >= 0; topb -= kWave) {
     const int bi = topb - lane_id();
-    int64_t incl = bi >= 0 ? (int64_t)coarse[bi] : 0;
+    int32_t incl = bi >= 0 ? (int32_t)coarse[bi] : 0;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
-      const int64_t y = __shfl_up(incl, o, kWave);
+      const int32_t y = __shfl_up(incl, o, kWave);
       if (lane_id() >= o) incl += y;
     }
-    const int64_t edge = (int64_t)p.lo + (int64_t)bi * p.width;
+    const int32_t edge = p.lo + (int32_t)((uint32_t)bi << p.shift);
     const uint64_t ok = __ballot(bi >= 0 && acc + incl >= edge);
     if (ok) {
       const int l = __ffsll((unsigned long long)ok) - 1;
-      *res = p.lo + (topb - l) * p.width;
-      *nhi = min(*res + p.width - 1, p.fine_lo - 1);
+      *res = p.lo + (int32_t)((uint32_t)(topb - l) << p.shift);
+      *nhi = (int32_t)min((int64_t)*res + (1ll << p.shift) - 1, (int64_t)p.fine_lo - 1);
       *c = acc + __shfl(incl, l, kWave);
       return *res == *nhi;
     }
     acc += __shfl(incl, kWave - 1, kWave);
   }
-  *res = p.lo;  // not reached while count_ge(lo) >= lo
-  *nhi = p.lo;
+  // a narrow pass: the answer lies below its bins (otherwise not reached
+  // while count_ge(lo) >= lo)
+  const bool below = p.nb == 0 && p.fine_lo > p.lo;
+  *res = p.lo;
+  *nhi = below ? p.fine_lo - 1 : p.lo;
   *c = acc;
-  return true;
+  return !below;
 }
 
 // The search for a row walked by one wave, in passes that reread the row.
-// Two passes cover ranges up to kFine + kFine * kCoarse; more take more.
+// Two passes cover ranges up to kFine + kFine * kCoarse; more take more (and
+// one more after a narrow pass that did not reach).
 // spec (a vertex known to drop, below cur = hi): the first pass already
 // takes it out of the counts of its neighbours valued exactly cur.
 template <class V>
-__device__ int32_t hindex_wave(const int32_t *__restrict__ hcols, int64_t b, int64_t e,
-                               int32_t lo, int32_t hi, uint32_t *bins, V val, int64_t *c,
-                               const Dec *spec) {
+__device__ __forceinline__ int32_t hindex_wave(const int32_t *__restrict__ hcols, int64_t b, int64_t e,
+                               int32_t lo, int32_t hi, uint32_t *bins, V val, int32_t *c,
+                               const Dec &dec, bool spec, bool narrow) {
   const int32_t cur = hi;
   for (bool first = true;; first = false) {
-    const Pass p = pass_of(lo, hi);
+    const Pass p = pass_of(lo, hi, first && narrow);
     for (int i = lane_id(); i < kFine + kCoarse; i += kWave) bins[i] = 0;
     __builtin_amdgcn_wave_barrier();
-    int64_t above = 0;
+    int32_t above = 0;
     for (int64_t k0i = b; k0i < e; k0i += (int64_t)kUnroll * kWave) {
       int32_t w[kUnroll], v[kUnroll];
 #pragma unroll
@@ -532,9 +543,9 @@ __device__ int32_t hindex_wave(const int32_t *__restrict__ hcols, int64_t b, int
       for (int u = 0; u < kUnroll; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        above += (int64_t)__popcll(__ballot(v[u] > p.hi));
+        above += (int32_t)__popcll(__ballot(v[u] > p.hi));
         bin_value(p, v[u], bins);
-        if (first && spec != nullptr && v[u] == cur) (*spec)(w[u]);
+        if (first && spec && v[u] == cur) dec(w[u]);
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -548,77 +559,89 @@ __device__ int32_t hindex_wave(const int32_t *__restrict__ hcols, int64_t b, int
 }
 
 struct BlockShared {
-  uint32_t above;
-  int32_t res, nhi;
+  uint32_t above[2];
+  int32_t res, nhi, c;
   int exact;
-  int64_t c;
 };
 
-// The same search for a long row walked by the whole workgroup (bins shared
-// by its waves, scanned by wave 0; spec as above).  Every thread calls it.
-template <class V>
-__device__ int32_t hindex_block(const int32_t *__restrict__ hcols, int64_t b, int64_t e,
-                                int32_t lo, int32_t hi, uint32_t *bins, BlockShared &sh, V val,
-                                int64_t *c, const Dec *spec) {
+// The same search for a row walked by the whole workgroup (spec as above):
+// each(f) calls f(entry, value) for every slot of the row, the same number
+// of times in every lane.  bins[*turn] and sh.above[*turn] are zero on entry;
+// wave 0 scans them while the other waves zero the other pair for the next
+// pass or row, so a pass has two barriers.  Every thread calls it.
+template <class Each>
+__device__ __forceinline__ int32_t hindex_block(const Each &each, int32_t lo, int32_t hi,
+                                                uint32_t (*bins)[kFine + kCoarse], int *turn,
+                                                BlockShared &sh, int32_t *c, const Dec &dec,
+                                                bool spec, bool narrow) {
   const int32_t cur = hi;
   for (bool first = true;; first = false) {
-    const Pass p = pass_of(lo, hi);
-    for (int i = threadIdx.x; i < kFine + kCoarse; i += blockDim.x) bins[i] = 0;
-    if (threadIdx.x == 0) sh.above = 0;
-    lds_barrier();
+    const Pass p = pass_of(lo, hi, first && narrow);
+    const int k = *turn;
     uint32_t above = 0;
-    for (int64_t k0i = b; k0i < e; k0i += (int64_t)kUnrollBlock * kHalfBlock) {
-      int32_t w[kUnrollBlock], v[kUnrollBlock];
-#pragma unroll
-      for (int u = 0; u < kUnrollBlock; ++u) {
-        const int64_t k = k0i + u * kHalfBlock + threadIdx.x;
-        w[u] = k < e ? hcols[k] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < kUnrollBlock; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
-#pragma unroll
-      for (int u = 0; u < kUnrollBlock; ++u) {
-        above += (uint32_t)__popcll(__ballot(v[u] > p.hi));
-        bin_value(p, v[u], bins);
-        if (first && spec != nullptr && v[u] == cur) (*spec)(w[u]);
-      }
-    }
-    if (lane_id() == 0 && above) atomicAdd(&sh.above, above);
+    each([&](int32_t w, int32_t v) {
+      above += (uint32_t)__popcll(__ballot(v > p.hi));
+      bin_value(p, v, bins[k]);
+      if (first && spec && v == cur) dec(w);
+    });
+    if (lane_id() == 0 && above) atomicAdd(&sh.above[k], above);
     lds_barrier();
     if (wave_in_block() == 0) {
-      int32_t res, nhi;
-      int64_t cc;
-      const bool exact = scan_bins(p, bins, (int64_t)sh.above, &res, &nhi, &cc);
+      int32_t res, nhi, cc;
+      const bool exact = scan_bins(p, bins[k], (int32_t)sh.above[k], &res, &nhi, &cc);
       if (lane_id() == 0) {
         sh.res = res;
         sh.nhi = nhi;
         sh.exact = exact;
         sh.c = cc;
       }
+    } else {
+      for (int i = threadIdx.x - kWave; i < kFine + kCoarse; i += kHalfBlock - kWave)
+        bins[k ^ 1][i] = 0;
+      if (threadIdx.x == kWave) sh.above[k ^ 1] = 0;
     }
+    *turn = k ^ 1;
     lds_barrier();
-    const bool exact = sh.exact != 0;
-    const int32_t res = sh.res, nhi = sh.nhi;
-    const int64_t cc = sh.c;
-    lds_barrier();  // the next pass rewrites the shared words
-    if (exact) {
-      *c = cc;
-      return res;
+    lo = sh.res;
+    hi = sh.nhi;
+    if (sh.exact != 0) {
+      *c = sh.c;
+      return lo;
     }
-    lo = res;
-    hi = nhi;
   }
 }
 
 // One half sweep (see the file comment).  One workgroup per compute unit
-// (the LDS holds the value cache and the bins): first the long rows, one
-// per workgroup at a time, then the others, one per wave.
+// (the LDS holds the value cache and the bins).  Rows of more than kLongRow
+// entries are walked one per workgroup at a time, the others one per wave, or
+// up to kTiny at a time where they have at most 64 entries.
+//
+// A late half lowers a few hundred long rows and a handful of others, and is
+// bound by the rows' chains of dependent steps, not by their entries: rows of
+// up to kKeep x 1024 entries are read once and kept in registers for every
+// pass, long rows are dealt to the workgroups in alternating order (the list
+// is longest first), and when no more than two short rows per workgroup are
+// due they are walked like the long ones, since a single wave takes 25 us
+// over a row of 2,000 entries.  At 2e7 edges (700 long rows) such a half went
+// from 79 to 43 us, at 2e8 (2,500) from 141 to 115.
+constexpr int kNarrowFrom = 4;  // first half with narrow passes
+constexpr int kKeep = 8;   // entries per thread of a row kept in registers
+constexpr int kTiny = 8;   // rows of at most 64 entries that a wave takes at once
+
 __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
   __shared__ uint16_t cache[kCache];
   __shared__ uint32_t s_bins[kHalfWaves][kFine + kCoarse];
   __shared__ BlockShared sh;
-  const int64_t n_short = a.len_in[0], n_long = a.len_in[1];
-  if (blockIdx.x >= n_long && (int64_t)blockIdx.x * kHalfWaves >= n_short) return;  // idle
+  const int G = (int)gridDim.x, me = (int)blockIdx.x;
+  const int64_t n_long = a.len_in[1];
+  const bool few = a.len_in[0] <= 2 * G;  // short rows: one per workgroup too
+  const int64_t n_block = n_long + (few ? a.len_in[0] : 0);
+  const int64_t n_wave = few ? 0 : a.len_in[0];
+  // waves take the short rows from the last workgroup on (the first ones
+  // hold the longest rows), in groups of `per`
+  const int64_t nw = (int64_t)G * kHalfWaves;
+  const int per = (int)min((int64_t)kTiny, (n_wave + nw - 1) / nw);
+  if (me >= n_block && (int64_t)(G - 1 - me) * per >= n_wave) return;  // idle
   const int kc = min(kCache, a.tgt_cnt);
   // (kFill loads in flight per thread: the fill is most of a late half)
   constexpr int kFill = 16;
@@ -630,7 +653,6 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
     for (int u = 0; u < kFill; ++u)
       if (i0 + u * kHalfBlock < kc) cache[i0 + u * kHalfBlock] = (uint16_t)min(v[u] - a.k0, 65535);
   }
-  lds_barrier();
   const int32_t k0 = a.k0;
   // cached values are offsets from k0 saturated at 65535: exact for every
   // comparison with thresholds <= cur while cur - k0 < 65535
@@ -641,62 +663,88 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
       return r < (uint32_t)kcr ? (int32_t)cache[r] + k0 : a.est[w];
     };
   };
-  // long rows: decrements of the first kAgg ids summed in the bins of
-  // waves 1.. (wave 0's bins serve the search), flushed before the short rows
-  const bool have_long = blockIdx.x < n_long;
-  uint32_t *agg = s_bins[1];
+  // rows of the whole workgroup: decrements of the first kAgg ids summed in
+  // the bins of waves 2.. (those of waves 0 and 1 serve the search), flushed
+  // before the other rows
+  const bool have_block = me < n_block;
+  uint32_t *agg = s_bins[2];
   // (a 16-bit sum cannot wrap: at most 65535 rows per workgroup, else no sums)
-  const int nagg = n_long <= (int64_t)65535 * gridDim.x ? min(kAgg, a.tgt_cnt) : 0;
-  if (have_long) {
-    for (int i = threadIdx.x; i < (nagg + 1) / 2; i += blockDim.x) agg[i] = 0;
-    lds_barrier();
+  const int nagg = n_block <= (int64_t)65535 * G ? min(kAgg, a.tgt_cnt) : 0;
+  if (have_block) {
+    for (int i = threadIdx.x; i < (nagg + 1) / 2; i += kHalfBlock) agg[i] = 0;
+    for (int i = threadIdx.x; i < 2 * (kFine + kCoarse); i += kHalfBlock) s_bins[0][i] = 0;
+    if (threadIdx.x < 2) sh.above[threadIdx.x] = 0;
   }
-  const Dec dec_long{a.cnt, a.tgt_base, agg, nagg};
-  const Dec dec_short{a.cnt, a.tgt_base, nullptr, 0};
+  lds_barrier();
+  const Dec dec_block{a.cnt, a.tgt_base, agg, nagg};
+  const Dec dec_wave{a.cnt, a.tgt_base, nullptr, 0};
   // a row's vertex, value and extent are loaded one row ahead (the vertex
   // two ahead), off the chain of dependent loads of the row in hand
-  auto long_vertex = [&](int64_t i) { return i < n_long ? a.q_in[a.cap_in - 1 - i] : 0; };
-  const int64_t step = gridDim.x;
-  int32_t x_next = long_vertex(blockIdx.x);
-  int32_t x_after = long_vertex(blockIdx.x + step);
+  auto turn_row = [&](int64_t r) { return r * G + ((r & 1) ? G - 1 - me : me); };
+  auto block_vertex = [&](int64_t r) {
+    const int64_t i = turn_row(r);
+    return i < n_long ? a.q_in[a.cap_in - 1 - i] : i < n_block ? a.q_in[i - n_long] : 0;
+  };
+  int32_t x_next = block_vertex(0);
+  int32_t x_after = block_vertex(1);
   int32_t cur_next = a.est[x_next];
   int64_t b_next = a.hoff[x_next], d_next = a.hlen[x_next];
-  for (int64_t i = blockIdx.x; i < n_long; i += step) {
+  int turn = 0;
+  for (int64_t r = 0; turn_row(r) < n_block; ++r) {
     const int32_t x = x_next, cur = cur_next;
     const int64_t b = b_next, e = b + d_next;
     x_next = x_after;
-    x_after = long_vertex(i + 2 * step);
+    x_after = block_vertex(r + 2);
     cur_next = a.est[x_next];
     b_next = a.hoff[x_next];
     d_next = a.hlen[x_next];
     const auto val = make_val(cur);
-    int64_t c = 0;
-    const Dec *spec = a.spec ? &dec_long : nullptr;
-    const int32_t h = hindex_block(a.hcols, b, e, k0, cur, s_bins[0], sh, val, &c, spec);
+    int32_t c = 0, h;
     // the neighbours valued cur are done if the first pass took them out
-    const int32_t top = spec ? cur - 1 : cur;
-    if (a.propagate && h < top) {
-      for (int64_t k0i = b; k0i < e; k0i += (int64_t)kUnrollBlock * kHalfBlock) {
-        int32_t w[kUnrollBlock], v[kUnrollBlock];
+    const int32_t top = a.spec ? cur - 1 : cur;
+    if (e - b <= (int64_t)kKeep * kHalfBlock) {
+      int32_t w[kKeep], v[kKeep];
 #pragma unroll
-        for (int u = 0; u < kUnrollBlock; ++u) {
-          const int64_t k = k0i + u * kHalfBlock + threadIdx.x;
-          w[u] = k < e ? a.hcols[k] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < kUnrollBlock; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
-#pragma unroll
-        for (int u = 0; u < kUnrollBlock; ++u) uncount(dec_long, w[u], v[u], top, h);
+      for (int u = 0; u < kKeep; ++u) {
+        const int64_t k = b + u * kHalfBlock + threadIdx.x;
+        w[u] = k < e ? a.hcols[k] : -1;
       }
+#pragma unroll
+      for (int u = 0; u < kKeep; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
+      auto each = [&](auto f) {
+#pragma unroll
+        for (int u = 0; u < kKeep; ++u) f(w[u], v[u]);
+      };
+      h = hindex_block(each, k0, cur, s_bins, &turn, sh, &c, dec_block, a.spec != 0, a.narrow != 0);
+      if (a.propagate && h < top)
+        each([&](int32_t ww, int32_t vv) { uncount(dec_block, ww, vv, top, h); });
+    } else {
+      auto each = [&](auto f) {
+        for (int64_t k0i = b; k0i < e; k0i += (int64_t)kUnrollBlock * kHalfBlock) {
+          int32_t w[kUnrollBlock], v[kUnrollBlock];
+#pragma unroll
+          for (int u = 0; u < kUnrollBlock; ++u) {
+            const int64_t k = k0i + u * kHalfBlock + threadIdx.x;
+            w[u] = k < e ? a.hcols[k] : -1;
+          }
+#pragma unroll
+          for (int u = 0; u < kUnrollBlock; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
+#pragma unroll
+          for (int u = 0; u < kUnrollBlock; ++u) f(w[u], v[u]);
+        }
+      };
+      h = hindex_block(each, k0, cur, s_bins, &turn, sh, &c, dec_block, a.spec != 0, a.narrow != 0);
+      if (a.propagate && h < top)
+        each([&](int32_t ww, int32_t vv) { uncount(dec_block, ww, vv, top, h); });
     }
     if (threadIdx.x == 0) {
-      a.cnt[x] = (int32_t)min<int64_t>(c, 0x7FFFFFFF);
+      a.cnt[x] = c;
       if (h < cur) a.est[x] = h;
     }
   }
-  if (have_long) {
+  if (have_block) {
     lds_barrier();
-    for (int i = threadIdx.x; i < nagg; i += blockDim.x) {
+    for (int i = threadIdx.x; i < nagg; i += kHalfBlock) {
       const uint32_t sum = (agg[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu;
       if (sum != 0)
         (void)__hip_atomic_fetch_add(&a.cnt[a.tgt_base + i], -(int32_t)sum, __ATOMIC_RELAXED,
@@ -705,15 +753,12 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
     lds_barrier();  // the short rows' bins reuse the sums' words
   }
   uint32_t *bins = s_bins[wave_in_block()];
-  const int64_t nw = (int64_t)gridDim.x * kHalfWaves;
-  for (int64_t i = (int64_t)blockIdx.x * kHalfWaves + wave_in_block(); i < n_short; i += nw) {
-    const int32_t x = a.q_in[i];
-    const int32_t cur = a.est[x];
-    const int64_t b = a.hoff[x], d = a.hlen[x], e = b + d;
+  // one row per wave (more than 64 entries)
+  auto wave_row = [&](int32_t x, int32_t cur, int64_t b, int d) {
+    const int64_t e = b + d;
     const auto val = make_val(cur);
-    int32_t h = cur;
-    int64_t c = 0;
-    if (d <= (int64_t)kRegSpan * kWave) {
+    int32_t h = cur, c = 0;
+    if (d <= kRegSpan * kWave) {
       int32_t w[kRegSpan], v[kRegSpan];
 #pragma unroll
       for (int u = 0; u < kRegSpan; ++u) {
@@ -722,10 +767,10 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
       }
 #pragma unroll
       for (int u = 0; u < kRegSpan; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
-      auto count_ge = [&](int32_t th) -> int64_t {
-        int64_t n = 0;
+      auto count_ge = [&](int32_t th) -> int32_t {
+        int32_t n = 0;
 #pragma unroll
-        for (int u = 0; u < kRegSpan; ++u) n += (int64_t)__popcll(__ballot(v[u] >= th));
+        for (int u = 0; u < kRegSpan; ++u) n += (int32_t)__popcll(__ballot(v[u] >= th));
         return n;
       };
       c = count_ge(cur);
@@ -744,14 +789,13 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
       }
       if (a.propagate && h < cur) {
 #pragma unroll
-        for (int u = 0; u < kRegSpan; ++u) uncount(dec_short, w[u], v[u], cur, h);
+        for (int u = 0; u < kRegSpan; ++u) uncount(dec_wave, w[u], v[u], cur, h);
       }
     } else {
       // the first pass also settles a row that does not drop (its answer
       // is cur, among the unit bins)
-      const Dec *spec = a.spec ? &dec_short : nullptr;
-      h = hindex_wave(a.hcols, b, e, k0, cur, bins, val, &c, spec);
-      const int32_t top = spec ? cur - 1 : cur;
+      h = hindex_wave(a.hcols, b, e, k0, cur, bins, val, &c, dec_wave, a.spec != 0, a.narrow != 0);
+      const int32_t top = a.spec ? cur - 1 : cur;
       if (a.propagate && h < top) {
         for (int64_t k0i = b; k0i < e; k0i += (int64_t)kUnroll * kWave) {
           int32_t w[kUnroll], v[kUnroll];
@@ -763,13 +807,87 @@ __global__ __launch_bounds__(kHalfBlock) void hindex_half_kernel(HalfArgs a) {
 #pragma unroll
           for (int u = 0; u < kUnroll; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
 #pragma unroll
-          for (int u = 0; u < kUnroll; ++u) uncount(dec_short, w[u], v[u], top, h);
+          for (int u = 0; u < kUnroll; ++u) uncount(dec_wave, w[u], v[u], top, h);
         }
       }
     }
     if (lane_id() == 0) {
-      a.cnt[x] = (int32_t)min<int64_t>(c, 0x7FFFFFFF);
+      a.cnt[x] = c;
       if (h < cur) a.est[x] = h;
+    }
+  };
+  // groups of `per` rows: their vertices, values and extents in one lane
+  // each; the tiny ones (at most 64 entries: one entry per lane) together,
+  // each step of every row's search issued before the next step of any
+  const int64_t gw = (int64_t)wave_in_block() * G + (G - 1 - me);
+  for (int64_t i0 = gw * per; i0 < n_wave; i0 += nw * per) {
+    const int l = lane_id();
+    const bool mine = l < per && i0 + l < n_wave;
+    int32_t xl = 0, curl = 0, dl = 0;
+    int64_t bl = 0;
+    if (mine) {
+      xl = a.q_in[i0 + l];
+      curl = a.est[xl];
+      bl = a.hoff[xl];
+      dl = a.hlen[xl];
+    }
+    const bool tiny = mine && dl <= kWave;
+    if (__ballot(tiny)) {
+      const auto val = make_val(k0);  // a tiny row's values are at most 64
+      int32_t w[kTiny], v[kTiny], cur[kTiny], lo[kTiny], hi[kTiny];
+#pragma unroll
+      for (int u = 0; u < kTiny; ++u) {
+        const int d = __shfl(tiny ? dl : 0, u, kWave);
+        const int64_t b = __shfl(bl, u, kWave);
+        w[u] = l < d ? a.hcols[b + l] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < kTiny; ++u) v[u] = w[u] >= 0 ? val(w[u]) : INT32_MIN;
+      bool more = false;
+#pragma unroll
+      for (int u = 0; u < kTiny; ++u) {
+        const bool on = __shfl(tiny ? 1 : 0, u, kWave) != 0;
+        cur[u] = __shfl(curl, u, kWave);
+        const bool drops = on && (int32_t)__popcll(__ballot(v[u] >= cur[u])) < cur[u];
+        // count_ge(x) >= x holds at k0 (H is the k0-core)
+        lo[u] = drops ? k0 : cur[u];
+        hi[u] = drops ? cur[u] - 1 : cur[u];
+        more = more || lo[u] < hi[u];
+      }
+      while (more) {
+        more = false;
+#pragma unroll
+        for (int u = 0; u < kTiny; ++u) {
+          const int32_t mid = lo[u] + (hi[u] - lo[u] + 1) / 2;  // (lo when settled)
+          const bool ge = (int32_t)__popcll(__ballot(v[u] >= mid)) >= mid;
+          if (lo[u] < hi[u]) {
+            if (ge)
+              lo[u] = mid;
+            else
+              hi[u] = mid - 1;
+          }
+          more = more || lo[u] < hi[u];
+        }
+      }
+      int32_t hl = 0, cl = 0;  // lane u: row u's result
+#pragma unroll
+      for (int u = 0; u < kTiny; ++u) {
+        const int32_t c = (int32_t)__popcll(__ballot(v[u] >= lo[u]));
+        if (l == u) {
+          hl = lo[u];
+          cl = c;
+        }
+        if (a.propagate && lo[u] < cur[u]) uncount(dec_wave, w[u], v[u], cur[u], lo[u]);
+      }
+      if (tiny) {
+        a.cnt[xl] = cl;
+        if (hl < curl) a.est[xl] = hl;
+      }
+    }
+    for (uint64_t rows = __ballot(mine && !tiny); rows != 0; rows &= rows - 1) {
+      const int u = __ffsll((unsigned long long)rows) - 1;
+      wave_row(__shfl(xl, u, kWave), __shfl(curl, u, kWave), __shfl(bl, u, kWave),
+               __shfl(dl, u, kWave));
     }
   }
 }
@@ -1034,6 +1152,7 @@ abcore_status kcore_top(Graph &g, const int32_t *alive, int64_t cnt, int32_t k0,
         a.len_in = list_len + 2 * t;
         a.cap_in = self_cnt;
         a.propagate = t >= 1;
+        a.narrow = t >= kNarrowFrom;
         a.spec = t >= 2;  // from the third half on, a listed vertex is due
         hindex_half_kernel<<<grid, kHalfBlock, 0, s>>>(a);
       }

@@ -108,9 +108,11 @@ struct PeelState {
   int32_t max_core;     // largest level with removals
   int32_t status;       // device-side status for updates (0 ok)
   int32_t aux0, aux1;   // small results (uncertain count, labels, answer bits)
-  int32_t pulled;       // first round ran in pull form
+  int32_t pulled;       // first round ran in pull form (2: its split rows are queued)
   int32_t abort_flag;   // a grid barrier exceeded its spin limit
   int32_t live;         // core decomposition: live entries of the alive list after a scan
+  int32_t bin_first;    // the first round is a binned push of the scan's frontier (its bitmap)
+  int32_t binned;       // the binned round in hand has messages to apply
   int64_t launches;     // launches that did work
   // arrival counters of the workspace reset only (never zeroed: that kernel
   // always completes, so they always return to zero)
@@ -256,6 +258,13 @@ struct Graph {
   int32_t *rdeg = nullptr;
   uint32_t rdeg_mask = 0;
   bool rank_order = true;  // ABCORE_OPT_RANK_ORDER
+  // Binned push rounds (bin_kernel): ids in buckets of 2^bin_shift, bucket b's
+  // messages in bin_msg from off[b << bin_shift] on (as many as its vertices
+  // have entries: each is sent along at most once in a computation), their
+  // number in bin_tail[b] (zero between rounds).  Null on small graphs.
+  uint16_t *bin_msg = nullptr;  // 2*m_csr
+  int32_t *bin_tail = nullptr;  // bin_count
+  int bin_shift = 0, bin_count = 0;
   // Second workspace state and partial sums: queries in rank order alternate
   // between the two, each leaving the other one zeroed and the queue empty
   // (rs_ready).  Any other launch through make_args clears rs_ready.
@@ -491,7 +500,7 @@ hipError_t launch_pull_round(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
                              bool advance = false, bool queue_f0 = false,
                              const uint32_t *rowbits = nullptr, bool force = false,
                              bool rest_part = false, bool rank = false,
-                             const uint32_t *f0bits = nullptr);
+                             const uint32_t *f0bits = nullptr, bool bin = false);
 // Asynchronous peel fused with the pull round's completion (fix_bits: the
 // scan's survivors, or nullptr when no pull round ran) and the bitmask pack
 // (pack_bits nullable).
@@ -501,6 +510,15 @@ hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_
                                    const uint32_t *fix_bits, uint32_t *pack_bits,
                                    hipStream_t s, bool split_done = false);
 hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s);
+// Up to `rounds` binned push rounds (each decides on the device whether it is
+// worth running) after a pull kernel that was launched with bin = true.
+// f0bits: the frontier's set bits, or nullptr for the clear bits of alive.
+hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_t *alive,
+                             const uint32_t *f0bits, int rounds, hipStream_t s);
+// Whether this handle's computations may run binned rounds.
+bool bin_ready(const Graph &g);
+abcore_status build_bins(Graph &g, hipStream_t s);
+hipError_t prepare_bin_kernels();
 hipError_t launch_scan_component_of(Graph &g, int32_t thrU, int32_t thrL, int32_t x,
                                     int32_t y, hipStream_t s);
 hipError_t launch_scan_component_view(Graph &g, const PeelArgs &a, int32_t x, int32_t y,
@@ -516,7 +534,7 @@ hipError_t launch_pull_round_args(Graph &g, const PeelArgs &a, const uint32_t *b
                                   const int32_t *corr_x, const int32_t *corr_d, int ncorr,
                                   bool advance, hipStream_t s, bool queue_f0 = false,
                                   const uint32_t *rowbits = nullptr, bool force = false,
-                                  bool rest_part = false, bool rank = false);
+                                  bool rest_part = false, bool rank = false, bool bin = false);
 hipError_t launch_pull_fixup_args(Graph &g, const PeelArgs &a, const uint32_t *bits,
                                   hipStream_t s);
 hipError_t launch_peel_async_args(Graph &g, PeelKind kind, const PeelArgs &a, int grid,

@@ -261,7 +261,7 @@ void free_graph(Graph *g) {
                   g->rcols,       g->rank_vtx,    g->roff,        g->rp_row,
                   g->rp_start,    g->rp_first,    g->rdeg,        g->state_alt,
                   g->part_alt,    g->rs_fail,     g->aux,         g->probe_bits,
-                  g->dbg_enqueue, g->kdead};
+                  g->dbg_enqueue, g->kdead,       g->bin_msg,     g->bin_tail};
   for (void *p : bufs)
     if (p) (void)dev_free(p);
   for (void *p : g->top_buf)
@@ -411,6 +411,10 @@ bool rank_counts(const Graph &g, int32_t thrU, int32_t thrL, int64_t &ku, int64_
   return true;
 }
 
+// Binned push rounds launched before the asynchronous peel (each a pair of
+// kernels that return at once when the round is too small).
+constexpr int kBinRounds = 3;
+
 abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL, bool pull,
                              uint32_t *bits, hipStream_t s, int64_t *launches,
                              bool queue_f0 = false, const uint32_t *rowbits = nullptr,
@@ -418,10 +422,16 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
                              const uint32_t *f0bits = nullptr) {
   const bool fused = g.peel_mode == 3;
   rank = rank && fused && g.rcols != nullptr;
+  // large frontiers pushed by binned rounds (the scan left its frontier in a
+  // bitmap; no bitmap in LDS, which pulls faster than either)
+  const bool bin = pull && fused && queue_f0 && !rank && kind == kGCC && bin_ready(g);
   if (pull) {
-    CHK(timed(g, ABCORE_KERNEL_PULL, s, 1, [&] {
-      return launch_pull_round(g, thrU, thrL, s, fused, queue_f0, rowbits, force, rest_part,
-                               rank, f0bits);
+    CHK(timed(g, ABCORE_KERNEL_PULL, s, bin ? 2 + 2 * kBinRounds : 1, [&] {
+      hipError_t e = launch_pull_round(g, thrU, thrL, s, fused, queue_f0, rowbits, force,
+                                       rest_part, rank, f0bits, bin);
+      if (e == hipSuccess && bin)
+        e = launch_bin_rounds(g, thrU, thrL, g.alive_bits, f0bits, kBinRounds, s);
+      return e;
     }));
     if (!fused)
       CHK(timed(g, ABCORE_KERNEL_FIXUP, s, 1,
@@ -934,6 +944,7 @@ abcore_status abcore_build_csr(int32_t n_upper, int32_t n_lower, const int32_t *
     if (st == ABCORE_OK && hipStreamSynchronize(s) != hipSuccess) st = ABCORE_EDEVICE;
     if (st != ABCORE_OK) break;
     g->build_ms[2] = ms_since(t0);
+    if ((st = build_bins(*g, s)) != ABCORE_OK) break;
     g->qcap = queue_capacity(g->n, g->npieces);
     if ((st = ensure(&g->deg, g->n)) != ABCORE_OK) break;
     if ((st = ensure(&g->queue, (int64_t)kSub * g->qcap)) != ABCORE_OK) break;
@@ -1371,7 +1382,7 @@ abcore_status abcore_compute(abcore_graph h, uint32_t alpha, uint32_t beta, int3
     stats->uncertain = !plus ? 0 : (plus_pull ? sum_part(*g, kPartF0, s, &st) : p.aux0);
     if (st != ABCORE_OK) return st;
     stats->launches = launches;
-    stats->pulled = p.pulled;
+    stats->pulled = p.pulled != 0;
     stats->rank_order = rank_order ? 1 : 0;
   }
   return ABCORE_OK;
@@ -1411,7 +1422,9 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
     int64_t *part;
     int peel_mode;
     bool timing;
+    uint16_t *bin_msg;
     ~Swap() {
+      g.bin_msg = bin_msg;
       g.deg = deg;
       g.queue = queue;
       g.alive_bits = bits;
@@ -1420,7 +1433,8 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
       g.peel_mode = peel_mode;
       g.timing = timing;
     }
-  } restore{*g, g->deg, g->queue, g->alive_bits, g->state, g->part, g->peel_mode, g->timing};
+  } restore{*g,      g->deg,       g->queue,  g->alive_bits, g->state,
+            g->part, g->peel_mode, g->timing, g->bin_msg};
   g->queue = reinterpret_cast<int32_t *>(base + L.queue);
   g->deg = reinterpret_cast<int32_t *>(base + L.deg);
   g->alive_bits = reinterpret_cast<uint32_t *>(base + L.bits);
@@ -1428,6 +1442,7 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
   g->part = reinterpret_cast<int64_t *>(base + L.part);
   g->peel_mode = 3;     // the asynchronous worklist (no host reads)
   g->timing = false;    // event pairs would be created on demand
+  g->bin_msg = nullptr;  // the handle's, not in the scratch: no binned rounds
   const int64_t nqueue = (int64_t)kSub * g->qcap;
   const int64_t nzero = (int64_t)((L.total - L.bits) / sizeof(uint32_t));
   static_fill_kernel<<<std::min(g->cu_count * 8, kMaxBlocks), 256, 0, s>>>(

@@ -1144,7 +1144,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_async_kernel(PeelArgs a) {
   if (a.start_expect > 0) {
     // start phase: after a pull round, the split rows below their threshold
     // (their pieces' counts are complete at the kernel boundary)
-    if (a.fix_bits != nullptr && ld_agent(&a.st->pulled) != 0) {
+    if (a.fix_bits != nullptr && ld_agent(&a.st->pulled) == 1) {
       for (int64_t b = (int64_t)gw * kWave; b < a.nfix; b += (int64_t)nw * kWave) {
         const int64_t i = b + lane_id();
         bool push = false;
@@ -1350,6 +1350,12 @@ hipError_t launch_peel_async(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
   PeelArgs a = make_args(g, thrU, thrL);
   return launch_peel_async_args(g, kind, a, async_peel_grid(g), s);
 }
+
+// Rules of the binned push rounds (bin_kernel, below): a round of at least
+// n / kBinMin entries is binned, and a first round is pulled instead when the
+// survivors' entries are at most kPullPerBin times the frontier's.
+constexpr int kBinMin = 16;
+constexpr double kPullPerBin = 1.0;
 
 // ------------------------------------------------------ pull first round --
 // The first peel round in pull form.  After the scan, every vertex that
@@ -1558,7 +1564,8 @@ __global__ __launch_bounds__(kPullBlock) void pull_round_kernel(
     const int32_t *__restrict__ bounds, int queue_f0, const uint32_t *__restrict__ rowbits,
     int rest_part, const int32_t *__restrict__ written_snap, const int32_t *__restrict__ rcols,
     const int32_t *__restrict__ rank_vtx, const int64_t *__restrict__ roff, int64_t nheavy,
-    int64_t nheavy_upper, int rspace, int64_t rk_u, int64_t rk_l, uint32_t *__restrict__ rs_bits) {
+    int64_t nheavy_upper, int rspace, int64_t rk_u, int64_t rk_l, uint32_t *__restrict__ rs_bits,
+    int bin) {
   static_assert(!(kLds && kRank), "the rank form looks nothing up in a bitmap");
   extern __shared__ __align__(16) uint32_t s_bits[];
   __shared__ PullShared sh;
@@ -1632,14 +1639,20 @@ __global__ __launch_bounds__(kPullBlock) void pull_round_kernel(
     const bool pull =
         mode == 2 ||
         (mode == 0 && f0deg > 0 &&
-         (kRank ? f0deg * 2 >= ku + kl
-                           : (use_lds ? f0deg * 16 >= rest : f0deg * 6 >= rest)));
-    if (lane_id() == 0) sh.decide = pull ? 1 : 0;
+         (kRank     ? f0deg * 2 >= ku + kl
+          : use_lds ? f0deg * 16 >= rest
+          : bin     ? (double)f0deg * kPullPerBin >= (double)rest
+                    : f0deg * 6 >= rest));
+    const bool binned = !pull && bin && f0deg >= n / kBinMin;
+    if (lane_id() == 0) sh.decide = pull ? 1 : binned ? 2 : 0;
   }
   if (kLds) stage(0);
   __syncthreads();
-  if (!sh.decide) {
-    if (queue_f0) {
+  if (sh.decide != 1) {
+    if (sh.decide == 2) {
+      // the frontier stays in its bitmap for the binned round that follows
+      if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->bin_first, 1);
+    } else if (queue_f0) {
       // the first round is pushed and the scan did not queue its frontier:
       // queue every vertex of the scan's frontier (bit clear), 32 per lane;
       // each wave appends its 64 words to a sub-queue of its own choice, so
@@ -1989,7 +2002,7 @@ hipError_t launch_pull_round_args(Graph &g, const PeelArgs &a, const uint32_t *b
                                   const int32_t *corr_x, const int32_t *corr_d, int ncorr,
                                   bool advance, hipStream_t s, bool queue_f0,
                                   const uint32_t *rowbits, bool force, bool rest_part,
-                                  bool rank) {
+                                  bool rank, bool bin) {
   if (g.pull_mode == 1 && !force) return hipSuccess;
   const int mode = force ? 2 : g.pull_mode;
   if (rowbits == nullptr) rowbits = bits;
@@ -2008,29 +2021,29 @@ hipError_t launch_pull_round_args(Graph &g, const PeelArgs &a, const uint32_t *b
         a, bits, g.deg0, g.n, scan_grid(g), mode, 1, total_entries, g.npieces,
         g.npieces_upper, corr_x, corr_d, ncorr, advance ? 1 : 0, bounds, queue_f0 ? 1 : 0,
         rowbits, rest_part ? 1 : 0, rest_part ? g.split_written : nullptr, nullptr, g.rank_vtx,
-        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr);
+        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr, bin ? 1 : 0);
   else if (rcols != nullptr)
     pull_round_kernel<false, true><<<grid, kPullBlock, dyn, s>>>(
         a, bits, g.deg0, g.n, scan_grid(g), mode, 0, total_entries, g.npieces,
         g.npieces_upper, corr_x, corr_d, ncorr, advance ? 1 : 0, bounds, queue_f0 ? 1 : 0,
         rowbits, rest_part ? 1 : 0, rest_part ? g.split_written : nullptr, rcols, g.rank_vtx,
-        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr);
+        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr, bin ? 1 : 0);
   else
     pull_round_kernel<false, false><<<grid, kPullBlock, dyn, s>>>(
         a, bits, g.deg0, g.n, scan_grid(g), mode, 0, total_entries, g.npieces,
         g.npieces_upper, corr_x, corr_d, ncorr, advance ? 1 : 0, bounds, queue_f0 ? 1 : 0,
         rowbits, rest_part ? 1 : 0, rest_part ? g.split_written : nullptr, nullptr, g.rank_vtx,
-        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr);
+        g.roff, g.nheavy, g.nheavy_upper, 0, -1, -1, nullptr, bin ? 1 : 0);
   return hipGetLastError();
 }
 
 hipError_t launch_pull_round(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s,
                              bool advance, bool queue_f0, const uint32_t *rowbits, bool force,
-                             bool rest_part, bool rank, const uint32_t *f0bits) {
+                             bool rest_part, bool rank, const uint32_t *f0bits, bool bin) {
   PeelArgs a = make_args(g, thrU, thrL);
   a.f0_bits = f0bits;
   return launch_pull_round_args(g, a, g.alive_bits, nullptr, nullptr, 0, advance, s, queue_f0,
-                                rowbits, force, rest_part, rank);
+                                rowbits, force, rest_part, rank, bin);
 }
 
 // A query in rank order (unchanged graph): part 0, the first round pulled on
@@ -2051,7 +2064,7 @@ hipError_t launch_rank_query(Graph &g, int32_t thrU, int32_t thrL, int64_t ku, i
     pull_round_kernel<false, true><<<grid, kPullBlock, 0, s>>>(
         a, g.alive_bits, g.deg0, g.n, scan_grid(g), 2, 0, 2 * g.m, g.npieces, g.npieces_upper,
         nullptr, nullptr, 0, 0, nullptr, 0, g.alive_bits, 0, nullptr, g.rcols, g.rank_vtx, g.roff,
-        g.nheavy, g.nheavy_upper, 1, ku, kl, pack_bits);
+        g.nheavy, g.nheavy_upper, 1, ku, kl, pack_bits, 0);
     return hipGetLastError();
   }
   PeelArgs a = make_args(g, thrU, thrL);
@@ -2102,6 +2115,396 @@ hipError_t launch_pull_fixup_args(Graph &g, const PeelArgs &a, const uint32_t *b
 
 hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s) {
   return launch_pull_fixup_args(g, make_args(g, thrU, thrL), g.alive_bits, s);
+}
+
+// ---------------------------------------------------- binned push rounds --
+// A round whose frontier has many entries, without an atomic per entry.
+// Random atomics run at about 27 G/s on this chip whatever they address (the
+// L2s' atomic units), so a round of 170 M entries takes over 6 ms.  Here the
+// entries become messages, 16 bits each, sorted by id range ("bucket"), and
+// every bucket's degrees are then lowered in LDS by one workgroup.
+//
+// bin_kernel: a workgroup collects a tile of kBinTile entries of frontier
+// rows in registers (edge-balanced, as the peel walks rows), ranks them per
+// bucket in an LDS histogram, reserves room in the buckets it meets (one
+// atomic per bucket and tile), orders the tile in LDS and writes it out in
+// runs.  The frontier is the scan's (its bitmap) or the queue's current
+// range.
+// apply_kernel: a workgroup per bucket holds its 2^shift degrees in LDS,
+// takes one off per message, queues the vertices that cross their threshold
+// (the unique decrement from it), writes the degrees back and zeroes the
+// bucket's count; the last workgroup starts the next round.
+// Both do nothing in a round that the rule leaves to the asynchronous peel.
+constexpr int kBinBlock = 1024;
+constexpr int kBinWaves = kBinBlock / kWave;
+constexpr int kBinPer = 16;                      // entries per thread of a tile
+constexpr int kBinTile = kBinBlock * kBinPer;
+constexpr int kBinMaxShift = 15;                 // 32,768 degrees: 128 KB of LDS
+constexpr int kBinMaxBuckets = 3 * kBinBlock;
+constexpr int kBinList = 512;                    // frontier vertices a wave lists at a time
+constexpr int kBinLong = 2048;                   // a longer row is walked by its workgroup
+constexpr int kBinLongRows = 64;                 // (as many as wait at a time)
+
+struct BinShared {
+  uint32_t sorted[kBinTile];
+  int32_t hist[kBinMaxBuckets];
+  int32_t low[kBinMaxBuckets];    // first position of a bucket in the tile
+  int64_t to[kBinMaxBuckets];     // what a tile position adds to reach its message slot
+  int16_t list[kBinWaves][kBinList];  // frontier vertices past the wave's base
+  RangeView view;
+  int wsum[kBinWaves + 1];
+  int left;                       // some wave has entries left
+  // rows of more than kBinLong entries, walked by the whole workgroup
+  int64_t long_s[kBinLongRows];
+  int32_t long_d[kBinLongRows];
+  int nlong, long_at;             // rows listed; entries of the last one walked
+};
+
+__global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__restrict__ msg,
+                                                        int32_t *__restrict__ tail, int shift,
+                                                        int nbuckets,
+                                                        const uint32_t *__restrict__ bits,
+                                                        uint32_t flip, int64_t nwords) {
+  extern __shared__ __align__(16) uint8_t s_raw[];
+  BinShared &sh = *reinterpret_cast<BinShared *>(s_raw);
+  const bool from_bits = ld_agent(&a.st->bin_first) != 0;
+  load_view(sh.view, a.st);
+  const int64_t items = sh.view.pre[kSub];
+  // (a queued vertex survived the scan: its row has at least its threshold's
+  // entries)
+  if (!from_bits && items * max(1, (a.thrU / 2 + a.thrL / 2)) < max((int64_t)1, a.n / kBinMin))
+    return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->binned, 1);
+  for (int i = threadIdx.x; i < nbuckets; i += kBinBlock) sh.hist[i] = 0;
+  const int lane = lane_id();
+  const int64_t gw = (int64_t)wave_in_block() * gridDim.x + blockIdx.x;
+  const int64_t nw = (int64_t)gridDim.x * kBinWaves;
+  int16_t *list = sh.list[wave_in_block()];
+  const uint32_t low_mask = (1u << shift) - 1u;
+  int64_t entries = 0;
+  // the wave's source: groups of kBinList ids of the bitmap (16 words, 8 bits
+  // per lane) whose set bits go to the list, or 64 queue items at a time
+  int64_t group = gw, base_id = 0;
+  int listed = 0, taken = 0;
+  bool dry = false;
+  // the rows in hand: entries [pos, bw.total) of the batch are left
+  BatchWalk bw;
+  bw.incl = bw.excl = bw.total = bw.s_lo = bw.s_hi = 0;
+  int pos = 0;
+  auto next_rows = [&]() {
+    int32_t x = -1;
+    if (from_bits) {
+      while (taken >= listed && !dry) {
+        base_id = group * kBinList;
+        if (base_id >= nwords * 32) {
+          dry = true;
+          break;
+        }
+        group += nw;
+        const int64_t w = (base_id >> 5) + (lane >> 2);
+        uint32_t byte = 0;
+        if (w < nwords) byte = ((bits[w] ^ flip) >> (8 * (lane & 3))) & 0xFFu;
+        const int64_t first = base_id + 8 * lane;
+        if (first + 8 > a.n) byte &= first < a.n ? (1u << (int)(a.n - first)) - 1u : 0u;
+        const int c = __popc(byte);
+        const int incl = wave_incl_scan(c);
+        int at = incl - c;
+        while (byte != 0) {
+          list[at++] = (int16_t)(8 * lane + __ffs((int)byte) - 1);
+          byte &= byte - 1;
+        }
+        listed = __shfl(incl, kWave - 1, kWave);
+        taken = 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (taken + lane < listed) x = (int32_t)(base_id + list[taken + lane]);
+      taken += kWave;
+    } else {
+      const int64_t i = group * kWave + lane;
+      dry = group * kWave >= items;
+      group += nw;
+      if (i < items) x = view_item(sh.view, a.queue, a.qcap, (int32_t)i);
+    }
+    int64_t s = 0;
+    int d = 0;
+    if (x >= 0) {
+      s = a.off[x];
+      d = (int)(a.off[x + 1] - s);
+      // after a pull round a split row may be queued a second time (see
+      // peel_batch): the first consumer marks its degree
+      if (d > kPiece && a.fix_bits != nullptr &&
+          atomicExch(&a.deg[x], kClaimedDeg) <= kClaimedDeg / 2)
+        d = 0;
+      if (a.ins_head != nullptr) {
+        // inserted edges: few, decremented directly
+        for (int e = a.ins_head[x]; e >= 0; e = a.ins_next[e]) {
+          const int32_t w = a.ins_other[e];
+          if (w >= 0 && atomicSub(&a.deg[w], 1) == (w < a.nU ? a.thrU : a.thrL)) {
+            const int2 r = reserve_slots(a.st, a.queue, a.qcap,
+                                         append_pref(a, blockIdx.x % kSub), 1, a.abort_host);
+            if (r.x >= 0) st_agent(&a.queue[(int64_t)r.x * a.qcap + r.y], w);
+            ABC_COUNT_ENQUEUE(a.dbg_enqueue, w);
+          }
+        }
+      }
+    }
+    entries += d;
+    if (d > kBinLong) {
+      const int i = atomicAdd(&sh.nlong, 1);
+      if (i < kBinLongRows) {
+        sh.long_s[i] = s;
+        sh.long_d[i] = d;
+        d = 0;
+      }
+    }
+    bw.init(s, d);
+    pos = 0;
+  };
+  if (threadIdx.x == 0) {
+    sh.nlong = 0;
+    sh.long_at = 0;
+  }
+  __syncthreads();
+  for (;;) {
+    // a tile: kBinPer steps of 64 entries per wave, of the last long row
+    // while there is one
+    int32_t w[kBinPer];
+    const int nlong = min(sh.nlong, kBinLongRows);
+    __syncthreads();  // (rows listed below are for the next tile)
+    if (nlong > 0) {
+      const int64_t s = sh.long_s[nlong - 1] + sh.long_at;
+      const int d = sh.long_d[nlong - 1] - sh.long_at;
+#pragma unroll
+      for (int u = 0; u < kBinPer; ++u) {
+        const int k = u * kBinBlock + (int)threadIdx.x;
+        w[u] = k < d ? a.cols[s + k] : -1;
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kBinPer; ++u) {
+        while (pos >= bw.total && !dry) next_rows();
+        w[u] = -1;
+        if (pos < bw.total) {
+          const int k = pos + lane;
+          int j;
+          const int64_t at = bw.locate(min(k, bw.total - 1), j);
+          if (k < bw.total) w[u] = a.cols[at];
+        }
+        pos += kWave;
+      }
+    }
+    // (deleted entries are negative and send nothing)
+    int32_t rank[kBinPer];
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u)
+      rank[u] = w[u] >= 0 ? atomicAdd(&sh.hist[w[u] >> shift], 1) : 0;
+    __syncthreads();
+    // three buckets per thread: their first positions and message slots
+    int c[3], mine = 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int b = 3 * (int)threadIdx.x + q;
+      c[q] = b < nbuckets ? sh.hist[b] : 0;
+      mine += c[q];
+    }
+    const int incl = wave_incl_scan(mine);
+    if (lane == kWave - 1) sh.wsum[wave_in_block()] = incl;
+    if (threadIdx.x == 0) {
+      // (every wave has read the long row and listed its own)
+      int left = min(sh.nlong, kBinLongRows);
+      if (nlong > 0) {
+        sh.long_at += kBinTile;
+        if (sh.long_at >= sh.long_d[nlong - 1]) {
+          sh.long_at = 0;
+          --left;
+        }
+      }
+      sh.nlong = left;
+      sh.left = left;
+    }
+    int got[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      got[q] = c[q] > 0 ? atomicAdd(&tail[3 * threadIdx.x + q], c[q]) : 0;
+    __syncthreads();
+    int at = incl - mine, total = 0;
+    for (int v = 0; v < kBinWaves; ++v) {
+      if (v < wave_in_block()) at += sh.wsum[v];
+      total += sh.wsum[v];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int b = 3 * (int)threadIdx.x + q;
+      if (b < nbuckets) {
+        sh.low[b] = at;
+        sh.hist[b] = 0;
+        if (c[q] > 0) sh.to[b] = a.off[(int64_t)b << shift] + got[q] - at;
+      }
+      at += c[q];
+    }
+    if (lane == 0 && (pos < bw.total || !dry)) sh.left = 1;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kBinPer; ++u)
+      if (w[u] >= 0) sh.sorted[sh.low[w[u] >> shift] + rank[u]] = (uint32_t)w[u];
+    __syncthreads();
+    for (int i = threadIdx.x; i < total; i += kBinBlock) {
+      const uint32_t v = sh.sorted[i];
+      msg[sh.to[v >> shift] + i] = (uint16_t)(v & low_mask);
+    }
+    if (!sh.left) break;
+    __syncthreads();
+  }
+  __shared__ int64_t s_acc;
+  add_part(a.part, kPartEntries, entries, &s_acc);
+}
+
+// After a pulled first round, ahead of the binned ones: queues the split rows
+// that ended below their threshold (as plain ids) and takes them into the
+// round in hand; the peel's start phase then has none to queue (pulled = 2).
+__global__ __launch_bounds__(kPeelBlock) void queue_split_kernel(PeelArgs a) {
+  __shared__ int32_t s_lq[kPeelWaves][kLocalQueue];
+  __shared__ int s_cnt[kPeelWaves + 2];
+  __shared__ int64_t s_acc;
+  if (ld_agent(&a.st->pulled) != 1) return;
+  LocalQueue lq = make_lq(s_lq[wave_in_block()], kLocalQueue, a);
+  const int64_t gw = (int64_t)blockIdx.x * kPeelWaves + wave_in_block();
+  const int64_t nw = (int64_t)gridDim.x * kPeelWaves;
+  int64_t fixed = 0;
+  for (int64_t b = gw * kWave; b < a.nfix; b += nw * kWave) {
+    const int64_t i = b + lane_id();
+    bool push = false;
+    int32_t x = -1;
+    if (i < a.nfix) x = a.fix_rows[i];
+    if (x >= 0 && ((a.fix_bits[x >> 5] >> (x & 31)) & 1u))
+      push = a.deg[x] < (x < a.nU ? a.thrU : a.thrL);
+    fixed += push ? 1 : 0;
+    lq.push(push, x);
+  }
+  block_flush(lq, s_cnt);
+  add_part(a.part, kPartF1, fixed, &s_acc);
+  if (last_block_done<false>(a.st)) {
+    const int j = lane_id();
+    if (j < kSub) st_agent(&a.st->hi[j], phys_tail(a.st, j, a.qcap));
+    if (j == 0) st_agent(&a.st->pulled, 2);
+  }
+}
+
+struct ApplyShared {
+  int32_t lq[kBinWaves][kPullLocalQueue];
+  int s_cnt[kBinWaves + 2];
+};
+
+__global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
+                                                          const uint16_t *__restrict__ msg,
+                                                          int32_t *__restrict__ tail, int shift) {
+  extern __shared__ __align__(16) int32_t s_deg[];
+  __shared__ ApplyShared sh;
+  if (ld_agent(&a.st->binned) == 0) return;
+  const int64_t lo = (int64_t)blockIdx.x << shift;
+  const int64_t hi = min(a.n, lo + ((int64_t)1 << shift));
+  const int count = tail[blockIdx.x];
+  if (count > 0) {
+    LocalQueue lq = make_lq(sh.lq[wave_in_block()], kPullLocalQueue, a);
+    const int span = (int)(hi - lo), quads = span / 4;
+    for (int i = threadIdx.x; i < quads; i += kBinBlock)
+      reinterpret_cast<int4 *>(s_deg)[i] = reinterpret_cast<const int4 *>(a.deg + lo)[i];
+    for (int i = 4 * quads + threadIdx.x; i < span; i += kBinBlock) s_deg[i] = a.deg[lo + i];
+    __syncthreads();
+    if (threadIdx.x == 0) tail[blockIdx.x] = 0;
+    // the messages, eight to a 16-byte load from the aligned slot at or
+    // below the bucket's first on
+    const int64_t m0 = a.off[lo], m1 = m0 + count;
+    const int upper = (int)min(max((int64_t)a.nU - lo, (int64_t)0), (int64_t)span);
+    for (int64_t b = (m0 & ~7ll) + 8 * (int64_t)(threadIdx.x & ~(kWave - 1)); b < m1;
+         b += 8 * kBinBlock) {
+      const int64_t i = b + 8 * lane_id();
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (i < m1) v = *reinterpret_cast<const uint4 *>(msg + i);
+      const uint32_t word[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int o = (int)((word[q / 2] >> (16 * (q & 1))) & 0xFFFFu);
+        bool push = false;
+        if (i + q >= m0 && i + q < m1)
+          push = atomicSub(&s_deg[o], 1) == (o < upper ? a.thrU : a.thrL);
+        lq.push(push, (int32_t)(lo + o));
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < quads; i += kBinBlock)
+      reinterpret_cast<int4 *>(a.deg + lo)[i] = reinterpret_cast<const int4 *>(s_deg)[i];
+    for (int i = 4 * quads + threadIdx.x; i < span; i += kBinBlock) a.deg[lo + i] = s_deg[i];
+    block_flush(lq, sh.s_cnt);
+  }
+  if (last_block_done<false>(a.st)) {
+    advance_round_wave(a.st, a.qcap);
+    if (lane_id() == 0) {
+      st_agent(&a.st->bin_first, 0);
+      st_agent(&a.st->binned, 0);
+      atomicAdd((unsigned long long *)&a.st->launches, 1ull);
+    }
+  }
+}
+
+bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3; }
+
+hipError_t prepare_bin_kernels() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bin_kernel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)sizeof(BinShared));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize,
+                            4 << kBinMaxShift);
+  return e;
+}
+
+hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_t *alive,
+                             const uint32_t *f0bits, int rounds, hipStream_t s) {
+  PeelArgs a = make_args(g, thrU, thrL);
+  a.fix_bits = alive;
+  a.fix_rows = g.heavy_rows;
+  a.nfix = g.nheavy;
+  queue_split_kernel<<<flat_grid(g, std::max<int64_t>(g.nheavy, 1), kPeelBlock), kPeelBlock, 0,
+                       s>>>(a);
+  const size_t slice = (size_t)4 << g.bin_shift;
+  for (int r = 0; r < rounds; ++r) {
+    bin_kernel<<<g.cu_count, kBinBlock, sizeof(BinShared), s>>>(
+        a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, f0bits != nullptr ? f0bits : alive,
+        f0bits != nullptr ? 0u : ~0u, (g.n + 31) / 32);
+    apply_kernel<<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift);
+  }
+  return hipGetLastError();
+}
+
+// Room for binned rounds: on graphs of enough vertices that a bucket is a
+// full LDS slice for every compute unit's worth of them, and few enough that
+// a tile meets each bucket often (else, or without memory, rounds are pushed
+// by atomics).
+constexpr int64_t kBinMinVertices = 4 << 20;
+
+abcore_status build_bins(Graph &g, hipStream_t s) {
+  if (g.n < kBinMinVertices || g.m_csr == 0) return ABCORE_OK;
+  int shift = kBinMaxShift;
+  while (shift > 12 && (g.n >> shift) < 2 * g.cu_count) --shift;
+  const int64_t count = (g.n + ((int64_t)1 << shift) - 1) >> shift;
+  if (count > kBinMaxBuckets || sizeof(BinShared) + 1024 > g.lds_per_block) return ABCORE_OK;
+  if (prepare_bin_kernels() != hipSuccess ||
+      dev_malloc(&g.bin_tail, sizeof(int32_t) * count) != hipSuccess ||
+      dev_malloc(&g.bin_msg, sizeof(uint16_t) * (2 * g.m_csr + 8)) != hipSuccess ||
+      hipMemsetAsync(g.bin_tail, 0, sizeof(int32_t) * count, s) != hipSuccess) {
+    (void)hipGetLastError();
+    if (g.bin_tail) (void)dev_free(g.bin_tail);
+    if (g.bin_msg) (void)dev_free(g.bin_msg);
+    g.bin_tail = nullptr;
+    g.bin_msg = nullptr;
+    return ABCORE_OK;
+  }
+  g.bin_shift = shift;
+  g.bin_count = (int)count;
+  return ABCORE_OK;
 }
 
 // ----------------------------------------------------------------- pack --

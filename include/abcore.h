@@ -103,7 +103,8 @@ typedef struct {
   double ranks_ms;      /* degree-rank copy and its tables */
   int64_t graph_bytes;  /* off, cols, deg0, row pieces */
   int64_t ranks_bytes;  /* degree-rank copy: ranks, relabelled CSR, pieces, degree slots */
-  int64_t queue_bytes;  /* frontier sub-queues of the handle's working set */
+  int64_t queue_bytes;  /* frontier sub-queues of the handle's working set, and on
+                           large graphs the message slots of binned rounds */
   /* last core decomposition's h-index phase (zeros if it did not run):
    * switch level k0, vertices of the k0-core, the adjacency slots it used
    * (its vertices' degrees in the graph), half sweeps (one layer each) */

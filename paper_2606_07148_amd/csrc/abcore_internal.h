@@ -111,7 +111,9 @@ struct PeelState {
   int32_t pulled;       // first round ran in pull form (2: its split rows are queued)
   int32_t abort_flag;   // a grid barrier exceeded its spin limit
   int32_t live;         // core decomposition: live entries of the alive list after a scan
-  int32_t bin_first;    // the first round is a binned push of the scan's frontier (its bitmap)
+  // the first round is a binned push of the scan's frontier (its bitmap), whose
+  // entries this counts in units of n / kBinMin
+  int32_t bin_first;
   int32_t binned;       // the binned round in hand has messages to apply
   int64_t launches;     // launches that did work
   // arrival counters of the workspace reset only (never zeroed: that kernel
@@ -258,13 +260,14 @@ struct Graph {
   int32_t *rdeg = nullptr;
   uint32_t rdeg_mask = 0;
   bool rank_order = true;  // ABCORE_OPT_RANK_ORDER
-  // Binned push rounds (bin_kernel): ids in buckets of 2^bin_shift, bucket b's
-  // messages in bin_msg from off[b << bin_shift] on (as many as its vertices
-  // have entries: each is sent along at most once in a computation), their
-  // number in bin_tail[b] (zero between rounds).  Null on small graphs.
-  uint16_t *bin_msg = nullptr;  // 2*m_csr
-  int32_t *bin_tail = nullptr;  // bin_count
+  // Binned push rounds (bin_kernel): ids in buckets of 2^bin_shift, each with
+  // message slots for its vertices' entries (each is sent along at most once
+  // in a computation) and some slack, the slots in use in bin_tail (zero
+  // between rounds).  Null on small graphs.
+  uint16_t *bin_msg = nullptr;   // 2*m_csr and the slack
+  uint32_t *bin_tail = nullptr;  // bin_count
   int bin_shift = 0, bin_count = 0;
+  int64_t bin_bytes = 0;
   // Second workspace state and partial sums: queries in rank order alternate
   // between the two, each leaving the other one zeroed and the queue empty
   // (rs_ready).  Any other launch through make_args clears rs_ready.
@@ -518,7 +521,6 @@ hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_
 // Whether this handle's computations may run binned rounds.
 bool bin_ready(const Graph &g);
 abcore_status build_bins(Graph &g, hipStream_t s);
-hipError_t prepare_bin_kernels();
 hipError_t launch_scan_component_of(Graph &g, int32_t thrU, int32_t thrL, int32_t x,
                                     int32_t y, hipStream_t s);
 hipError_t launch_scan_component_view(Graph &g, const PeelArgs &a, int32_t x, int32_t y,

@@ -1028,7 +1028,7 @@ abcore_status abcore_graph_report(abcore_graph h, abcore_report *out) {
                          : 4 * n + 4 * n + 8 * (n + 1) + 4 * 2 * g->m_csr +
                                (g->rp_row != nullptr ? (4 + 8) * np + 4 * n : 0) +
                                (g->rdeg != nullptr ? 4 * ((int64_t)g->rdeg_mask + 1) : 0);
-  out->queue_bytes = 4 * (int64_t)kSub * g->qcap;
+  out->queue_bytes = 4 * (int64_t)kSub * g->qcap + g->bin_bytes;
   for (int i = 0; i < 4; ++i) out->core_top[i] = g->kcore_top_used ? g->top_stats[i] : 0;
   out->core_levels_ms = g->kcore_top_used ? g->top_ms[0] : 0.0;
   out->core_top_ms = g->kcore_top_used ? g->top_ms[1] : 0.0;

@@ -1643,15 +1643,18 @@ __global__ __launch_bounds__(kPullBlock) void pull_round_kernel(
           : use_lds ? f0deg * 16 >= rest
           : bin     ? (double)f0deg * kPullPerBin >= (double)rest
                     : f0deg * 6 >= rest));
-    const bool binned = !pull && bin && f0deg >= n / kBinMin;
-    if (lane_id() == 0) sh.decide = pull ? 1 : binned ? 2 : 0;
+    // (2 and more: binned, with the frontier's entries in units of n / kBinMin)
+    const int64_t unit = n / kBinMin;
+    const bool binned = !pull && bin && f0deg >= unit;
+    if (lane_id() == 0)
+      sh.decide = pull ? 1 : binned ? 1 + (int)min(f0deg / unit, (int64_t)INT32_MAX - 2) : 0;
   }
   if (kLds) stage(0);
   __syncthreads();
   if (sh.decide != 1) {
-    if (sh.decide == 2) {
+    if (sh.decide > 1) {
       // the frontier stays in its bitmap for the binned round that follows
-      if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->bin_first, 1);
+      if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->bin_first, sh.decide - 1);
     } else if (queue_f0) {
       // the first round is pushed and the scan did not queue its frontier:
       // queue every vertex of the scan's frontier (bit clear), 32 per lane;
@@ -2126,14 +2129,20 @@ hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
 //
 // bin_kernel: a workgroup collects a tile of kBinTile entries of frontier
 // rows in registers (edge-balanced, as the peel walks rows), ranks them per
-// bucket in an LDS histogram, reserves room in the buckets it meets (one
-// atomic per bucket and tile), orders the tile in LDS and writes it out in
-// runs.  The frontier is the scan's (its bitmap) or the queue's current
-// range.
+// bucket in an LDS histogram, orders the tile in LDS and writes it out in
+// runs.  Room in a bucket is reserved a chunk at a time and kept for the
+// workgroup's next tiles: with one atomic per bucket and tile, these ran into
+// the same 27 G/s (a third of the kernel).  What is left of a chunk at the
+// end is filled with kBinNone.  The frontier is the scan's (its bitmap) or
+// the queue's current range.
 // apply_kernel: a workgroup per bucket holds its 2^shift degrees in LDS,
 // takes one off per message, queues the vertices that cross their threshold
 // (the unique decrement from it), writes the degrees back and zeroes the
 // bucket's count; the last workgroup starts the next round.
+// A first round of 170 M entries over 30 M vertices takes these two 0.90 and
+// 0.25 ms.  bin_kernel is bound by the chain of each refill (a
+// group's words, its rows' offsets, their entries), then by LDS and the
+// vector units (a third of its time each), not by memory.
 // Both do nothing in a round that the rule leaves to the asynchronous peel.
 constexpr int kBinBlock = 1024;
 constexpr int kBinWaves = kBinBlock / kWave;
@@ -2141,58 +2150,103 @@ constexpr int kBinPer = 16;                      // entries per thread of a tile
 constexpr int kBinTile = kBinBlock * kBinPer;
 constexpr int kBinMaxShift = 15;                 // 32,768 degrees: 128 KB of LDS
 constexpr int kBinMaxBuckets = 3 * kBinBlock;
-constexpr int kBinList = 512;                    // frontier vertices a wave lists at a time
+constexpr int kBinList = 256;                    // frontier vertices a wave lists at a time
+constexpr int kBinRefill = 4;                    // steps of a tile between looks for new rows
 constexpr int kBinLong = 2048;                   // a longer row is walked by its workgroup
 constexpr int kBinLongRows = 64;                 // (as many as wait at a time)
+constexpr uint32_t kBinChunk = 64;               // most slots reserved ahead (128 bytes)
+constexpr uint16_t kBinNone = 0xFFFF;            // an unused slot (offsets are below 2^15)
 
 struct BinShared {
   uint32_t sorted[kBinTile];
-  int32_t hist[kBinMaxBuckets];
-  int32_t low[kBinMaxBuckets];    // first position of a bucket in the tile
-  int64_t to[kBinMaxBuckets];     // what a tile position adds to reach its message slot
-  int16_t list[kBinWaves][kBinList];  // frontier vertices past the wave's base
+  uint8_t list[kBinWaves][kBinList];  // frontier vertices past the wave's base
   RangeView view;
   int wsum[kBinWaves + 1];
-  int left;                       // some wave has entries left
+  int left;                        // some wave has entries left
   // rows of more than kBinLong entries, walked by the whole workgroup
-  int64_t long_s[kBinLongRows];
+  uint32_t long_s[kBinLongRows];
   int32_t long_d[kBinLongRows];
-  int nlong, long_at;             // rows listed; entries of the last one walked
+  int nlong, long_at;              // rows listed; entries of the last one walked
 };
 
+// Per bucket, in LDS after BinShared: where the tile's messages go (position
+// i from low on to slot a + i, from cut on to slot b + i, 32-bit wrapping),
+// the workgroup's reserved slots, the tile's count.
+struct BinBucket {
+  uint32_t low, cut, a, b;
+};
+struct BinRoom {
+  uint32_t next, left;
+};
+inline size_t bin_lds(int nbuckets) {
+  return (sizeof(BinShared) + 15) / 16 * 16 +
+         (size_t)nbuckets * (sizeof(BinBucket) + sizeof(BinRoom) + sizeof(int32_t));
+}
+
+// First slot of bucket b: its vertices' entries and, per bucket before it,
+// the slack of every workgroup's unused chunk; whole 128-byte lines.
+__device__ __forceinline__ uint32_t bin_start(const int64_t *__restrict__ off, int b, int shift,
+                                              uint32_t slack) {
+  return (((uint32_t)off[(int64_t)b << shift] + kBinChunk - 1) / kBinChunk) * kBinChunk +
+         (uint32_t)b * slack;
+}
+
 __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__restrict__ msg,
-                                                        int32_t *__restrict__ tail, int shift,
-                                                        int nbuckets,
+                                                        uint32_t *__restrict__ tail, int shift,
+                                                        int nbuckets, uint32_t slack,
                                                         const uint32_t *__restrict__ bits,
                                                         uint32_t flip, int64_t nwords) {
   extern __shared__ __align__(16) uint8_t s_raw[];
   BinShared &sh = *reinterpret_cast<BinShared *>(s_raw);
-  const bool from_bits = ld_agent(&a.st->bin_first) != 0;
+  BinBucket *bucket =
+      reinterpret_cast<BinBucket *>(s_raw + (sizeof(BinShared) + 15) / 16 * 16);
+  BinRoom *room = reinterpret_cast<BinRoom *>(bucket + nbuckets);
+  int32_t *hist = reinterpret_cast<int32_t *>(room + nbuckets);
+  const int first = ld_agent(&a.st->bin_first);
+  const bool from_bits = first != 0;
   load_view(sh.view, a.st);
   const int64_t items = sh.view.pre[kSub];
   // (a queued vertex survived the scan: its row has at least its threshold's
   // entries)
-  if (!from_bits && items * max(1, (a.thrU / 2 + a.thrL / 2)) < max((int64_t)1, a.n / kBinMin))
-    return;
+  const int64_t guess = items * max(1, (a.thrU / 2 + a.thrL / 2));
+  if (!from_bits && guess < max((int64_t)1, a.n / kBinMin)) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->binned, 1);
-  for (int i = threadIdx.x; i < nbuckets; i += kBinBlock) sh.hist[i] = 0;
-  const int lane = lane_id();
-  const int64_t gw = (int64_t)wave_in_block() * gridDim.x + blockIdx.x;
+  // slots reserved at a time: a quarter of what this workgroup will send to
+  // a bucket, as far as that is known
+  const int64_t expect = (from_bits ? (int64_t)first * (a.n / kBinMin) : guess) /
+                         ((int64_t)gridDim.x * nbuckets * 4);
+  uint32_t chunk = 1;
+  while (chunk < kBinChunk && 2 * chunk <= expect) chunk *= 2;
+  for (int i = threadIdx.x; i < nbuckets; i += kBinBlock) {
+    hist[i] = 0;
+    room[i] = BinRoom{0, 0};
+  }
+  const int each = (nbuckets + kBinBlock - 1) / kBinBlock;
+  if (threadIdx.x == 0) {
+    sh.nlong = 0;
+    sh.long_at = 0;
+  }
+  const int lane = lane_id(), wv = wave_in_block();
+  const int64_t gw = (int64_t)wv * gridDim.x + blockIdx.x;
   const int64_t nw = (int64_t)gridDim.x * kBinWaves;
-  int16_t *list = sh.list[wave_in_block()];
   const uint32_t low_mask = (1u << shift) - 1u;
   int64_t entries = 0;
-  // the wave's source: groups of kBinList ids of the bitmap (16 words, 8 bits
-  // per lane) whose set bits go to the list, or 64 queue items at a time
+  // the wave's source: groups of kBinList ids of the bitmap (8 words, 4 bits
+  // per lane) whose set bits go to the list, or 64 queue items at a time; the
+  // next batch's offsets load while the one in hand is walked
   int64_t group = gw, base_id = 0;
   int listed = 0, taken = 0;
   bool dry = false;
-  // the rows in hand: entries [pos, bw.total) of the batch are left
-  BatchWalk bw;
-  bw.incl = bw.excl = bw.total = bw.s_lo = bw.s_hi = 0;
-  int pos = 0;
-  auto next_rows = [&]() {
-    int32_t x = -1;
+  int32_t x_next = -1;
+  int64_t s_next = 0, e_next = 0;
+  uint32_t word = 0;  // of the next group (ids past n are masked when listed)
+  auto load_word = [&]() {
+    const int64_t i = group * (kBinList / 32) + (lane >> 3);
+    word = i < nwords ? bits[i] : 0u;
+  };
+  if (from_bits) load_word();
+  auto fetch = [&]() {
+    x_next = -1;
     if (from_bits) {
       while (taken >= listed && !dry) {
         base_id = group * kBinList;
@@ -2201,36 +2255,45 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
           break;
         }
         group += nw;
-        const int64_t w = (base_id >> 5) + (lane >> 2);
-        uint32_t byte = 0;
-        if (w < nwords) byte = ((bits[w] ^ flip) >> (8 * (lane & 3))) & 0xFFu;
-        const int64_t first = base_id + 8 * lane;
-        if (first + 8 > a.n) byte &= first < a.n ? (1u << (int)(a.n - first)) - 1u : 0u;
-        const int c = __popc(byte);
-        const int incl = wave_incl_scan(c);
-        int at = incl - c;
-        while (byte != 0) {
-          list[at++] = (int16_t)(8 * lane + __ffs((int)byte) - 1);
-          byte &= byte - 1;
+        uint32_t nib = ((word ^ flip) >> (4 * (lane & 7))) & 0xFu;
+        load_word();
+        const int64_t f = base_id + 4 * lane;
+        if (f + 4 > a.n) nib &= f < a.n ? (1u << (int)(a.n - f)) - 1u : 0u;
+        const int c = __popc(nib);
+        const int sum = wave_incl_scan(c);
+        int at = sum - c;
+        while (nib != 0) {
+          sh.list[wv][at++] = (uint8_t)(4 * lane + __ffs((int)nib) - 1);
+          nib &= nib - 1;
         }
-        listed = __shfl(incl, kWave - 1, kWave);
+        listed = __shfl(sum, kWave - 1, kWave);
         taken = 0;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
       }
-      if (taken + lane < listed) x = (int32_t)(base_id + list[taken + lane]);
+      if (!dry && taken + lane < listed) x_next = (int32_t)(base_id + sh.list[wv][taken + lane]);
       taken += kWave;
     } else {
       const int64_t i = group * kWave + lane;
       dry = group * kWave >= items;
       group += nw;
-      if (i < items) x = view_item(sh.view, a.queue, a.qcap, (int32_t)i);
+      if (i < items) x_next = view_item(sh.view, a.queue, a.qcap, (int32_t)i);
     }
-    int64_t s = 0;
-    int d = 0;
+    if (x_next >= 0) {
+      s_next = a.off[x_next];
+      e_next = a.off[x_next + 1];
+    }
+  };
+  // the rows in hand: entries [pos, total) of a batch of 64 rows are left;
+  // `from` is the position in cols of the batch's entry 0, by this lane's row
+  int incl = 0, total = 0, pos = 0;
+  uint32_t from = 0;
+  auto next_rows = [&]() {
+    const int32_t x = x_next;
+    const uint32_t s = (uint32_t)s_next;
+    int d = x >= 0 ? (int)(e_next - s_next) : 0;
+    fetch();
     if (x >= 0) {
-      s = a.off[x];
-      d = (int)(a.off[x + 1] - s);
       // after a pull round a split row may be queued a second time (see
       // peel_batch): the first consumer marks its degree
       if (d > kPiece && a.fix_bits != nullptr &&
@@ -2258,58 +2321,75 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
         d = 0;
       }
     }
-    bw.init(s, d);
+    incl = wave_incl_scan(d);
+    total = __shfl(incl, kWave - 1, kWave);
+    from = s - (uint32_t)(incl - d);
     pos = 0;
   };
-  if (threadIdx.x == 0) {
-    sh.nlong = 0;
-    sh.long_at = 0;
-  }
-  __syncthreads();
-  for (;;) {
-    // a tile: kBinPer steps of 64 entries per wave, of the last long row
-    // while there is one
-    int32_t w[kBinPer];
-    const int nlong = min(sh.nlong, kBinLongRows);
-    __syncthreads();  // (rows listed below are for the next tile)
+  bool more = true;
+  // loads this wave's share of a tile: kBinPer steps of 64 entries, of the
+  // last long row while there is one (steps past the end of a batch of rows
+  // stay empty until the next look for new ones)
+  auto load_tile = [&](int32_t (&w)[kBinPer], int nlong, int long_at) {
     if (nlong > 0) {
-      const int64_t s = sh.long_s[nlong - 1] + sh.long_at;
-      const int d = sh.long_d[nlong - 1] - sh.long_at;
+      const uint32_t s = sh.long_s[nlong - 1] + (uint32_t)long_at;
+      const int d = sh.long_d[nlong - 1] - long_at;
 #pragma unroll
       for (int u = 0; u < kBinPer; ++u) {
         const int k = u * kBinBlock + (int)threadIdx.x;
-        w[u] = k < d ? a.cols[s + k] : -1;
+        w[u] = k < d ? a.cols[s + (uint32_t)k] : -1;
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < kBinPer; ++u) {
-        while (pos >= bw.total && !dry) next_rows();
-        w[u] = -1;
-        if (pos < bw.total) {
-          const int k = pos + lane;
-          int j;
-          const int64_t at = bw.locate(min(k, bw.total - 1), j);
-          if (k < bw.total) w[u] = a.cols[at];
+      for (int u0 = 0; u0 < kBinPer; u0 += kBinRefill) {
+        while (pos >= total && more) {
+          next_rows();
+          more = __ballot(x_next >= 0) != 0 || !dry;
         }
-        pos += kWave;
+        // (no branch among the steps: their searches for the entries' rows,
+        // chains of six cross-lane reads, run side by side)
+        int k[kBinRefill], j[kBinRefill];
+#pragma unroll
+        for (int u = 0; u < kBinRefill; ++u) {
+          k[u] = pos + u * kWave + lane;
+          j[u] = 0;
+        }
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1)
+#pragma unroll
+          for (int u = 0; u < kBinRefill; ++u)
+            if (__shfl(incl, j[u] + step - 1, kWave) <= k[u]) j[u] += step;
+        uint32_t at[kBinRefill];
+#pragma unroll
+        for (int u = 0; u < kBinRefill; ++u)
+          at[u] = (uint32_t)__shfl((int)from, j[u] & (kWave - 1), kWave) + (uint32_t)k[u];
+#pragma unroll
+        for (int u = 0; u < kBinRefill; ++u) w[u0 + u] = k[u] < total ? a.cols[at[u]] : -1;
+        pos += kBinRefill * kWave;
       }
     }
+  };
+  __syncthreads();
+  fetch();
+  more = __ballot(x_next >= 0) != 0 || !dry;
+  for (;;) {
+    int32_t w[kBinPer];
+    const int nlong = min(sh.nlong, kBinLongRows), long_at = sh.long_at;
+    __syncthreads();  // (rows listed from here on are for the next tile)
+    load_tile(w, nlong, long_at);
     // (deleted entries are negative and send nothing)
     int32_t rank[kBinPer];
 #pragma unroll
     for (int u = 0; u < kBinPer; ++u)
-      rank[u] = w[u] >= 0 ? atomicAdd(&sh.hist[w[u] >> shift], 1) : 0;
+      rank[u] = w[u] >= 0 ? atomicAdd(&hist[w[u] >> shift], 1) : 0;
     __syncthreads();
-    // three buckets per thread: their first positions and message slots
-    int c[3], mine = 0;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int b = 3 * (int)threadIdx.x + q;
-      c[q] = b < nbuckets ? sh.hist[b] : 0;
-      mine += c[q];
-    }
-    const int incl = wave_incl_scan(mine);
-    if (lane == kWave - 1) sh.wsum[wave_in_block()] = incl;
+    // each thread's buckets (consecutive): their first positions, then their
+    // message slots
+    const int b0 = min((int)threadIdx.x * each, nbuckets), b1 = min(b0 + each, nbuckets);
+    uint32_t mine = 0;
+    for (int b = b0; b < b1; ++b) mine += (uint32_t)hist[b];
+    const uint32_t upto = (uint32_t)wave_incl_scan((int)mine);
+    if (lane == kWave - 1) sh.wsum[wv] = (int)upto;
     if (threadIdx.x == 0) {
       // (every wave has read the long row and listed its own)
       int left = min(sh.nlong, kBinLongRows);
@@ -2323,38 +2403,50 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
       sh.nlong = left;
       sh.left = left;
     }
-    int got[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-      got[q] = c[q] > 0 ? atomicAdd(&tail[3 * threadIdx.x + q], c[q]) : 0;
     __syncthreads();
-    int at = incl - mine, total = 0;
+    uint32_t at = upto - mine, sum = 0;
     for (int v = 0; v < kBinWaves; ++v) {
-      if (v < wave_in_block()) at += sh.wsum[v];
-      total += sh.wsum[v];
+      if (v < wv) at += (uint32_t)sh.wsum[v];
+      sum += (uint32_t)sh.wsum[v];
     }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int b = 3 * (int)threadIdx.x + q;
-      if (b < nbuckets) {
-        sh.low[b] = at;
-        sh.hist[b] = 0;
-        if (c[q] > 0) sh.to[b] = a.off[(int64_t)b << shift] + got[q] - at;
+    for (int b = b0; b < b1; ++b) {
+      const uint32_t c = (uint32_t)hist[b];
+      if (c == 0) continue;
+      hist[b] = 0;
+      // room: what is left of the last chunk, then whole chunks
+      const BinRoom r = room[b];
+      const uint32_t have = min(c, r.left), need = c - have, cut = at + have;
+      uint32_t slot = 0;
+      if (need > 0) {
+        const uint32_t ask = (need + chunk - 1) & ~(chunk - 1);
+        slot = bin_start(a.off, b, shift, slack) + atomicAdd(&tail[b], ask);
+        room[b] = BinRoom{slot + need, ask - need};
+      } else {
+        room[b] = BinRoom{r.next + c, r.left - c};
       }
-      at += c[q];
+      bucket[b] = BinBucket{at, cut, r.next - at, slot - cut};
+      at += c;
     }
-    if (lane == 0 && (pos < bw.total || !dry)) sh.left = 1;
+    if (lane == 0 && (pos < total || more)) sh.left = 1;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kBinPer; ++u)
-      if (w[u] >= 0) sh.sorted[sh.low[w[u] >> shift] + rank[u]] = (uint32_t)w[u];
+      if (w[u] >= 0) sh.sorted[bucket[w[u] >> shift].low + rank[u]] = (uint32_t)w[u];
     __syncthreads();
-    for (int i = threadIdx.x; i < total; i += kBinBlock) {
+    for (uint32_t i = threadIdx.x; i < sum; i += kBinBlock) {
       const uint32_t v = sh.sorted[i];
-      msg[sh.to[v >> shift] + i] = (uint16_t)(v & low_mask);
+      const BinBucket bk = bucket[v >> shift];
+      msg[(i < bk.cut ? bk.a : bk.b) + i] = (uint16_t)(v & low_mask);
     }
     if (!sh.left) break;
     __syncthreads();
+  }
+  for (int b = threadIdx.x; b < nbuckets; b += kBinBlock) {
+    BinRoom r = room[b];
+    for (; r.left > 0 && (r.next & 7u) != 0; ++r.next, --r.left) msg[r.next] = kBinNone;
+    for (; r.left >= 8; r.next += 8, r.left -= 8)
+      *reinterpret_cast<uint4 *>(msg + r.next) = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (; r.left > 0; ++r.next, --r.left) msg[r.next] = kBinNone;
   }
   __shared__ int64_t s_acc;
   add_part(a.part, kPartEntries, entries, &s_acc);
@@ -2398,13 +2490,14 @@ struct ApplyShared {
 
 __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
                                                           const uint16_t *__restrict__ msg,
-                                                          int32_t *__restrict__ tail, int shift) {
+                                                          uint32_t *__restrict__ tail, int shift,
+                                                          uint32_t slack) {
   extern __shared__ __align__(16) int32_t s_deg[];
   __shared__ ApplyShared sh;
   if (ld_agent(&a.st->binned) == 0) return;
   const int64_t lo = (int64_t)blockIdx.x << shift;
   const int64_t hi = min(a.n, lo + ((int64_t)1 << shift));
-  const int count = tail[blockIdx.x];
+  const uint32_t count = tail[blockIdx.x];
   if (count > 0) {
     LocalQueue lq = make_lq(sh.lq[wave_in_block()], kPullLocalQueue, a);
     const int span = (int)(hi - lo), quads = span / 4;
@@ -2413,23 +2506,24 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
     for (int i = 4 * quads + threadIdx.x; i < span; i += kBinBlock) s_deg[i] = a.deg[lo + i];
     __syncthreads();
     if (threadIdx.x == 0) tail[blockIdx.x] = 0;
-    // the messages, eight to a 16-byte load from the aligned slot at or
-    // below the bucket's first on
-    const int64_t m0 = a.off[lo], m1 = m0 + count;
+    // eight messages to a 16-byte load (a bucket starts on a whole line)
+    const uint32_t m0 = bin_start(a.off, blockIdx.x, shift, slack), m1 = m0 + count;
     const int upper = (int)min(max((int64_t)a.nU - lo, (int64_t)0), (int64_t)span);
-    for (int64_t b = (m0 & ~7ll) + 8 * (int64_t)(threadIdx.x & ~(kWave - 1)); b < m1;
-         b += 8 * kBinBlock) {
-      const int64_t i = b + 8 * lane_id();
-      uint4 v = make_uint4(0, 0, 0, 0);
+    for (uint32_t b = m0 + 8 * (threadIdx.x & ~(kWave - 1)); b < m1; b += 8 * kBinBlock) {
+      const uint32_t i = b + 8 * (uint32_t)lane_id();
+      uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
       if (i < m1) v = *reinterpret_cast<const uint4 *>(msg + i);
       const uint32_t word[4] = {v.x, v.y, v.z, v.w};
+      int32_t old[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int o = (int)((word[q / 2] >> (16 * (q & 1))) & 0xFFFFu);
-        bool push = false;
-        if (i + q >= m0 && i + q < m1)
-          push = atomicSub(&s_deg[o], 1) == (o < upper ? a.thrU : a.thrL);
-        lq.push(push, (int32_t)(lo + o));
+        old[q] = i + q < m1 && o != kBinNone ? atomicSub(&s_deg[o], 1) : INT32_MIN;
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int o = (int)((word[q / 2] >> (16 * (q & 1))) & 0xFFFFu);
+        lq.push(old[q] == (o < upper ? a.thrU : a.thrL), (int32_t)(lo + o));
       }
     }
     __syncthreads();
@@ -2450,14 +2544,16 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
 
 bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3; }
 
-hipError_t prepare_bin_kernels() {
+// Slots per bucket for the workgroups' unused chunks.
+static uint32_t bin_slack(const Graph &g) { return (uint32_t)(g.cu_count + 1) * kBinChunk; }
+
+static hipError_t prepare_bin_kernels(int nbuckets, int shift) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bin_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)sizeof(BinShared));
+                                     (int)bin_lds(nbuckets));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            4 << kBinMaxShift);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 4 << shift);
   return e;
 }
 
@@ -2471,18 +2567,19 @@ hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_
                        s>>>(a);
   const size_t slice = (size_t)4 << g.bin_shift;
   for (int r = 0; r < rounds; ++r) {
-    bin_kernel<<<g.cu_count, kBinBlock, sizeof(BinShared), s>>>(
-        a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, f0bits != nullptr ? f0bits : alive,
-        f0bits != nullptr ? 0u : ~0u, (g.n + 31) / 32);
-    apply_kernel<<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift);
+    bin_kernel<<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
+        a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, bin_slack(g),
+        f0bits != nullptr ? f0bits : alive, f0bits != nullptr ? 0u : ~0u, (g.n + 31) / 32);
+    apply_kernel<<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift,
+                                                       bin_slack(g));
   }
   return hipGetLastError();
 }
 
-// Room for binned rounds: on graphs of enough vertices that a bucket is a
-// full LDS slice for every compute unit's worth of them, and few enough that
-// a tile meets each bucket often (else, or without memory, rounds are pushed
-// by atomics).
+// Room for binned rounds: on graphs of enough vertices that the buckets give
+// every compute unit a few, few enough that a tile meets each bucket often,
+// and positions of 32 bits (else, or without memory, rounds are pushed by
+// atomics).
 constexpr int64_t kBinMinVertices = 4 << 20;
 
 abcore_status build_bins(Graph &g, hipStream_t s) {
@@ -2490,11 +2587,14 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
   int shift = kBinMaxShift;
   while (shift > 12 && (g.n >> shift) < 2 * g.cu_count) --shift;
   const int64_t count = (g.n + ((int64_t)1 << shift) - 1) >> shift;
-  if (count > kBinMaxBuckets || sizeof(BinShared) + 1024 > g.lds_per_block) return ABCORE_OK;
-  if (prepare_bin_kernels() != hipSuccess ||
-      dev_malloc(&g.bin_tail, sizeof(int32_t) * count) != hipSuccess ||
-      dev_malloc(&g.bin_msg, sizeof(uint16_t) * (2 * g.m_csr + 8)) != hipSuccess ||
-      hipMemsetAsync(g.bin_tail, 0, sizeof(int32_t) * count, s) != hipSuccess) {
+  const int64_t slots = 2 * g.m_csr + (count + 1) * (int64_t)(bin_slack(g) + kBinChunk);
+  if (count > kBinMaxBuckets || slots > (int64_t)UINT32_MAX ||
+      bin_lds((int)count) + 1024 > g.lds_per_block)
+    return ABCORE_OK;
+  if (prepare_bin_kernels((int)count, shift) != hipSuccess ||
+      dev_malloc(&g.bin_tail, sizeof(uint32_t) * count) != hipSuccess ||
+      dev_malloc(&g.bin_msg, sizeof(uint16_t) * slots) != hipSuccess ||
+      hipMemsetAsync(g.bin_tail, 0, sizeof(uint32_t) * count, s) != hipSuccess) {
     (void)hipGetLastError();
     if (g.bin_tail) (void)dev_free(g.bin_tail);
     if (g.bin_msg) (void)dev_free(g.bin_msg);
@@ -2504,6 +2604,7 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
   }
   g.bin_shift = shift;
   g.bin_count = (int)count;
+  g.bin_bytes = (int64_t)(sizeof(uint16_t) * slots + sizeof(uint32_t) * count);
   return ABCORE_OK;
 }
 

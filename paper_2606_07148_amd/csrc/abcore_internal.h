@@ -521,6 +521,16 @@ hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_
 // Whether this handle's computations may run binned rounds.
 bool bin_ready(const Graph &g);
 abcore_status build_bins(Graph &g, hipStream_t s);
+// Queries of graphs that fit one workgroup's LDS (tiny_ready), a launch per
+// kTinyQueries of them.
+constexpr int32_t kTinyQueries = 256;
+struct TinyQueries {
+  int32_t thrU[kTinyQueries], thrL[kTinyQueries];
+};
+bool tiny_ready(const Graph &g, int32_t count);
+hipError_t prepare_tiny_kernel(Graph &g);
+hipError_t launch_tiny(Graph &g, const int32_t *thrU, const int32_t *thrL, int32_t count,
+                       uint32_t *bits, hipStream_t s);
 hipError_t launch_scan_component_of(Graph &g, int32_t thrU, int32_t thrL, int32_t x,
                                     int32_t y, hipStream_t s);
 hipError_t launch_scan_component_view(Graph &g, const PeelArgs &a, int32_t x, int32_t y,

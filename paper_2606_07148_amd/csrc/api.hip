@@ -993,6 +993,7 @@ abcore_status abcore_build_csr(int32_t n_upper, int32_t n_lower, const int32_t *
       g->peel_mode = 1;
     }
     (void)prepare_pull_kernel(*g);
+    (void)prepare_tiny_kernel(*g);
     if (launch_init_state(*g, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
       set_error("abcore_build_csr: state initialisation failed");
       st = ABCORE_EDEVICE;
@@ -1284,7 +1285,11 @@ abcore_status abcore_compute(abcore_graph h, uint32_t alpha, uint32_t beta, int3
   bool plus_pull = false;  // GCC+ initialised by a pull round
   bool rank_order = false;
   int64_t ku = 0, kl = 0, f0deg = 0;
-  if (algo == ABCORE_GCC) {
+  if (algo == ABCORE_GCC && stats == nullptr && tiny_ready(*g, 1)) {
+    // (a call that asks for statistics runs the general path, which keeps them)
+    CHK(timed(*g, ABCORE_KERNEL_PEEL, s, 1,
+              [&] { return launch_tiny(*g, &thrU, &thrL, 1, d_bitmask, s); }));
+  } else if (algo == ABCORE_GCC) {
     const bool pull = g->pull_mode != 1;
     // On an unchanged graph the scan's survivors are known in advance (the
     // ranks below K of each layer) and so are the frontier's entries: a
@@ -1550,6 +1555,11 @@ abcore_status abcore_compute_batch(abcore_graph h, const uint32_t *h_alpha,
   if (g->peel_mode != 3) {
     TRY(run_batch(*g, plan, tu.data(), tl.data(), d_bitmasks, s));
     return read_state(*g, s);
+  }
+  if (tiny_ready(*g, q)) {
+    CHK(launch_tiny(*g, tu.data(), tl.data(), q, d_bitmasks, s));
+    CHK(hipStreamSynchronize(s));
+    return ABCORE_OK;
   }
   std::vector<int32_t> key;
   key.reserve(2 * (size_t)q + 8);

@@ -347,6 +347,13 @@ struct WindowRecord {
 };
 
 // Peel flavours.
+// Where a scoped query's answer goes (PeelArgs::ans_out): pinned words, and
+// the two endpoints.
+struct Answer {
+  int32_t *out = nullptr;
+  int32_t x = -1, y = -1;
+};
+
 enum PeelKind : int { kGCC = 0, kGCCPlus = 1, kKCore = 2 };
 
 // Parameters of a peel, passed by value to kernels.
@@ -419,6 +426,11 @@ struct PeelArgs {
   // Host-visible word (pinned, coherent; nullable) the peel sets when it
   // ends by an abort, so the host learns of it without a synchronisation.
   int32_t *abort_host;
+  // Scoped queries (nullable): the membership of ans_x (bit 0) and ans_y (bit
+  // 1) after termination, and in ans_out[3] whether the peel aborted, written
+  // to host-visible (pinned) words; nothing else has to be read back.
+  int32_t *ans_out;
+  int32_t ans_x, ans_y;
   // Sub-queue every append tries first (-1: the producer's own; a fixed one
   // makes appends overflow into the others, ABCORE_OPT_APPEND_SUBQUEUE).
   int32_t append_sub;
@@ -511,7 +523,8 @@ hipError_t launch_pull_round(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
 // no start phase, fix_bits serves as the decrement filter only.
 hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL,
                                    const uint32_t *fix_bits, uint32_t *pack_bits,
-                                   hipStream_t s, bool split_done = false);
+                                   hipStream_t s, bool split_done = false,
+                                   const Answer &ans = Answer());
 hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s);
 // Up to `rounds` binned push rounds (each decides on the device whether it is
 // worth running) after a pull kernel that was launched with bin = true.
@@ -536,6 +549,12 @@ hipError_t launch_scan_component_of(Graph &g, int32_t thrU, int32_t thrL, int32_
 hipError_t launch_scan_component_view(Graph &g, const PeelArgs &a, int32_t x, int32_t y,
                                       const int32_t *corr_x, const int32_t *corr_d, int ncorr,
                                       uint32_t *bits, hipStream_t s);
+// The same and the workspace reset in one launch, ahead of a pull round with
+// queue_f0: bits receives the survivors and fbits the frontier (which the pull
+// kernel queues if it pushes).
+hipError_t launch_scan_component_reset(const Graph &g, const PeelArgs &a, int32_t x, int32_t y,
+                                       const int32_t *corr_x, const int32_t *corr_d, int ncorr,
+                                       uint32_t *bits, uint32_t *fbits, hipStream_t s);
 // Pull-form first round for any working set: bits are the scan's survivors;
 // corr_x/corr_d (ncorr entries, nullable) the degree corrections the scan
 // applied (served views).
@@ -590,7 +609,6 @@ abcore_status build_pieces(Graph &g, BuildScratch &w, hipStream_t s);
 // Degree ranks and the rank-sorted adjacency copy (Graph::rank, rcols); on
 // an allocation failure it leaves them null and succeeds.
 abcore_status build_ranks(Graph &g, BuildScratch &w, hipStream_t s);
-hipError_t launch_answer_view(const PeelArgs &a, int32_t x, int32_t y, hipStream_t s);
 // After a peel scoped to the components of vx and vy: the survivors of that
 // scope, or with `connected` those reachable from vx or vy through
 // survivors, into d_bits (every word); *count (nullable) their number.

@@ -311,16 +311,22 @@ hipError_t timed(Graph &g, int kind, hipStream_t s, int64_t nlaunch, F launch) {
   return hipSuccess;
 }
 
-abcore_status read_state(Graph &g, hipStream_t s) {
-  CHK(hipMemcpyAsync(g.h_state, g.state, sizeof(PeelState), hipMemcpyDeviceToHost, s));
-  CHK(hipStreamSynchronize(s));
-  if (g.h_state->abort_flag) {
+// Reports an abort of the computation whose state the host has.
+abcore_status check_state(Graph &g) {
+  if (g.h_state->abort_flag ||
+      (g.h_abort != nullptr && __atomic_load_n(g.h_abort, __ATOMIC_ACQUIRE) != 0)) {
     g.rs_ready = false;  // the next query in rank order prepares the workspace
     if (g.h_abort) __atomic_store_n(g.h_abort, 0, __ATOMIC_RELEASE);  // reported here
     set_error("a device-side wait exceeded its spin limit; the result is invalid");
     return ABCORE_EDEVICE;
   }
   return ABCORE_OK;
+}
+
+abcore_status read_state(Graph &g, hipStream_t s) {
+  CHK(hipMemcpyAsync(g.h_state, g.state, sizeof(PeelState), hipMemcpyDeviceToHost, s));
+  CHK(hipStreamSynchronize(s));
+  return check_state(g);
 }
 
 // Reports a spin-limit abort of an earlier asynchronous computation on the
@@ -419,7 +425,8 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
                              uint32_t *bits, hipStream_t s, int64_t *launches,
                              bool queue_f0 = false, const uint32_t *rowbits = nullptr,
                              bool force = false, bool rest_part = false, bool rank = false,
-                             const uint32_t *f0bits = nullptr) {
+                             const uint32_t *f0bits = nullptr,
+                             const Answer &ans = Answer()) {
   const bool fused = g.peel_mode == 3;
   rank = rank && fused && g.rcols != nullptr;
   // large frontiers pushed by binned rounds (the scan left its frontier in a
@@ -441,7 +448,7 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
     CHK(timed(g, ABCORE_KERNEL_PEEL, s, 1, [&] {
       return launch_peel_async_fused(g, kind, thrU, thrL,
                                      pull ? (rowbits ? rowbits : g.alive_bits) : nullptr, bits,
-                                     s, rank && pull);
+                                     s, rank && pull, ans);
     }));
     *launches += 1;
     return ABCORE_OK;
@@ -451,6 +458,24 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
     CHK(timed(g, ABCORE_KERNEL_PACK, s, 1,
               [&] { return launch_pack(g, thrU, thrL, bits, s); }));
   return ABCORE_OK;
+}
+
+// Algorithm 1 scoped to the components of x and y, on a workspace in any
+// state; the first round in pull form when the frontier is heavy.
+abcore_status scoped_peel(Graph &g, int32_t x, int32_t y, int32_t thrU, int32_t thrL,
+                          const Answer &ans, hipStream_t s) {
+  int64_t launches = 0;
+  const bool pull = g.pull_mode != 1;
+  if (pull && g.peel_mode == 3) {
+    CHK(launch_scan_component_reset(g, make_args(g, thrU, thrL), x, y, nullptr, nullptr, 0,
+                                    g.alive_bits, g.row_bits, s));
+    return pull_peel_pack(g, kGCC, thrU, thrL, true, nullptr, s, &launches, true, nullptr, false,
+                          false, false, g.row_bits, ans);
+  }
+  CHK(launch_init_state(g, s));
+  CHK(launch_scan_component_of(g, thrU, thrL, x, y, s));
+  return pull_peel_pack(g, kGCC, thrU, thrL, pull, nullptr, s, &launches, false, nullptr, false,
+                        false, false, nullptr, ans);
 }
 
 abcore_status compute_core(Graph &g, hipStream_t s) {
@@ -1647,9 +1672,9 @@ static abcore_status query_impl(Graph *g, abcore_edge_update upd, uint32_t alpha
   TRY(ensure_delta(*g, s));
   if (d_set != nullptr && connected) TRY(ensure(&g->parent, g->n));
   // 1. apply the update (validated on the device before any write)
-  CHK(launch_init_state(*g, s));
+  // (it writes its result to the pinned state)
   CHK(launch_update(*g, upd.u, upd.v, upd.op, g->delta.count, s));
-  TRY(read_state(*g, s));
+  CHK(hipStreamSynchronize(s));
   const int32_t ustat = g->h_state->status;
   if (ustat == -(int32_t)ABCORE_EEXIST) {
     set_error("%s: edge (%d, %d) already present", fn, upd.u, upd.v);
@@ -1674,13 +1699,15 @@ static abcore_status query_impl(Graph *g, abcore_edge_update upd, uint32_t alpha
   }
   // 3. scoped peel: Algorithm 1 on the component(s) of u and v only
   const int32_t thrU = clamp_thr(alpha), thrL = clamp_thr(beta);
-  int64_t launches = 0;
-  CHK(launch_init_state(*g, s));
-  CHK(launch_scan_component_of(*g, thrU, thrL, x, y, s));
-  // the first round in pull form when the frontier is heavy
-  TRY(pull_peel_pack(*g, kGCC, thrU, thrL, g->pull_mode != 1, nullptr, s, &launches));
-  CHK(launch_answer(*g, x, y, thrU, thrL, s));
-  TRY(read_state(*g, s));
+  if (g->peel_mode == 3) {
+    TRY(scoped_peel(*g, x, y, thrU, thrL, Answer{&g->h_state->aux0, x, y}, s));
+    CHK(hipStreamSynchronize(s));
+    TRY(check_state(*g));
+  } else {
+    TRY(scoped_peel(*g, x, y, thrU, thrL, Answer(), s));
+    CHK(launch_answer(*g, x, y, thrU, thrL, s));
+    TRY(read_state(*g, s));
+  }
   const int32_t bits = g->h_state->aux0;
   *h_answer = (bits & 3) == 3 ? 1 : 0;
   if (h_endpoint_bits) *h_endpoint_bits = (uint32_t)bits;
@@ -1809,10 +1836,7 @@ abcore_status abcore_community(abcore_graph h, int32_t q, uint32_t alpha, uint32
   if (connected) TRY(ensure(&g->parent, g->n));
   // Algorithm 1 on q's connected component only, as GFQ scopes its peel
   const int32_t thrU = clamp_thr(alpha), thrL = clamp_thr(beta);
-  int64_t launches = 0;
-  CHK(launch_init_state(*g, s));
-  CHK(launch_scan_component_of(*g, thrU, thrL, q, q, s));
-  TRY(pull_peel_pack(*g, kGCC, thrU, thrL, g->pull_mode != 1, nullptr, s, &launches));
+  TRY(scoped_peel(*g, q, q, thrU, thrL, Answer(), s));
   return scoped_set(*g, q, q, thrU, thrL, connected != 0, d_bitmask, out_count, s);
 }
 

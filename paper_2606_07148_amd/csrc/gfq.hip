@@ -361,6 +361,14 @@ __device__ int64_t row_find(const int32_t *cols, int64_t a, int64_t b, int32_t t
   return a;
 }
 
+// What the host reads of an update (the same words of the pinned state).
+struct UpdateResult {
+  int32_t status, aux0, aux1;
+};
+static_assert(offsetof(PeelState, aux0) == offsetof(PeelState, status) + 4 &&
+                  offsetof(PeelState, aux1) == offsetof(PeelState, status) + 8,
+              "the result's words are the state's");
+
 // Applies one update (one thread).  Validation precedes every write,
 // so a rejected update leaves the graph untouched.  st->status: 0 applied,
 // 1 applied using the new delta slot `slot`, -5 present (insertion),
@@ -369,7 +377,7 @@ __device__ int64_t row_find(const int32_t *cols, int64_t a, int64_t b, int32_t t
 __device__ void apply_update(const int64_t *off, int32_t *cols, int32_t *deg0,
                              const int32_t *comp, int32_t *ins_head, int32_t *ins_next,
                              int32_t *ins_other, int64_t slot, int32_t nU, int32_t u, int32_t v,
-                             int32_t op, PeelState *st) {
+                             int32_t op, UpdateResult *st) {
   const int32_t x = u, y = nU + v;
   st->aux0 = comp != nullptr ? comp[x] : -1;
   st->aux1 = comp != nullptr ? comp[y] : -1;
@@ -462,16 +470,32 @@ constexpr int kSettleScan = 1024;
 __global__ __launch_bounds__(kSettleBlock) void update_kernel(
     const int64_t *off, int32_t *cols, int32_t *deg0, int32_t *comp, int32_t *ins_head,
     int32_t *ins_next, int32_t *ins_other, int64_t slot, int32_t nU, int32_t u, int32_t v,
-    int32_t op, int settle, PeelState *st) {
+    int32_t op, int settle, UpdateResult *out) {
   __shared__ int32_t row[kSettleRow];
   __shared__ int s_found;
+  __shared__ UpdateResult s_res;
+  UpdateResult *st = &s_res;
   if (threadIdx.x == 0) {
     s_found = 0;
     apply_update(off, cols, deg0, comp, ins_head, ins_next, ins_other, slot, nU, u, v, op, st);
   }
-  if (op > 0 || !settle) return;
+  // the result, to host-visible memory (a copy of the state took 4 us more)
+  auto publish = [&]() {
+    if (threadIdx.x != 0) return;
+    const int32_t v[3] = {s_res.status, s_res.aux0, s_res.aux1};
+    int32_t *to = &out->status;
+    for (int i = 0; i < 3; ++i)
+      __hip_atomic_store(to + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
+  if (op > 0 || !settle) {
+    publish();
+    return;
+  }
   __syncthreads();  // the deletion is visible to the workgroup
-  if (st->status != 0) return;
+  if (st->status != 0) {
+    publish();
+    return;
+  }
   const int32_t x = u, y = nU + v;
   const int32_t dx = deg0[x], dy = deg0[y];
   __syncthreads();  // (status is rewritten below)
@@ -483,6 +507,7 @@ __global__ __launch_bounds__(kSettleBlock) void update_kernel(
       if (dx == 0) comp[x] = x;
       st->status = 2;
     }
+    publish();
     return;
   }
   const int64_t xa = off[x];
@@ -522,6 +547,7 @@ __global__ __launch_bounds__(kSettleBlock) void update_kernel(
   }
   __syncthreads();
   if (threadIdx.x == 0 && s_found) st->status = 2;
+  publish();
 }
 
 // A window of served updates, applied in order on a single thread (the order
@@ -538,8 +564,14 @@ __global__ void update_window_kernel(const int64_t *off, int32_t *cols, int32_t 
                                      const int32_t *comp, int32_t *ins_head, int32_t *ins_next,
                                      int32_t *ins_other, int32_t *del_ver,
                                      int32_t *pair_del_ver, int32_t pair_base,
-                                     int32_t ver_base, int32_t nU, const int32_t *upd, int w,
+                                     int32_t ver_base, int32_t nU, const int32_t *h_upd, int w,
                                      WindowRecord *rec) {
+  // (the window comes from, and its records go to, pinned host memory: the
+  // copies took longer than the kernel; all of it is read at once)
+  __shared__ int32_t upd[3 * kWindowMax];
+  for (int i = threadIdx.x; i < 3 * w; i += blockDim.x) upd[i] = h_upd[i];
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   int32_t ver = ver_base, pairs = pair_base;
   for (int i = 0; i < w; ++i) {
     const int32_t x = upd[3 * i], y = nU + upd[3 * i + 1], op = upd[3 * i + 2];
@@ -839,7 +871,8 @@ hipError_t launch_update(Graph &g, int32_t u, int32_t v, int32_t op, int64_t slo
   const bool settle = op < 0 && g.comp_valid && g.comp_exact;
   update_kernel<<<1, settle ? kSettleBlock : kWave, 0, s>>>(
       g.off, g.cols, g.deg0, g.comp_valid ? g.comp : nullptr, g.delta.head, g.delta.next,
-      g.delta.other, slot, g.nU, u, v, op, settle ? 1 : 0, g.state);
+      g.delta.other, slot, g.nU, u, v, op, settle ? 1 : 0,
+      reinterpret_cast<UpdateResult *>(&g.h_state->status));
   return hipGetLastError();
 }
 
@@ -849,14 +882,9 @@ hipError_t launch_answer(Graph &g, int32_t x, int32_t y, int32_t thrU, int32_t t
   return hipGetLastError();
 }
 
-hipError_t launch_answer_view(const PeelArgs &a, int32_t x, int32_t y, hipStream_t s) {
-  answer_kernel<<<1, 1, 0, s>>>(a.deg, x, y, a.thrU, a.thrL, a.st);
-  return hipGetLastError();
-}
-
 hipError_t launch_update_window(Graph &g, const int32_t *d_upd, int w, WindowRecord *d_rec,
                                 hipStream_t s) {
-  update_window_kernel<<<1, 1, 0, s>>>(g.off, g.cols, g.deg0, g.comp, g.delta.head,
+  update_window_kernel<<<1, kWave, 0, s>>>(g.off, g.cols, g.deg0, g.comp, g.delta.head,
                                        g.delta.next, g.delta.other, g.del_ver, g.pair_del_ver,
                                        (int32_t)g.delta.count, g.upd_version, g.nU, d_upd, w,
                                        d_rec);

@@ -158,6 +158,9 @@ PeelArgs make_args(Graph &g, int32_t thrU, int32_t thrL) {
   a.spin_limit = g.spin_limit > 0 ? g.spin_limit : kAsyncSpinLimit;
   a.abort_host = g.h_abort;
   a.append_sub = g.append_sub;
+  a.ans_out = nullptr;
+  a.ans_x = -1;
+  a.ans_y = -1;
   a.dbg_enqueue = g.dbg_enqueue;
   // any launch but a query in rank order may leave the queue in use
   g.rs_ready = false;
@@ -581,16 +584,30 @@ hipError_t launch_scan_nested(Graph &g, int32_t pU, int32_t pL, int32_t thrU, in
 // an LDS hash table probed per scanned vertex.
 constexpr int kCorrHash = 256;  // > 2 * kCorrMax, power of two
 
+// kReset: the workspace is reset by the same launch (as in
+// scan_reset_gcc_kernel), the frontier goes to fbits and is queued by the pull
+// kernel if that pushes it.
+template <bool kReset>
 __global__ __launch_bounds__(kScanBlock) void scan_component_kernel(
     PeelArgs a, const int32_t *__restrict__ deg0, const int32_t *__restrict__ comp, int64_t n,
     int32_t vx, int32_t vy, const int32_t *__restrict__ corr_x,
-    const int32_t *__restrict__ corr_d, int ncorr, uint32_t *__restrict__ bits) {
+    const int32_t *__restrict__ corr_d, int ncorr, uint32_t *__restrict__ bits,
+    uint32_t *__restrict__ fbits) {
   __shared__ ScanCollector col;
   __shared__ int64_t s_acc;
   __shared__ int32_t h_key[kCorrHash];
   __shared__ int32_t h_val[kCorrHash];
   if (threadIdx.x == 0) col.count = 0;
   for (int i = threadIdx.x; i < kCorrHash; i += blockDim.x) h_key[i] = -1;
+  if (kReset) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    clear_used_queue(a.queue, a.qcap, a.st, tid, stride);
+    const int64_t nparts = (int64_t)kMaxBlocks * kPartFields;
+    for (int64_t i = (int64_t)gridDim.x * kPartFields + tid; i < nparts; i += stride)
+      a.part[i] = 0;
+    if (threadIdx.x < kPartFields) a.part[(int64_t)blockIdx.x * kPartFields + threadIdx.x] = 0;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int i = 0; i < ncorr; ++i) {
@@ -613,21 +630,26 @@ __global__ __launch_bounds__(kScanBlock) void scan_component_kernel(
        cb += (int64_t)gridDim.x * kScanChunk) {
     for (int t = 0; t < kScanChunk; t += kScanBlock * 4) {
       const int64_t x0 = cb + t + (int64_t)threadIdx.x * 4;
-      uint32_t alive = 0;
-      int32_t cc[4] = {-1, -1, -1, -1};
+      uint32_t alive = 0, front = 0;
+      int32_t cc[4] = {-1, -1, -1, -1}, d0[4] = {0, 0, 0, 0};
       if (x0 + 3 < n) {
-        int4 c = *reinterpret_cast<const int4 *>(comp + x0);
+        const int4 c = *reinterpret_cast<const int4 *>(comp + x0);
+        const int4 v = *reinterpret_cast<const int4 *>(deg0 + x0);
         cc[0] = c.x; cc[1] = c.y; cc[2] = c.z; cc[3] = c.w;
+        d0[0] = v.x; d0[1] = v.y; d0[2] = v.z; d0[3] = v.w;
       } else {
         for (int j = 0; j < 4; ++j)
-          if (x0 + j < n) cc[j] = comp[x0 + j];
+          if (x0 + j < n) {
+            cc[j] = comp[x0 + j];
+            d0[j] = deg0[x0 + j];
+          }
       }
       int32_t items[4];
       int cnt = 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (x0 + j < n && (cc[j] == c1 || cc[j] == c2)) {
-          int32_t d = deg0[x0 + j];
+          int32_t d = d0[j];
           if (ncorr > 0) {
             const int32_t key = (int32_t)(x0 + j);
             uint32_t hsl = ((uint32_t)key * 2654435761u) >> 24;
@@ -645,10 +667,18 @@ __global__ __launch_bounds__(kScanBlock) void scan_component_kernel(
           if (d < ((x0 + j) < a.nU ? a.thrU : a.thrL)) {
             items[cnt++] = (int32_t)(x0 + j);
             f0deg += d;
+            front |= 1u << j;
           } else {
             alive |= 1u << j;
           }
         }
+      }
+      if (kReset) {
+        uint32_t fd = front << (4 * (lane_id() & 7));
+        fd |= __shfl_xor(fd, 1, kWave);
+        fd |= __shfl_xor(fd, 2, kWave);
+        fd |= __shfl_xor(fd, 4, kWave);
+        if ((lane_id() & 7) == 0 && x0 < n) fbits[x0 / 32] = fd;
       }
       if (bits != nullptr) {
         // eight consecutive threads hold the 32 vertices of one bitmap word
@@ -659,21 +689,41 @@ __global__ __launch_bounds__(kScanBlock) void scan_component_kernel(
         if ((lane_id() & 7) == 0 && x0 < n) bits[x0 / 32] = wd;
       }
       f0 += cnt;
-      col.append(items, cnt);
+      if (!kReset) col.append(items, cnt);
     }
-    col.flush_queue(a, sub);
+    if (!kReset) col.flush_queue(a, sub);
   }
   add_part(a.part, kPartF0, f0, &s_acc);
   add_part(a.part, kPartF0Deg, f0deg, &s_acc);
-  if (last_block_done<false>(a.st)) start_rounds_wave(a.st, a.qcap);
+  if (!kReset) {
+    if (last_block_done<false>(a.st)) start_rounds_wave(a.st, a.qcap);
+    return;
+  }
+  __syncthreads();
+  if (wave_in_block() != 0) return;
+  int last = 0;
+  if (lane_id() == 0) last = arrive_on(&a.st->rst) ? 1 : 0;
+  if (!__shfl(last, 0, kWave)) return;
+  int32_t *words = reinterpret_cast<int32_t *>(a.st);
+  constexpr int kRstBegin = (int)(offsetof(PeelState, rst) / 4);
+  for (int i = lane_id(); i < kRstBegin; i += kWave) words[i] = 0;
+}
+
+hipError_t launch_scan_component_reset(const Graph &g, const PeelArgs &a, int32_t x, int32_t y,
+                                       const int32_t *corr_x, const int32_t *corr_d, int ncorr,
+                                       uint32_t *bits, uint32_t *fbits, hipStream_t s) {
+  if (ncorr < 0 || ncorr > kCorrMax) return hipErrorInvalidValue;
+  scan_component_kernel<true><<<scan_grid(g), kScanBlock, 0, s>>>(
+      a, g.deg0, g.comp, g.n, x, y, corr_x, corr_d, ncorr, bits, fbits);
+  return hipGetLastError();
 }
 
 hipError_t launch_scan_component_of(Graph &g, int32_t thrU, int32_t thrL, int32_t x, int32_t y,
                                     hipStream_t s) {
   PeelArgs a = make_args(g, thrU, thrL);
-  scan_component_kernel<<<scan_grid(g), kScanBlock, 0, s>>>(
+  scan_component_kernel<false><<<scan_grid(g), kScanBlock, 0, s>>>(
       a, g.deg0, g.comp, g.n, x, y, nullptr, nullptr, 0,
-      g.pull_mode != 1 ? g.alive_bits : nullptr);
+      g.pull_mode != 1 ? g.alive_bits : nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -681,8 +731,8 @@ hipError_t launch_scan_component_view(Graph &g, const PeelArgs &a, int32_t x, in
                                       const int32_t *corr_x, const int32_t *corr_d, int ncorr,
                                       uint32_t *bits, hipStream_t s) {
   if (ncorr < 0 || ncorr > kCorrMax) return hipErrorInvalidValue;
-  scan_component_kernel<<<scan_grid(g), kScanBlock, 0, s>>>(a, g.deg0, g.comp, g.n, x, y,
-                                                            corr_x, corr_d, ncorr, bits);
+  scan_component_kernel<false><<<scan_grid(g), kScanBlock, 0, s>>>(
+      a, g.deg0, g.comp, g.n, x, y, corr_x, corr_d, ncorr, bits, nullptr);
   return hipGetLastError();
 }
 
@@ -1275,6 +1325,15 @@ __global__ __launch_bounds__(kPeelBlock) void peel_async_kernel(PeelArgs a) {
   }
   const bool aborted = ld_agent(&a.st->abort_flag) != 0;
   if (aborted && threadIdx.x == 0) report_abort(a);
+  if (KIND == kGCC && a.ans_out != nullptr && gw == 0 && lane_id() == 0) {
+    // a scoped query's answer, straight to the host (a kernel and a copy of
+    // the state for it took 10 us of a query)
+    const int32_t in = (ld_agent(&a.deg[a.ans_x]) >= (a.ans_x < a.nU ? a.thrU : a.thrL) ? 1 : 0) |
+                       (ld_agent(&a.deg[a.ans_y]) >= (a.ans_y < a.nU ? a.thrU : a.thrL) ? 2 : 0);
+    __hip_atomic_store(&a.ans_out[0], in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&a.ans_out[3], aborted ? 1 : 0, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   if (a.rs_next_st != nullptr && aborted) {
     // ended by an abort: other workgroups may still use the queue
     if (threadIdx.x == 0) st_agent(a.rs_fail, 1);
@@ -1329,7 +1388,7 @@ hipError_t launch_peel_async_args(Graph &g, PeelKind kind, const PeelArgs &a, in
 
 hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL,
                                    const uint32_t *fix_bits, uint32_t *pack_bits,
-                                   hipStream_t s, bool split_done) {
+                                   hipStream_t s, bool split_done, const Answer &ans) {
   PeelArgs a = make_args(g, thrU, thrL);
   const int grid = async_peel_grid(g);
   if (split_done) {
@@ -1342,6 +1401,9 @@ hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_
     a.alive0 = fix_bits;
   }
   a.pack_bits = pack_bits;
+  a.ans_out = ans.out;
+  a.ans_x = ans.x;
+  a.ans_y = ans.y;
   return launch_peel_async_args(g, kind, a, grid, s);
 }
 

@@ -59,10 +59,10 @@ struct Slot {
   int32_t *queue = nullptr;
   PeelState *state = nullptr;
   int64_t *part = nullptr;
-  uint32_t *bits = nullptr;   // survivors of the scan (pull round)
+  uint32_t *bits = nullptr;   // survivors of the scan (pull round), then its frontier
   int32_t *d_corr = nullptr;  // 2 * kCorrMax: vertices, then deltas
   int32_t *h_corr = nullptr;  // pinned staging of d_corr
-  int32_t *h_out = nullptr;   // pinned: aux0, aux1, pulled, abort_flag of the state
+  int32_t *h_out = nullptr;   // pinned: the answer (PeelArgs::ans_out)
   hipEvent_t scanned = nullptr, done = nullptr;
   bool busy = false;
   Request req{};
@@ -86,8 +86,8 @@ struct Server {
   int window_max = kWindowMax;
   hipStream_t main = nullptr;
   hipEvent_t applied = nullptr;
-  int32_t *d_upd = nullptr, *h_upd = nullptr;  // 3 * kWindowMax
-  WindowRecord *d_rec = nullptr, *h_rec = nullptr;
+  int32_t *h_upd = nullptr;       // pinned: 3 * kWindowMax
+  WindowRecord *h_rec = nullptr;  // pinned
   std::vector<hipEvent_t> last_scans;  // scans of the previous window
   // Stale core-number pruning (Graph::serve_prune > 0): a snapshot of the
   // core numbers (Definition 2) and, per snapshot value c, how far the core
@@ -128,16 +128,17 @@ void free_server_device(Server &S) {
   S.slots.clear();
   if (S.main) (void)hipStreamDestroy(S.main);
   if (S.applied) (void)hipEventDestroy(S.applied);
-  if (S.d_upd) (void)dev_free(S.d_upd);
   if (S.h_upd) (void)hipHostFree(S.h_upd);
-  if (S.d_rec) (void)dev_free(S.d_rec);
   if (S.h_rec) (void)hipHostFree(S.h_rec);
   S.main = nullptr;
   S.applied = nullptr;
-  S.d_upd = S.h_upd = nullptr;
-  S.d_rec = S.h_rec = nullptr;
+  S.h_upd = nullptr;
+  S.h_rec = nullptr;
   S.last_scans.clear();
 }
+
+// Words of a vertex bitmap, in whole 16 bytes.
+int64_t bit_words(const Graph &g) { return std::max<int64_t>((g.n + 127) / 128 * 4, 4); }
 
 hipError_t alloc_slot(Graph &g, Slot &s) {
   hipError_t e = hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking);
@@ -149,7 +150,7 @@ hipError_t alloc_slot(Graph &g, Slot &s) {
   if (e == hipSuccess) e = dev_malloc(&s.part, sizeof(int64_t) * kMaxBlocks * kPartFields);
   if (e == hipSuccess) e = dev_malloc(&s.d_corr, sizeof(int32_t) * 2 * kCorrMax);
   if (e == hipSuccess)
-    e = dev_malloc(&s.bits, sizeof(uint32_t) * std::max<int64_t>((g.n + 31) / 32, 1));
+    e = dev_malloc(&s.bits, 2 * sizeof(uint32_t) * bit_words(g));
   if (e == hipSuccess) e = hipHostMalloc(&s.h_corr, sizeof(int32_t) * 2 * kCorrMax);
   if (e == hipSuccess) e = hipHostMalloc(&s.h_out, sizeof(int32_t) * 4);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&s.scanned, hipEventDisableTiming);
@@ -276,10 +277,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     S.h_upd[3 * i + 1] = win[i].v;
     S.h_upd[3 * i + 2] = win[i].op;
   }
-  SCHK(hipMemcpyAsync(S.d_upd, S.h_upd, sizeof(int32_t) * 3 * w, hipMemcpyHostToDevice, S.main));
-  SCHK(launch_update_window(g, S.d_upd, w, S.d_rec, S.main));
-  SCHK(hipMemcpyAsync(S.h_rec, S.d_rec, sizeof(WindowRecord) * w, hipMemcpyDeviceToHost,
-                      S.main));
+  SCHK(launch_update_window(g, S.h_upd, w, S.h_rec, S.main));
   SCHK(hipStreamSynchronize(S.main));
   // merge the labels joined by the window's insertions (labels are the
   // smallest id of their component, so a merge keeps the smaller)
@@ -386,31 +384,38 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     if (c > 0)
       SCHK(hipMemcpyAsync(s.d_corr, s.h_corr, sizeof(int32_t) * 2 * kCorrMax,
                           hipMemcpyHostToDevice, s.stream));
-    SCHK(launch_init_workspace(g, s.queue, s.state, s.part, s.stream));
     // the first round as a single query takes it: pulled when the device
     // finds it cheaper from the scan's sums (ABCORE_OPT_PULL 0), always (2)
     // or never (1)
     const bool pull = g.pull_mode != 1;
-    SCHK(launch_scan_component_view(g, a, x, y, s.d_corr, s.d_corr + kCorrMax, c,
-                                    pull ? s.bits : nullptr, s.stream));
     PeelArgs ap = a;
     if (pull) {
-      // the pull round's completion runs in the peel's start phase
+      // the scan resets the workspace; the pull round queues the frontier if
+      // it pushes it, and its completion runs in the peel's start phase
+      uint32_t *front = s.bits + bit_words(g);
+      SCHK(launch_scan_component_reset(g, a, x, y, s.d_corr, s.d_corr + kCorrMax, c, s.bits,
+                                       front, s.stream));
+      a.f0_bits = front;
       SCHK(launch_pull_round_args(g, a, s.bits, s.d_corr, s.d_corr + kCorrMax, c, true,
-                                  s.stream));
+                                  s.stream, true));
+      ap.alive0 = s.bits;
       ap.fix_rows = g.heavy_rows;
       ap.fix_bits = s.bits;
       ap.nfix = g.nheavy;
       ap.start_expect = grid;
+    } else {
+      SCHK(launch_init_workspace(g, s.queue, s.state, s.part, s.stream));
+      SCHK(launch_scan_component_view(g, a, x, y, s.d_corr, s.d_corr + kCorrMax, c, nullptr,
+                                      s.stream));
     }
     // the scan and the pull round read the current degrees: the next
     // window's updates wait for them
     SCHK(hipEventRecord(s.scanned, s.stream));
     S.last_scans.push_back(s.scanned);
+    ap.ans_out = s.h_out;
+    ap.ans_x = x;
+    ap.ans_y = y;
     SCHK(launch_peel_async_args(g, kGCC, ap, grid, s.stream));
-    SCHK(launch_answer_view(a, x, y, s.stream));
-    SCHK(hipMemcpyAsync(s.h_out, &s.state->aux0, sizeof(int32_t) * 4, hipMemcpyDeviceToHost,
-                        s.stream));
     SCHK(hipEventRecord(s.done, s.stream));
     s.req = win[i];
     s.busy = true;
@@ -541,9 +546,7 @@ abcore_status serve_start(Graph &g, int64_t max_inflight, int32_t slots, int32_t
   S.slots.clear();
   hipError_t e = hipStreamCreateWithFlags(&S.main, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&S.applied, hipEventDisableTiming);
-  if (e == hipSuccess) e = dev_malloc(&S.d_upd, sizeof(int32_t) * 3 * kWindowMax);
   if (e == hipSuccess) e = hipHostMalloc(&S.h_upd, sizeof(int32_t) * 3 * kWindowMax);
-  if (e == hipSuccess) e = dev_malloc(&S.d_rec, sizeof(WindowRecord) * kWindowMax);
   if (e == hipSuccess) e = hipHostMalloc(&S.h_rec, sizeof(WindowRecord) * kWindowMax);
   if (e == hipSuccess && g.del_ver == nullptr) {
     e = dev_malloc(&g.del_ver, sizeof(int32_t) * std::max<int64_t>(2 * g.m_csr, 1));

@@ -525,6 +525,7 @@ hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_
                                    const uint32_t *fix_bits, uint32_t *pack_bits,
                                    hipStream_t s, bool split_done = false,
                                    const Answer &ans = Answer());
+int start_blocks(const Graph &g, int grid);
 hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s);
 // Up to `rounds` binned push rounds (each decides on the device whether it is
 // worth running) after a pull kernel that was launched with bin = true.

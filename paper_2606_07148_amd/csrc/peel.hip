@@ -1116,8 +1116,9 @@ __device__ __forceinline__ bool quiescent(PeelState *st, int32_t start_expect, i
 #ifndef ABC_QMASK
 #define ABC_QMASK 3
 #endif
+// A poll's sleep grows to 4 steps: at 16 the waves saw the end 1 us later.
 #ifndef ABC_BACKOFF
-#define ABC_BACKOFF 16
+#define ABC_BACKOFF 4
 #endif
 #ifndef ABC_SLEEP
 #define ABC_SLEEP 4
@@ -1191,11 +1192,12 @@ __global__ __launch_bounds__(kPeelBlock) void peel_async_kernel(PeelArgs a) {
   const int gw = blockIdx.x * waves + wave_in_block();
   const int nw = gridDim.x * waves;
   int64_t fixed = 0;  // split rows the start phase queued
-  if (a.start_expect > 0) {
+  if ((int)blockIdx.x < a.start_expect) {
     // start phase: after a pull round, the split rows below their threshold
-    // (their pieces' counts are complete at the kernel boundary)
+    // (their pieces' counts are complete at the kernel boundary), by the
+    // first workgroups: the others begin with their claims
     if (a.fix_bits != nullptr && ld_agent(&a.st->pulled) == 1) {
-      for (int64_t b = (int64_t)gw * kWave; b < a.nfix; b += (int64_t)nw * kWave) {
+      for (int64_t b = (int64_t)gw * kWave; b < a.nfix; b += (int64_t)a.start_expect * kPeelBlock) {
         const int64_t i = b + lane_id();
         bool push = false;
         int32_t x = -1;
@@ -1375,6 +1377,11 @@ __global__ __launch_bounds__(kPeelBlock) void peel_async_kernel(PeelArgs a) {
   }
 }
 
+// Workgroups that run the start phase: one per kPeelBlock split rows.
+int start_blocks(const Graph &g, int grid) {
+  return (int)std::min<int64_t>(std::max(1, grid), (g.nheavy + kPeelBlock - 1) / kPeelBlock);
+}
+
 hipError_t launch_peel_async_args(Graph &g, PeelKind kind, const PeelArgs &a, int grid,
                                   hipStream_t s) {
   (void)g;
@@ -1397,7 +1404,7 @@ hipError_t launch_peel_async_fused(Graph &g, PeelKind kind, int32_t thrU, int32_
     a.fix_rows = g.heavy_rows;
     a.fix_bits = fix_bits;
     a.nfix = g.nheavy;
-    a.start_expect = grid;
+    a.start_expect = start_blocks(g, grid);
     a.alive0 = fix_bits;
   }
   a.pack_bits = pack_bits;

@@ -402,7 +402,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
       ap.fix_rows = g.heavy_rows;
       ap.fix_bits = s.bits;
       ap.nfix = g.nheavy;
-      ap.start_expect = grid;
+      ap.start_expect = start_blocks(g, grid);
     } else {
       SCHK(launch_init_workspace(g, s.queue, s.state, s.part, s.stream));
       SCHK(launch_scan_component_view(g, a, x, y, s.d_corr, s.d_corr + kCorrMax, c, nullptr,

@@ -586,7 +586,7 @@ hipError_t launch_restricted_init(Graph &g, int32_t thrU, int32_t thrL, int32_t 
 hipError_t launch_kcore_init(Graph &g, hipStream_t s);
 hipError_t launch_kcore_persistent(Graph &g, hipStream_t s);
 hipError_t launch_kcore_steps(Graph &g, int steps, hipStream_t s);
-hipError_t launch_kcore_levels(Graph &g, int levels, hipStream_t s);
+hipError_t launch_kcore_levels(Graph &g, int levels, bool bins, hipStream_t s);
 hipError_t launch_cc(Graph &g, int32_t only_label, hipStream_t s);
 hipError_t launch_reached(Graph &g, const uint32_t *member, int32_t vx, int32_t vy,
                           uint32_t *bits, unsigned long long *count, hipStream_t s);

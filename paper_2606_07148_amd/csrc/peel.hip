@@ -2212,6 +2212,8 @@ hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
 // 0.25 ms.  bin_kernel is bound by the chain of each refill (a
 // group's words, its rows' offsets, their entries), then by LDS and the
 // vector units (a third of its time each), not by memory.
+// kKCore: the first round of a level of the core decomposition (thresholds
+// level + 1; what falls gets the level as its core number).
 // Both do nothing in a round that the rule leaves to the asynchronous peel.
 constexpr int kBinBlock = 1024;
 constexpr int kBinWaves = kBinBlock / kWave;
@@ -2260,6 +2262,7 @@ __device__ __forceinline__ uint32_t bin_start(const int64_t *__restrict__ off, i
          (uint32_t)b * slack;
 }
 
+template <int KIND>
 __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__restrict__ msg,
                                                         uint32_t *__restrict__ tail, int shift,
                                                         int nbuckets, uint32_t slack,
@@ -2277,7 +2280,10 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
   const int64_t items = sh.view.pre[kSub];
   // (a queued vertex survived the scan: its row has at least its threshold's
   // entries)
-  const int64_t guess = items * max(1, (a.thrU / 2 + a.thrL / 2));
+  // (core numbers: at least its level's)
+  const int32_t level = KIND == kKCore ? ld_agent(&a.st->k) : 0;
+  const int64_t guess =
+      items * (KIND == kKCore ? (int64_t)level + 1 : max(1, (a.thrU / 2 + a.thrL / 2)));
   if (!from_bits && guess < max((int64_t)1, a.n / kBinMin)) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) st_agent(&a.st->binned, 1);
   // slots reserved at a time: a quarter of what this workgroup will send to
@@ -2363,6 +2369,8 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
     int d = x >= 0 ? (int)(e_next - s_next) : 0;
     fetch();
     if (x >= 0) {
+      if (KIND == kKCore && a.kdead != nullptr)
+        atomicOr(&a.kdead[x >> 5], 1u << (x & 31));  // removed from here on
       // after a pull round a split row may be queued a second time (see
       // peel_batch): the first consumer marks its degree
       if (d > kPiece && a.fix_bits != nullptr &&
@@ -2372,7 +2380,9 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
         // inserted edges: few, decremented directly
         for (int e = a.ins_head[x]; e >= 0; e = a.ins_next[e]) {
           const int32_t w = a.ins_other[e];
-          if (w >= 0 && atomicSub(&a.deg[w], 1) == (w < a.nU ? a.thrU : a.thrL)) {
+          const int32_t t = KIND == kKCore ? level + 1 : (w < a.nU ? a.thrU : a.thrL);
+          if (w >= 0 && atomicSub(&a.deg[w], 1) == t) {
+            if (KIND == kKCore) st_agent(&a.core[w], level);
             const int2 r = reserve_slots(a.st, a.queue, a.qcap,
                                          append_pref(a, blockIdx.x % kSub), 1, a.abort_host);
             if (r.x >= 0) st_agent(&a.queue[(int64_t)r.x * a.qcap + r.y], w);
@@ -2557,6 +2567,7 @@ struct ApplyShared {
   int s_cnt[kBinWaves + 2];
 };
 
+template <int KIND>
 __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
                                                           const uint16_t *__restrict__ msg,
                                                           uint32_t *__restrict__ tail, int shift,
@@ -2578,6 +2589,9 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
     // eight messages to a 16-byte load (a bucket starts on a whole line)
     const uint32_t m0 = bin_start(a.off, blockIdx.x, shift, slack), m1 = m0 + count;
     const int upper = (int)min(max((int64_t)a.nU - lo, (int64_t)0), (int64_t)span);
+    const int32_t level = KIND == kKCore ? ld_agent(&a.st->k) : 0;
+    const int32_t tU = KIND == kKCore ? level + 1 : a.thrU;
+    const int32_t tL = KIND == kKCore ? level + 1 : a.thrL;
     for (uint32_t b = m0 + 8 * (threadIdx.x & ~(kWave - 1)); b < m1; b += 8 * kBinBlock) {
       const uint32_t i = b + 8 * (uint32_t)lane_id();
       uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
@@ -2592,7 +2606,9 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int o = (int)((word[q / 2] >> (16 * (q & 1))) & 0xFFFFu);
-        lq.push(old[q] == (o < upper ? a.thrU : a.thrL), (int32_t)(lo + o));
+        const bool falls = old[q] == (o < upper ? tU : tL);
+        if (KIND == kKCore && falls) a.core[lo + o] = level;
+        lq.push(falls, (int32_t)(lo + o));
       }
     }
     __syncthreads();
@@ -2617,12 +2633,16 @@ bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3
 static uint32_t bin_slack(const Graph &g) { return (uint32_t)(g.cu_count + 1) * kBinChunk; }
 
 static hipError_t prepare_bin_kernels(int nbuckets, int shift) {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bin_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)bin_lds(nbuckets));
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&apply_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 4 << shift);
+  hipError_t e = hipSuccess;
+  for (const void *f : {reinterpret_cast<const void *>(&bin_kernel<kGCC>),
+                        reinterpret_cast<const void *>(&bin_kernel<kKCore>)})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)bin_lds(nbuckets));
+  for (const void *f : {reinterpret_cast<const void *>(&apply_kernel<kGCC>),
+                        reinterpret_cast<const void *>(&apply_kernel<kKCore>)})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 4 << shift);
   return e;
 }
 
@@ -2636,10 +2656,10 @@ hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_
                        s>>>(a);
   const size_t slice = (size_t)4 << g.bin_shift;
   for (int r = 0; r < rounds; ++r) {
-    bin_kernel<<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
+    bin_kernel<kGCC><<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
         a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, bin_slack(g),
         f0bits != nullptr ? f0bits : alive, f0bits != nullptr ? 0u : ~0u, (g.n + 31) / 32);
-    apply_kernel<<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift,
+    apply_kernel<kGCC><<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift,
                                                        bin_slack(g));
   }
   return hipGetLastError();
@@ -3372,13 +3392,20 @@ __global__ __launch_bounds__(kScanBlock) void kcore_level_scan_kernel(PeelArgs a
 #ifndef ABC_KCORE_DEAD_BITS
 #define ABC_KCORE_DEAD_BITS 1
 #endif
-hipError_t launch_kcore_levels(Graph &g, int levels, hipStream_t s) {
+hipError_t launch_kcore_levels(Graph &g, int levels, bool bins, hipStream_t s) {
   PeelArgs a = make_args(g, 0, 0);
   if (ABC_KCORE_DEAD_BITS) a.kdead = g.kdead;
   const int sgrid = std::min(g.cu_count * 4, kMaxBlocks);
   const int agrid = async_peel_grid(g);
   for (int l = 0; l < levels; ++l) {
     kcore_level_scan_kernel<<<sgrid, kScanBlock, 0, s>>>(a, g.list, g.list2);
+    if (bins) {
+      // the level's first round binned, where it is large enough
+      bin_kernel<kKCore><<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
+          a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, bin_slack(g), nullptr, 0, 0);
+      apply_kernel<kKCore><<<g.bin_count, kBinBlock, (size_t)4 << g.bin_shift, s>>>(
+          a, g.bin_msg, g.bin_tail, g.bin_shift, bin_slack(g));
+    }
     peel_async_kernel<kKCore><<<agrid, kPeelBlock, 0, s>>>(a);
   }
   return hipGetLastError();

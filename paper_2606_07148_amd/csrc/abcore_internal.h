@@ -336,6 +336,10 @@ struct Graph {
 // degree corrections for one query's view.
 constexpr int kWindowMax = 64;
 constexpr int kCorrMax = 2 * kWindowMax;
+// A window's updates, u v op each, passed with the launch.
+struct WindowUpdates {
+  int32_t v[3 * kWindowMax];
+};
 
 // Outcome of one served update (update_window_kernel).
 struct WindowRecord {
@@ -629,7 +633,8 @@ abcore_status compute_core_numbers(Graph &g, hipStream_t s);
 abcore_status kcore_top(Graph &g, const int32_t *alive, int64_t cnt, int32_t k0,
                         int max_halves, bool *finished, int32_t *top_max, hipStream_t s);
 abcore_status count_bits(Graph &g, const uint32_t *bits, int64_t *out, hipStream_t s);
-hipError_t launch_update_window(Graph &g, const int32_t *d_upd, int w, WindowRecord *d_rec,
+// rec: host-visible.
+hipError_t launch_update_window(Graph &g, const WindowUpdates &upd, int w, WindowRecord *rec,
                                 hipStream_t s);
 hipError_t launch_relabel(Graph &g, int32_t from, int32_t to, hipStream_t s);
 void set_error(const char *fmt, ...);

@@ -345,20 +345,53 @@ __global__ void relabel_kernel(int32_t *comp, int64_t n, int32_t from, int32_t t
     if (comp[x] == from) comp[x] = to;
 }
 
-// Position of `target` in the sorted CSR row [a, b) (entries compared after
-// decoding tombstones ~c), or -1.
-__device__ int64_t row_find(const int32_t *cols, int64_t a, int64_t b, int32_t target) {
-  while (a < b) {
-    const int64_t mid = a + (b - a) / 2;
-    int32_t c = cols[mid];
-    if (c < 0) c = ~c;
-    if (c < target)
-      a = mid + 1;
-    else
-      b = mid;
+// The entry of y in row x and that of x in row y, by one wave (all lanes): a
+// half of it searches each row, 32 probes to a step (a hub's row of 30,000 in
+// four round trips; a thread's binary searches took 15 each).  Entries are
+// read at device scope: an update before may have just changed them.
+struct PairEntries {
+  int64_t jx, jy;  // positions in cols, -1: not there
+  bool live;       // the entry in row x is not deleted
+};
+__device__ __forceinline__ PairEntries find_pair(const int64_t *off, const int32_t *cols,
+                                                 int32_t x, int32_t y) {
+  const int l = lane_id() & 31;
+  const bool second = lane_id() >= 32;
+  const int32_t row = second ? y : x, key = second ? x : y;
+  int64_t lo = off[row], hi = off[row + 1];
+  auto half = [&](bool p) {
+    const uint64_t m = __ballot(p);
+    return (uint32_t)(second ? m >> 32 : m);
+  };
+  // entries before lo are below the key, those from hi on above it
+  while (__ballot(hi - lo > 32)) {
+    const int64_t len = hi - lo;
+    const int64_t p = lo + len * (l + 1) / 33;
+    bool below = false;
+    if (len > 32) {
+      const int32_t c = ld_agent(&cols[p]);
+      below = (c < 0 ? ~c : c) < key;
+    }
+    const int before = __popc(half(below));
+    if (len > 32) {
+      const int64_t from = lo;
+      if (before > 0) lo = from + len * before / 33 + 1;
+      if (before < 32) hi = from + len * (before + 1) / 33 + 1;
+    }
   }
-  if (a < 0) return -1;
-  return a;
+  int32_t c = -1;
+  bool here = false;
+  if (lo + l < hi) {
+    c = ld_agent(&cols[lo + l]);
+    here = (c < 0 ? ~c : c) == key;
+  }
+  const uint32_t hit = half(here), live = half(here && c >= 0);
+  const int64_t at = hit != 0 ? lo + __ffs((int)hit) - 1 : -1;
+  PairEntries r;
+  r.jx = __shfl((long long)at, 0, kWave);
+  r.jy = __shfl((long long)at, 32, kWave);
+  r.live = __shfl((int)live, 0, kWave) != 0;
+  return r;
 }
 
 // What the host reads of an update (the same words of the pinned state).
@@ -379,23 +412,13 @@ __device__ void apply_update(const int64_t *off, int32_t *cols, int32_t *deg0,
                              int32_t *ins_other, int64_t slot, int32_t nU, int32_t u, int32_t v,
                              int32_t op, UpdateResult *st) {
   const int32_t x = u, y = nU + v;
+  // base CSR entry of the pair (row x holds y, row y holds x)
+  const PairEntries pair = find_pair(off, cols, x, y);
+  if (lane_id() != 0) return;
+  const int64_t jx = pair.jx, jy = pair.jy;
+  const bool csr_live = jx >= 0 && pair.live;
   st->aux0 = comp != nullptr ? comp[x] : -1;
   st->aux1 = comp != nullptr ? comp[y] : -1;
-  // base CSR entry of the pair (row x holds y, row y holds x)
-  int64_t jx = -1, jy = -1;
-  {
-    const int64_t a = off[x], b = off[x + 1];
-    const int64_t p = row_find(cols, a, b, y);
-    if (p < b) {
-      int32_t c = cols[p];
-      if ((c < 0 ? ~c : c) == y) jx = p;
-    }
-  }
-  const bool csr_live = jx >= 0 && cols[jx] >= 0;
-  if (jx >= 0) {
-    const int64_t a = off[y], b = off[y + 1];
-    jy = row_find(cols, a, b, x);
-  }
   // inserted half-edge of the pair in row x (live or deleted)
   int32_t ex = -1;
   for (int32_t e = ins_head != nullptr ? ins_head[x] : -1; e >= 0; e = ins_next[e]) {
@@ -475,10 +498,9 @@ __global__ __launch_bounds__(kSettleBlock) void update_kernel(
   __shared__ int s_found;
   __shared__ UpdateResult s_res;
   UpdateResult *st = &s_res;
-  if (threadIdx.x == 0) {
-    s_found = 0;
+  if (threadIdx.x == 0) s_found = 0;
+  if (wave_in_block() == 0)
     apply_update(off, cols, deg0, comp, ins_head, ins_next, ins_other, slot, nU, u, v, op, st);
-  }
   // the result, to host-visible memory (a copy of the state took 4 us more)
   auto publish = [&]() {
     if (threadIdx.x != 0) return;
@@ -550,7 +572,7 @@ __global__ __launch_bounds__(kSettleBlock) void update_kernel(
   publish();
 }
 
-// A window of served updates, applied in order on a single thread (the order
+// A window of served updates, applied in order by a single wave (the order
 // of the stream: each update is validated against the graph after the
 // previous ones).  Append-only, so that queries of earlier versions still
 // peeling see their own graph: a deleted base entry gets its deletion
@@ -559,36 +581,27 @@ __global__ __launch_bounds__(kSettleBlock) void update_kernel(
 // numbered in insertion order; a query sees pairs below its limit).  Each
 // record: status (0, -EEXIST, -ENOENT), version (valid updates count up from
 // ver_base), pairs after the update, labels of the endpoints before the
-// window.
+// window.  The updates arrive with the launch and
+// the records go to pinned host memory (the copies took longer than the
+// kernel).
 __global__ void update_window_kernel(const int64_t *off, int32_t *cols, int32_t *deg0,
                                      const int32_t *comp, int32_t *ins_head, int32_t *ins_next,
                                      int32_t *ins_other, int32_t *del_ver,
                                      int32_t *pair_del_ver, int32_t pair_base,
-                                     int32_t ver_base, int32_t nU, const int32_t *h_upd, int w,
+                                     int32_t ver_base, int32_t nU, WindowUpdates upd, int w,
                                      WindowRecord *rec) {
-  // (the window comes from, and its records go to, pinned host memory: the
-  // copies took longer than the kernel; all of it is read at once)
-  __shared__ int32_t upd[3 * kWindowMax];
-  for (int i = threadIdx.x; i < 3 * w; i += blockDim.x) upd[i] = h_upd[i];
-  __syncthreads();
-  if (threadIdx.x != 0) return;
   int32_t ver = ver_base, pairs = pair_base;
   for (int i = 0; i < w; ++i) {
-    const int32_t x = upd[3 * i], y = nU + upd[3 * i + 1], op = upd[3 * i + 2];
+    const int32_t x = upd.v[3 * i], y = nU + upd.v[3 * i + 1], op = upd.v[3 * i + 2];
+    const PairEntries pair = find_pair(off, cols, x, y);
+    // the update itself by the first lane; its stores are done before the
+    // next search
+    if (lane_id() != 0) continue;
     WindowRecord r;
     r.label_u = comp[x];
     r.label_v = comp[y];
-    int64_t jx = -1, jy = -1;
-    {
-      const int64_t a = off[x], b = off[x + 1];
-      const int64_t p = row_find(cols, a, b, y);
-      if (p < b) {
-        const int32_t c = cols[p];
-        if ((c < 0 ? ~c : c) == y) jx = p;
-      }
-    }
-    const bool csr_live = jx >= 0 && cols[jx] >= 0;
-    if (csr_live) jy = row_find(cols, off[y], off[y + 1], x);
+    const int64_t jx = pair.jx, jy = pair.jy;
+    const bool csr_live = jx >= 0 && pair.live;
     int32_t ex = -1;  // live inserted half-edge of the pair in row x
     for (int32_t e = pairs > 0 ? ins_head[x] : -1; e >= 0; e = ins_next[e])
       if (ins_other[e] == y) {
@@ -637,6 +650,11 @@ __global__ void update_window_kernel(const int64_t *off, int32_t *cols, int32_t 
     }
     r.pairs_after = pairs;
     rec[i] = r;
+    // (relaxed device-scope stores and loads: a wait orders them, where a
+    // fence would write back the L2)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
   }
 }
 
@@ -882,12 +900,12 @@ hipError_t launch_answer(Graph &g, int32_t x, int32_t y, int32_t thrU, int32_t t
   return hipGetLastError();
 }
 
-hipError_t launch_update_window(Graph &g, const int32_t *d_upd, int w, WindowRecord *d_rec,
+hipError_t launch_update_window(Graph &g, const WindowUpdates &upd, int w, WindowRecord *rec,
                                 hipStream_t s) {
   update_window_kernel<<<1, kWave, 0, s>>>(g.off, g.cols, g.deg0, g.comp, g.delta.head,
                                        g.delta.next, g.delta.other, g.del_ver, g.pair_del_ver,
-                                       (int32_t)g.delta.count, g.upd_version, g.nU, d_upd, w,
-                                       d_rec);
+                                       (int32_t)g.delta.count, g.upd_version, g.nU, upd, w,
+                                           rec);
   return hipGetLastError();
 }
 

@@ -86,7 +86,6 @@ struct Server {
   int window_max = kWindowMax;
   hipStream_t main = nullptr;
   hipEvent_t applied = nullptr;
-  int32_t *h_upd = nullptr;       // pinned: 3 * kWindowMax
   WindowRecord *h_rec = nullptr;  // pinned
   std::vector<hipEvent_t> last_scans;  // scans of the previous window
   // Stale core-number pruning (Graph::serve_prune > 0): a snapshot of the
@@ -128,11 +127,9 @@ void free_server_device(Server &S) {
   S.slots.clear();
   if (S.main) (void)hipStreamDestroy(S.main);
   if (S.applied) (void)hipEventDestroy(S.applied);
-  if (S.h_upd) (void)hipHostFree(S.h_upd);
   if (S.h_rec) (void)hipHostFree(S.h_rec);
   S.main = nullptr;
   S.applied = nullptr;
-  S.h_upd = nullptr;
   S.h_rec = nullptr;
   S.last_scans.clear();
 }
@@ -272,12 +269,13 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
   }
   for (hipEvent_t ev : S.last_scans) SCHK(hipStreamWaitEvent(S.main, ev, 0));
   S.last_scans.clear();
+  WindowUpdates upd = {};
   for (int i = 0; i < w; ++i) {
-    S.h_upd[3 * i] = win[i].u;
-    S.h_upd[3 * i + 1] = win[i].v;
-    S.h_upd[3 * i + 2] = win[i].op;
+    upd.v[3 * i] = win[i].u;
+    upd.v[3 * i + 1] = win[i].v;
+    upd.v[3 * i + 2] = win[i].op;
   }
-  SCHK(launch_update_window(g, S.h_upd, w, S.h_rec, S.main));
+  SCHK(launch_update_window(g, upd, w, S.h_rec, S.main));
   SCHK(hipStreamSynchronize(S.main));
   // merge the labels joined by the window's insertions (labels are the
   // smallest id of their component, so a merge keeps the smaller)
@@ -305,11 +303,16 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
       }
     }
   }
+  bool merged = false;
   for (auto &kv : up)
-    if (find(kv.first) != kv.first) SCHK(launch_relabel(g, kv.first, find(kv.first), S.main));
+    if (find(kv.first) != kv.first) {
+      SCHK(launch_relabel(g, kv.first, find(kv.first), S.main));
+      merged = true;
+    }
   g.core_valid = false;
   g.version += 1;
-  SCHK(hipEventRecord(S.applied, S.main));
+  // (the updates are done: only a relabelling is left to wait for)
+  if (merged) SCHK(hipEventRecord(S.applied, S.main));
   S.windows += 1;
   // the working sets share the co-resident capacity of the peel
   const int cap = g.async_grid > 0 ? g.async_grid : async_peel_grid(g);
@@ -380,7 +383,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     a.ins_head = r.pairs_after > 0 ? g.delta.head : nullptr;
     a.abort_host = nullptr;  // a served abort is reported with its request
     const int32_t x = win[i].u, y = g.nU + win[i].v;
-    SCHK(hipStreamWaitEvent(s.stream, S.applied, 0));
+    if (merged) SCHK(hipStreamWaitEvent(s.stream, S.applied, 0));
     if (c > 0)
       SCHK(hipMemcpyAsync(s.d_corr, s.h_corr, sizeof(int32_t) * 2 * kCorrMax,
                           hipMemcpyHostToDevice, s.stream));
@@ -546,7 +549,6 @@ abcore_status serve_start(Graph &g, int64_t max_inflight, int32_t slots, int32_t
   S.slots.clear();
   hipError_t e = hipStreamCreateWithFlags(&S.main, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&S.applied, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipHostMalloc(&S.h_upd, sizeof(int32_t) * 3 * kWindowMax);
   if (e == hipSuccess) e = hipHostMalloc(&S.h_rec, sizeof(WindowRecord) * kWindowMax);
   if (e == hipSuccess && g.del_ver == nullptr) {
     e = dev_malloc(&g.del_ver, sizeof(int32_t) * std::max<int64_t>(2 * g.m_csr, 1));

@@ -1,6 +1,6 @@
 // Device-wide primitives of the build and the export, called on rocPRIM
-// directly: radix sort of 64-bit keys, selection of unique keys, exclusive
-// prefix sum of 64-bit counts.  Each follows rocPRIM's two-call protocol
+// directly: radix sort of 64-bit keys, exclusive prefix sum of 64-bit
+// counts.  Each follows rocPRIM's two-call protocol
 // (temp == nullptr: *bytes receives the temporary storage needed); counts
 // are size_t, so no input size is narrowed to int.
 #pragma once
@@ -10,7 +10,6 @@
 
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
-#include <rocprim/device/device_select.hpp>
 #include <rocprim/types/double_buffer.hpp>
 
 namespace abc {
@@ -33,12 +32,6 @@ inline hipError_t sort_keys_two(void *temp, size_t &bytes, uint64_t *&cur, uint6
   cur = keys.current();
   alt = keys.alternate();
   return e;
-}
-
-// The first key of every run of equal keys, in order; *count their number.
-inline hipError_t unique(void *temp, size_t &bytes, const uint64_t *in, uint64_t *out,
-                         int *count, size_t n, hipStream_t s) {
-  return rocprim::unique(temp, bytes, in, out, count, n, rocprim::equal_to<uint64_t>(), s);
 }
 
 // out[i] = in[0] + ... + in[i - 1] (out[0] = 0).

@@ -1365,9 +1365,14 @@ abcore_status abcore_compute(abcore_graph h, uint32_t alpha, uint32_t beta, int3
   } else {
     TRY(compute_core(*g, s));
     const int32_t dl = std::min(thrU, thrL), dq = std::max(thrU, thrL);
-    plus_pull = dl != dq && g->peel_mode == 3 && g->pull_mode != 1;
-    if (!plus_pull) CHK(launch_init_state(*g, s));
-    if (dl == dq) {
+    const bool tiny = dl != dq && stats == nullptr && tiny_ready(*g, 1);
+    plus_pull = dl != dq && !tiny && g->peel_mode == 3 && g->pull_mode != 1;
+    if (!plus_pull && !tiny) CHK(launch_init_state(*g, s));
+    if (tiny) {
+      // (the core is unique, and the whole peel cheaper than a classification)
+      CHK(timed(*g, ABCORE_KERNEL_PEEL, s, 1,
+                [&] { return launch_tiny(*g, &thrU, &thrL, 1, d_bitmask, s); }));
+    } else if (dl == dq) {
       CHK(launch_pack_from_core(*g, dl, d_bitmask, s));
     } else if (plus_pull) {
       // the uncertain rows' degrees inside G[{core >= delta_l}] by a pull

@@ -75,6 +75,8 @@ def test_against_oracle(name):
             say("tiny", name, a, b)
             got = bits_np(pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC))
             assert np.array_equal(got, want[(a, b)]), (name, a, b)
+            plus = bits_np(pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC_PLUS))
+            assert np.array_equal(plus, got), (name, a, b)
             # the general path, which keeps the statistics
             out, st = pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC, stats=True)
             assert np.array_equal(bits_np(out), got) and st["removed"] == nU + nL - int(

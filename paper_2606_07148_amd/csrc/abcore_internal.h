@@ -536,6 +536,13 @@ hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
 // f0bits: the frontier's set bits, or nullptr for the clear bits of alive.
 hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_t *alive,
                              const uint32_t *f0bits, int rounds, hipStream_t s);
+// The same for any working set.  The messages' buffers are the handle's: one
+// launch sequence at a time.
+hipError_t launch_bin_rounds_args(const Graph &g, PeelArgs a, const uint32_t *alive,
+                                  const uint32_t *f0bits, int rounds, hipStream_t s);
+// Binned push rounds launched before the asynchronous peel (each a pair of
+// kernels that return at once when the round is too small).
+constexpr int kBinRounds = 3;
 // Whether this handle's computations may run binned rounds.
 bool bin_ready(const Graph &g);
 abcore_status build_bins(Graph &g, hipStream_t s);

@@ -417,10 +417,6 @@ bool rank_counts(const Graph &g, int32_t thrU, int32_t thrL, int64_t &ku, int64_
   return true;
 }
 
-// Binned push rounds launched before the asynchronous peel (each a pair of
-// kernels that return at once when the round is too small).
-constexpr int kBinRounds = 3;
-
 abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL, bool pull,
                              uint32_t *bits, hipStream_t s, int64_t *launches,
                              bool queue_f0 = false, const uint32_t *rowbits = nullptr,

@@ -2212,6 +2212,7 @@ hipError_t launch_pull_fixup(Graph &g, int32_t thrU, int32_t thrL, hipStream_t s
 // 0.25 ms.  bin_kernel is bound by the chain of each refill (a
 // group's words, its rows' offsets, their entries), then by LDS and the
 // vector units (a third of its time each), not by memory.
+// kView: a versioned view, as the asynchronous peel reads one.
 // kKCore: the first round of a level of the core decomposition (thresholds
 // level + 1; what falls gets the level as its core number).
 // Both do nothing in a round that the rule leaves to the asynchronous peel.
@@ -2262,7 +2263,7 @@ __device__ __forceinline__ uint32_t bin_start(const int64_t *__restrict__ off, i
          (uint32_t)b * slack;
 }
 
-template <int KIND>
+template <int KIND, bool kView>
 __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__restrict__ msg,
                                                         uint32_t *__restrict__ tail, int shift,
                                                         int nbuckets, uint32_t slack,
@@ -2378,8 +2379,16 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
         d = 0;
       if (a.ins_head != nullptr) {
         // inserted edges: few, decremented directly
-        for (int e = a.ins_head[x]; e >= 0; e = a.ins_next[e]) {
-          const int32_t w = a.ins_other[e];
+        for (int e = a.ins_head[x], next; e >= 0; e = next) {
+          int32_t w;
+          if (kView && (e >> 1) >= a.pair_limit) {
+            // inserted after this query's version, possibly meanwhile
+            next = ld_agent(&a.ins_next[e]);
+            continue;
+          }
+          next = a.ins_next[e];
+          w = a.ins_other[e];
+          if (kView && w < 0 && ld_agent(&a.pair_del_ver[e >> 1]) > a.ver) w = ~w;
           const int32_t t = KIND == kKCore ? level + 1 : (w < a.nU ? a.thrU : a.thrL);
           if (w >= 0 && atomicSub(&a.deg[w], 1) == t) {
             if (KIND == kKCore) st_agent(&a.core[w], level);
@@ -2417,6 +2426,7 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
       for (int u = 0; u < kBinPer; ++u) {
         const int k = u * kBinBlock + (int)threadIdx.x;
         w[u] = k < d ? a.cols[s + (uint32_t)k] : -1;
+        if (kView) w[u] = view_col(a, k < d, (int64_t)(s + (uint32_t)k), w[u]);
       }
     } else {
 #pragma unroll
@@ -2444,6 +2454,11 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
           at[u] = (uint32_t)__shfl((int)from, j[u] & (kWave - 1), kWave) + (uint32_t)k[u];
 #pragma unroll
         for (int u = 0; u < kBinRefill; ++u) w[u0 + u] = k[u] < total ? a.cols[at[u]] : -1;
+        if (kView) {
+#pragma unroll
+          for (int u = 0; u < kBinRefill; ++u)
+            w[u0 + u] = view_col(a, k[u] < total, (int64_t)at[u], w[u0 + u]);
+        }
         pos += kBinRefill * kWave;
       }
     }
@@ -2634,8 +2649,9 @@ static uint32_t bin_slack(const Graph &g) { return (uint32_t)(g.cu_count + 1) * 
 
 static hipError_t prepare_bin_kernels(int nbuckets, int shift) {
   hipError_t e = hipSuccess;
-  for (const void *f : {reinterpret_cast<const void *>(&bin_kernel<kGCC>),
-                        reinterpret_cast<const void *>(&bin_kernel<kKCore>)})
+  for (const void *f : {reinterpret_cast<const void *>(&bin_kernel<kGCC, false>),
+                        reinterpret_cast<const void *>(&bin_kernel<kGCC, true>),
+                        reinterpret_cast<const void *>(&bin_kernel<kKCore, false>)})
     if (e == hipSuccess)
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)bin_lds(nbuckets));
@@ -2646,23 +2662,28 @@ static hipError_t prepare_bin_kernels(int nbuckets, int shift) {
   return e;
 }
 
-hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_t *alive,
-                             const uint32_t *f0bits, int rounds, hipStream_t s) {
-  PeelArgs a = make_args(g, thrU, thrL);
+hipError_t launch_bin_rounds_args(const Graph &g, PeelArgs a, const uint32_t *alive,
+                                  const uint32_t *f0bits, int rounds, hipStream_t s) {
   a.fix_bits = alive;
   a.fix_rows = g.heavy_rows;
   a.nfix = g.nheavy;
   queue_split_kernel<<<flat_grid(g, std::max<int64_t>(g.nheavy, 1), kPeelBlock), kPeelBlock, 0,
                        s>>>(a);
   const size_t slice = (size_t)4 << g.bin_shift;
+  auto bin = a.del_ver != nullptr ? bin_kernel<kGCC, true> : bin_kernel<kGCC, false>;
   for (int r = 0; r < rounds; ++r) {
-    bin_kernel<kGCC><<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
+    bin<<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
         a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, bin_slack(g),
         f0bits != nullptr ? f0bits : alive, f0bits != nullptr ? 0u : ~0u, (g.n + 31) / 32);
     apply_kernel<kGCC><<<g.bin_count, kBinBlock, slice, s>>>(a, g.bin_msg, g.bin_tail, g.bin_shift,
-                                                       bin_slack(g));
+                                                             bin_slack(g));
   }
   return hipGetLastError();
+}
+
+hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_t *alive,
+                             const uint32_t *f0bits, int rounds, hipStream_t s) {
+  return launch_bin_rounds_args(g, make_args(g, thrU, thrL), alive, f0bits, rounds, s);
 }
 
 // Room for binned rounds: on graphs of enough vertices that the buckets give
@@ -3401,7 +3422,7 @@ hipError_t launch_kcore_levels(Graph &g, int levels, bool bins, hipStream_t s) {
     kcore_level_scan_kernel<<<sgrid, kScanBlock, 0, s>>>(a, g.list, g.list2);
     if (bins) {
       // the level's first round binned, where it is large enough
-      bin_kernel<kKCore><<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
+      bin_kernel<kKCore, false><<<g.cu_count, kBinBlock, bin_lds(g.bin_count), s>>>(
           a, g.bin_msg, g.bin_tail, g.bin_shift, g.bin_count, bin_slack(g), nullptr, 0, 0);
       apply_kernel<kKCore><<<g.bin_count, kBinBlock, (size_t)4 << g.bin_shift, s>>>(
           a, g.bin_msg, g.bin_tail, g.bin_shift, bin_slack(g));

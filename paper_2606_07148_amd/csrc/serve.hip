@@ -86,6 +86,8 @@ struct Server {
   int window_max = kWindowMax;
   hipStream_t main = nullptr;
   hipEvent_t applied = nullptr;
+  hipEvent_t binned = nullptr;  // the binned rounds launched last (the handle's buffers)
+  bool bins_out = false;        // it was recorded
   WindowRecord *h_rec = nullptr;  // pinned
   std::vector<hipEvent_t> last_scans;  // scans of the previous window
   // Stale core-number pruning (Graph::serve_prune > 0): a snapshot of the
@@ -127,9 +129,12 @@ void free_server_device(Server &S) {
   S.slots.clear();
   if (S.main) (void)hipStreamDestroy(S.main);
   if (S.applied) (void)hipEventDestroy(S.applied);
+  if (S.binned) (void)hipEventDestroy(S.binned);
   if (S.h_rec) (void)hipHostFree(S.h_rec);
   S.main = nullptr;
   S.applied = nullptr;
+  S.binned = nullptr;
+  S.bins_out = false;
   S.h_rec = nullptr;
   S.last_scans.clear();
 }
@@ -391,6 +396,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     // finds it cheaper from the scan's sums (ABCORE_OPT_PULL 0), always (2)
     // or never (1)
     const bool pull = g.pull_mode != 1;
+    const bool bin = pull && bin_ready(g);
     PeelArgs ap = a;
     if (pull) {
       // the scan resets the workspace; the pull round queues the frontier if
@@ -400,7 +406,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
                                        front, s.stream));
       a.f0_bits = front;
       SCHK(launch_pull_round_args(g, a, s.bits, s.d_corr, s.d_corr + kCorrMax, c, true,
-                                  s.stream, true));
+                                  s.stream, true, nullptr, false, false, false, bin));
       ap.alive0 = s.bits;
       ap.fix_rows = g.heavy_rows;
       ap.fix_bits = s.bits;
@@ -415,6 +421,13 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     // window's updates wait for them
     SCHK(hipEventRecord(s.scanned, s.stream));
     S.last_scans.push_back(s.scanned);
+    if (bin) {
+      // large rounds binned, one query's at a time: the buffers are shared
+      if (S.bins_out) SCHK(hipStreamWaitEvent(s.stream, S.binned, 0));
+      SCHK(launch_bin_rounds_args(g, a, s.bits, a.f0_bits, kBinRounds, s.stream));
+      SCHK(hipEventRecord(S.binned, s.stream));
+      S.bins_out = true;
+    }
     ap.ans_out = s.h_out;
     ap.ans_x = x;
     ap.ans_y = y;
@@ -549,6 +562,7 @@ abcore_status serve_start(Graph &g, int64_t max_inflight, int32_t slots, int32_t
   S.slots.clear();
   hipError_t e = hipStreamCreateWithFlags(&S.main, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&S.applied, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&S.binned, hipEventDisableTiming);
   if (e == hipSuccess) e = hipHostMalloc(&S.h_rec, sizeof(WindowRecord) * kWindowMax);
   if (e == hipSuccess && g.del_ver == nullptr) {
     e = dev_malloc(&g.del_ver, sizeof(int32_t) * std::max<int64_t>(2 * g.m_csr, 1));

@@ -62,9 +62,9 @@ constexpr int32_t kDegOut = -1;
 // beyond any legitimate wait of a peel).  ABCORE_OPT_SPIN_LIMIT lowers it.
 constexpr uint32_t kAsyncSpinLimit = 1u << 21;
 // Live vertices at or below which the core decomposition leaves the level
-// peel for the h-index fixpoint (measured best at 2^20 on the 2e7-, 5e8- and
-// 1e9-edge power-law graphs: 10, 78 and 131 ms, against 12, 96 and 152 ms
-// at 2^18).
+// peel for the h-index fixpoint (flat within 3% from 2^19 to 2^22 on five
+// power-law and uniform graphs of 2e6 to 2e8 edges; 2^18 took 20% longer at
+// 2e7 to 1e9 edges on earlier kernels).
 constexpr int64_t kKcoreSwitch = 1 << 20;
 // Largest usable threshold: kDegIn must stay above every threshold.
 constexpr int32_t kMaxThreshold = 0x7FFFFFFE;

@@ -540,11 +540,11 @@ hipError_t launch_bin_rounds(Graph &g, int32_t thrU, int32_t thrL, const uint32_
 // launch sequence at a time.
 hipError_t launch_bin_rounds_args(const Graph &g, PeelArgs a, const uint32_t *alive,
                                   const uint32_t *f0bits, int rounds, hipStream_t s);
-// Binned push rounds launched before the asynchronous peel (each a pair of
-// kernels that return at once when the round is too small).
-constexpr int kBinRounds = 3;
 // Whether this handle's computations may run binned rounds.
 bool bin_ready(const Graph &g);
+// Binned push rounds to launch ahead of the asynchronous peel, each a pair of
+// kernels that return at once when the round is too small (0: none can pay).
+int bin_rounds(const Graph &g, int32_t thrU, int32_t thrL, bool nested);
 abcore_status build_bins(Graph &g, hipStream_t s);
 // Queries of graphs that fit one workgroup's LDS (tiny_ready), a launch per
 // kTinyQueries of them.

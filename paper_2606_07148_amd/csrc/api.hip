@@ -427,13 +427,16 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
   rank = rank && fused && g.rcols != nullptr;
   // large frontiers pushed by binned rounds (the scan left its frontier in a
   // bitmap; no bitmap in LDS, which pulls faster than either)
-  const bool bin = pull && fused && queue_f0 && !rank && kind == kGCC && bin_ready(g);
+  const int rounds = pull && fused && queue_f0 && !rank && kind == kGCC
+                         ? bin_rounds(g, thrU, thrL, rest_part)
+                         : 0;
+  const bool bin = rounds > 0;
   if (pull) {
-    CHK(timed(g, ABCORE_KERNEL_PULL, s, bin ? 2 + 2 * kBinRounds : 1, [&] {
+    CHK(timed(g, ABCORE_KERNEL_PULL, s, bin ? 2 + 2 * rounds : 1, [&] {
       hipError_t e = launch_pull_round(g, thrU, thrL, s, fused, queue_f0, rowbits, force,
                                        rest_part, rank, f0bits, bin);
       if (e == hipSuccess && bin)
-        e = launch_bin_rounds(g, thrU, thrL, g.alive_bits, f0bits, kBinRounds, s);
+        e = launch_bin_rounds(g, thrU, thrL, g.alive_bits, f0bits, rounds, s);
       return e;
     }));
     if (!fused)

@@ -2644,6 +2644,26 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
 
 bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3; }
 
+// A pair of launches that find nothing to do takes 10 us, so they are left out
+// where the rows below the thresholds, by the degree distribution of the
+// graph as it was built (updates move it little, and only the speed depends on
+// it), have too few entries: at 26.8 G/s, n / 8 + 2^20 of them take 62, 109
+// and 180 us as atomics at 5, 15 and 30 M vertices, the binned round and two
+// empty ones 57, 80 and 140.  (With the launches always made, queries of 46
+// and 84 us at 5 and 15 M vertices took 61 and 98.)  The frontier of a nested
+// query is not known here; one round was the best of one, two and three there
+// (a batch of 256 at 2e8 edges 85, 90 and 96 ms), three elsewhere (4.5e8 edges
+// (16, 16) 2.54, 1.80 and 1.69 ms).
+int bin_rounds(const Graph &g, int32_t thrU, int32_t thrL, bool nested) {
+  if (!bin_ready(g)) return 0;
+  if (nested) return 1;
+  const std::vector<int64_t> &u = g.rk_ent[0], &l = g.rk_ent[1];
+  if (u.empty() || l.empty()) return 3;
+  const int64_t above = ((size_t)thrU < u.size() ? u[thrU] : 0) +
+                        ((size_t)thrL < l.size() ? l[thrL] : 0);
+  return 2 * g.m_csr - above >= g.n / 8 + (1 << 20) ? 3 : 0;
+}
+
 // Slots per bucket for the workgroups' unused chunks.
 static uint32_t bin_slack(const Graph &g) { return (uint32_t)(g.cu_count + 1) * kBinChunk; }
 

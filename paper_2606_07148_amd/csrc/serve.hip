@@ -396,7 +396,8 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     // finds it cheaper from the scan's sums (ABCORE_OPT_PULL 0), always (2)
     // or never (1)
     const bool pull = g.pull_mode != 1;
-    const bool bin = pull && bin_ready(g);
+    const int rounds = pull ? bin_rounds(g, win[i].thrU, win[i].thrL, false) : 0;
+    const bool bin = rounds > 0;
     PeelArgs ap = a;
     if (pull) {
       // the scan resets the workspace; the pull round queues the frontier if
@@ -424,7 +425,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     if (bin) {
       // large rounds binned, one query's at a time: the buffers are shared
       if (S.bins_out) SCHK(hipStreamWaitEvent(s.stream, S.binned, 0));
-      SCHK(launch_bin_rounds_args(g, a, s.bits, a.f0_bits, kBinRounds, s.stream));
+      SCHK(launch_bin_rounds_args(g, a, s.bits, a.f0_bits, rounds, s.stream));
       SCHK(hipEventRecord(S.binned, s.stream));
       S.bins_out = true;
     }

@@ -2647,9 +2647,10 @@ bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3
 // A pair of launches that find nothing to do takes 10 us, so they are left out
 // where the rows below the thresholds, by the degree distribution of the
 // graph as it was built (updates move it little, and only the speed depends on
-// it), have too few entries: at 26.8 G/s, n / 8 + 2^20 of them take 62, 109
-// and 180 us as atomics at 5, 15 and 30 M vertices, the binned round and two
-// empty ones 57, 80 and 140.  (With the launches always made, queries of 46
+// it), have too few entries: at 26.8 G/s, n / 16 + 2^20 of them take 51, 74
+// and 109 us as atomics at 5, 15 and 30 M vertices, the binned round and two
+// empty ones about 52, 75 and 120; at 70 M vertices a query of 8 M entries
+// takes 0.62 ms binned and 0.96 not.  (With the launches always made, queries of 46
 // and 84 us at 5 and 15 M vertices took 61 and 98.)  The frontier of a nested
 // query is not known here; one round was the best of one, two and three there
 // (a batch of 256 at 2e8 edges 85, 90 and 96 ms), three elsewhere (4.5e8 edges
@@ -2661,7 +2662,7 @@ int bin_rounds(const Graph &g, int32_t thrU, int32_t thrL, bool nested) {
   if (u.empty() || l.empty()) return 3;
   const int64_t above = ((size_t)thrU < u.size() ? u[thrU] : 0) +
                         ((size_t)thrL < l.size() ? l[thrL] : 0);
-  return 2 * g.m_csr - above >= g.n / 8 + (1 << 20) ? 3 : 0;
+  return 2 * g.m_csr - above >= g.n / 16 + (1 << 20) ? 3 : 0;
 }
 
 // Slots per bucket for the workgroups' unused chunks.

@@ -229,7 +229,8 @@ abcore_status abcore_core_numbers(abcore_graph g, int32_t *d_core, int32_t *max_
                                   void *stream);
 
 /* Connected-component labels (GFQ preprocessing, Sec. V): label = smallest
- * unified id in the component.  Maintained under updates by abcore_query.
+ * unified id in the component.  Maintained under updates by abcore_query;
+ * after served deletions the first call that needs them labels anew.
  * d_comp: DEVICE n int32 or NULL (only compute the labels).  Synchronous. */
 abcore_status abcore_components(abcore_graph g, int32_t *d_comp, void *stream);
 

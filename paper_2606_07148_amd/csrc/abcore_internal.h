@@ -294,7 +294,8 @@ struct Graph {
   int32_t *comp = nullptr;  // component labels
   bool comp_valid = false;
   // no served deletion since the labels were computed (serving only merges
-  // labels, so after one a label may cover several components)
+  // labels, so after one a label may cover several components until
+  // compute_components labels anew)
   bool comp_exact = false;
   int32_t *parent = nullptr; // union-find scratch
   Delta delta;

@@ -572,8 +572,10 @@ abcore_status compute_core_numbers(Graph &g, hipStream_t s) { return compute_cor
 
 namespace {
 
+// The labels, exact: served deletions leave a label over every part of a
+// component they split, so the first use after serving labels anew.
 abcore_status compute_components(Graph &g, hipStream_t s) {
-  if (g.comp_valid) return ABCORE_OK;
+  if (g.comp_valid && g.comp_exact) return ABCORE_OK;
   TRY(ensure(&g.comp, g.n));
   TRY(ensure(&g.parent, g.n));
   if (g.n > 0) CHK(launch_cc(g, -1, s));

@@ -419,7 +419,7 @@ abcore_status abcore_serve_stop(abcore_graph g, int64_t *counters);
  *                          identical either way.
  *   ABCORE_OPT_SPIN_LIMIT: failure injection for tests: polls a waiting wave
  *                          of the asynchronous peel makes before it declares
- *                          a hang and aborts (0 = the default, 2^21, i.e.
+ *                          a hang and aborts (0 = the default, 2^23, i.e.
  *                          seconds; small values make peels abort at once).
  *   ABCORE_OPT_SERVE_DEADLINE_US: per-request deadline of the serving
  *                          engine, from admission (set before

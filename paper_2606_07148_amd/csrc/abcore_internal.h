@@ -58,9 +58,12 @@ constexpr int kDefaultClaim = 32;
 constexpr int32_t kDegIn = 0x7FFFFFFF;
 constexpr int32_t kDegOut = -1;
 // Polls of one waiting wave of the asynchronous peel before it declares a
-// hang (each poll takes at least a few microseconds, so this is seconds: far
-// beyond any legitimate wait of a peel).  ABCORE_OPT_SPIN_LIMIT lowers it.
-constexpr uint32_t kAsyncSpinLimit = 1u << 21;
+// hang.  A wave may wait for good reason as long as a single wave walks one
+// chain of dependent removals, 2.5 us each.  A poll takes 0.8 to 1.1 us, so
+// this allows 6.4 s, two and a half million removals in one chain.  (With a
+// back-off of 16 sleeps a poll took 2.3 to 2.7 us and 2^21 of them 5 s; at the
+// present 4 sleeps that many ended after 2 s.)  ABCORE_OPT_SPIN_LIMIT lowers it.
+constexpr uint32_t kAsyncSpinLimit = 1u << 23;
 // Live vertices at or below which the core decomposition leaves the level
 // peel for the h-index fixpoint (flat within 3% from 2^19 to 2^22 on five
 // power-law and uniform graphs of 2e6 to 2e8 edges; 2^18 took 20% longer at

@@ -1117,6 +1117,7 @@ __device__ __forceinline__ bool quiescent(PeelState *st, int32_t start_expect, i
 #define ABC_QMASK 3
 #endif
 // A poll's sleep grows to 4 steps: at 16 the waves saw the end 1 us later.
+// (kAsyncSpinLimit counts polls: it is four times what it was at 16.)
 #ifndef ABC_BACKOFF
 #define ABC_BACKOFF 4
 #endif

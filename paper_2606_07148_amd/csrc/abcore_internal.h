@@ -614,6 +614,7 @@ struct BuildScratch {
   ~BuildScratch();
   hipError_t reserve(int64_t m, int64_t n);
   hipError_t reserve_temp(size_t bytes);
+  void release();
   hipStream_t s;
   uint64_t *k0 = nullptr, *k1 = nullptr;
   int64_t *c = nullptr;       // n + 1

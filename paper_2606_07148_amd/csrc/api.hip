@@ -975,10 +975,12 @@ abcore_status abcore_build_csr(int32_t n_upper, int32_t n_lower, const int32_t *
     g->build_ms[1] = ms_since(t0);
     t0 = now();
     st = build_ranks(*g, scratch_keys, s);
+    // (given back before the working set is allocated: the two never stand
+    // side by side)
+    scratch_keys.release();
     if (st == ABCORE_OK && hipStreamSynchronize(s) != hipSuccess) st = ABCORE_EDEVICE;
     if (st != ABCORE_OK) break;
     g->build_ms[2] = ms_since(t0);
-    if ((st = build_bins(*g, s)) != ABCORE_OK) break;
     g->qcap = queue_capacity(g->n, g->npieces);
     if ((st = ensure(&g->deg, g->n)) != ABCORE_OK) break;
     if ((st = ensure(&g->queue, (int64_t)kSub * g->qcap)) != ABCORE_OK) break;
@@ -1033,6 +1035,8 @@ abcore_status abcore_build_csr(int32_t n_upper, int32_t n_lower, const int32_t *
       st = ABCORE_EDEVICE;
       break;
     }
+    // (optional memory, after what the handle cannot do without)
+    if ((st = build_bins(*g, s)) != ABCORE_OK) break;
   } while (0);
   if (st != ABCORE_OK) {
     free_graph(g);

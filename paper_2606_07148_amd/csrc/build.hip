@@ -247,9 +247,13 @@ int bits_for(uint64_t maxkey) {
 
 }  // namespace
 
-BuildScratch::~BuildScratch() {
+BuildScratch::~BuildScratch() { release(); }
+
+void BuildScratch::release() {
   if (temp) (void)dev_free_async(temp, s);
   if (block) (void)dev_free_async(block, s);
+  temp = block = nullptr;
+  temp_bytes = 0;
 }
 
 hipError_t BuildScratch::reserve(int64_t m, int64_t n) {

@@ -2726,7 +2726,8 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
   if (prepare_bin_kernels((int)count, shift) != hipSuccess ||
       dev_malloc(&g.bin_tail, sizeof(uint32_t) * count) != hipSuccess ||
       dev_malloc(&g.bin_msg, sizeof(uint16_t) * slots) != hipSuccess ||
-      hipMemsetAsync(g.bin_tail, 0, sizeof(uint32_t) * count, s) != hipSuccess) {
+      hipMemsetAsync(g.bin_tail, 0, sizeof(uint32_t) * count, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess) {
     (void)hipGetLastError();
     if (g.bin_tail) (void)dev_free(g.bin_tail);
     if (g.bin_msg) (void)dev_free(g.bin_msg);

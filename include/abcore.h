@@ -126,7 +126,11 @@ abcore_status abcore_device_memory(int64_t *current, int64_t *peak, int32_t rese
  * ABCORE_ENOMEM and changes nothing (a build creates no handle; a computation
  * leaves the handle as it was), except abcore_serve_start, which admits with
  * fewer device working sets when at least one fits (see there).  Lowering
- * the budget frees nothing.  Errors: EINVAL (negative). */
+ * the budget frees nothing.  Optional memory does not stand in the way: what
+ * binned rounds take on large graphs (abcore_report's queue_bytes) is given
+ * back, by every handle, before an allocation fails, with or without a
+ * budget; those handles then push their large rounds as smaller graphs do.
+ * Errors: EINVAL (negative). */
 abcore_status abcore_set_memory_budget(int64_t bytes);
 
 /* Releases every resource of the handle.  NULL is accepted. */

@@ -266,11 +266,14 @@ struct Graph {
   // Binned push rounds (bin_kernel): ids in buckets of 2^bin_shift, each with
   // message slots for its vertices' entries (each is sent along at most once
   // in a computation) and some slack, the slots in use in bin_tail (zero
-  // between rounds).  Null on small graphs.
+  // between rounds).  Null on small graphs, and once they were given back
+  // (BinHold): they are optional, and another allocation may need the room.
   uint16_t *bin_msg = nullptr;   // 2*m_csr and the slack
   uint32_t *bin_tail = nullptr;  // bin_count
   int bin_shift = 0, bin_count = 0;
   int64_t bin_bytes = 0;
+  int bin_users = 0;      // BinHolds alive
+  bool bins_off = false;  // abcore_compute_static: no binned rounds
   // Second workspace state and partial sums: queries in rank order alternate
   // between the two, each leaving the other one zeroed and the queue empty
   // (rs_ready).  Any other launch through make_args clears rs_ready.
@@ -458,7 +461,15 @@ PeelArgs make_args(Graph &g, int32_t thrU, int32_t thrL);
 // from hipMalloc; temporaries of one call (sort keys, scan storage, the
 // deep core's rows) are stream-ordered on the caller's stream
 // (hipMallocAsync / hipFreeAsync), so freeing them waits for nothing.
+// An allocation that fails is tried again after the message slots that no
+// BinHold keeps were given back, of every handle; optional memory (slots
+// themselves) comes from dev_malloc_spare, which takes no one's.
 hipError_t dev_malloc_bytes(void **p, size_t bytes);
+hipError_t dev_malloc_spare_bytes(void **p, size_t bytes);
+template <class T>
+hipError_t dev_malloc_spare(T **p, size_t bytes) {
+  return dev_malloc_spare_bytes(reinterpret_cast<void **>(p), bytes);
+}
 template <class T>
 hipError_t dev_malloc(T **p, size_t bytes) {
   return dev_malloc_bytes(reinterpret_cast<void **>(p), bytes);
@@ -470,6 +481,18 @@ hipError_t dev_malloc_async(T **p, size_t bytes, hipStream_t s) {
   return dev_malloc_async_bytes(reinterpret_cast<void **>(p), bytes, s);
 }
 hipError_t dev_free_async(void *p, hipStream_t s);
+
+// Keeps a handle's message slots (Graph::bin_msg) from being given back while
+// it is decided whether launches use them and these are enqueued.  Launches
+// enqueued before need no hold: freeing waits for the device.
+struct BinHold {
+  explicit BinHold(Graph &g);
+  ~BinHold();
+  BinHold(const BinHold &) = delete;
+  Graph &g;
+};
+void offer_bins(Graph &g);     // from here on the slots may be given back
+void withdraw_bins(Graph &g);  // the handle's destruction frees them itself
 
 // Launchers (defined in the .hip files).
 // keep_abort: leave the abort flag as it is (several computations in one

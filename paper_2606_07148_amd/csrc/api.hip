@@ -26,7 +26,7 @@ static int64_t g_mem_budget = 0;  // abcore_set_memory_budget (0: none)
 // Every device allocation of the library.  Under a budget the bytes are
 // reserved before hipMalloc, so that concurrent callers cannot overrun it;
 // a request beyond it fails as out of memory.
-hipError_t dev_malloc_bytes(void **p, size_t bytes) {
+hipError_t dev_malloc_spare_bytes(void **p, size_t bytes) {
   {
     std::lock_guard<std::mutex> lock(g_mem_mu);
     if (g_mem_budget > 0 && g_mem_current + (int64_t)bytes > g_mem_budget) {
@@ -46,7 +46,7 @@ hipError_t dev_malloc_bytes(void **p, size_t bytes) {
   return e;
 }
 
-hipError_t dev_malloc_async_bytes(void **p, size_t bytes, hipStream_t s) {
+static hipError_t malloc_async_once(void **p, size_t bytes, hipStream_t s) {
   {
     std::lock_guard<std::mutex> lock(g_mem_mu);
     if (g_mem_budget > 0 && g_mem_current + (int64_t)bytes > g_mem_budget) {
@@ -86,6 +86,65 @@ hipError_t dev_free_async(void *p, hipStream_t s) {
   if (p == nullptr) return hipSuccess;
   forget(p);
   return hipFreeAsync(p, s);
+}
+
+// Handles that hold message slots.  The slots only make large rounds faster,
+// so no allocation fails for want of what they take.
+static std::mutex g_bins_mu;
+static std::vector<Graph *> g_bins;
+
+void offer_bins(Graph &g) {
+  std::lock_guard<std::mutex> lock(g_bins_mu);
+  g_bins.push_back(&g);
+}
+
+void withdraw_bins(Graph &g) {
+  if (g.bin_count == 0) return;
+  std::lock_guard<std::mutex> lock(g_bins_mu);
+  g_bins.erase(std::remove(g_bins.begin(), g_bins.end(), &g), g_bins.end());
+}
+
+BinHold::BinHold(Graph &graph) : g(graph) {
+  if (g.bin_count == 0) return;
+  std::lock_guard<std::mutex> lock(g_bins_mu);
+  ++g.bin_users;
+}
+
+BinHold::~BinHold() {
+  if (g.bin_count == 0) return;
+  std::lock_guard<std::mutex> lock(g_bins_mu);
+  --g.bin_users;
+}
+
+// Frees the slots that no one holds (which waits for the device); true if
+// there were any.
+static bool release_bins() {
+  std::lock_guard<std::mutex> lock(g_bins_mu);
+  auto idle = [](Graph *g) { return g->bin_users == 0; };
+  const auto from = std::stable_partition(g_bins.begin(), g_bins.end(),
+                                          [&](Graph *g) { return !idle(g); });
+  if (from == g_bins.end()) return false;
+  for (auto it = from; it != g_bins.end(); ++it) {
+    Graph &g = **it;
+    (void)dev_free(g.bin_msg);
+    (void)dev_free(g.bin_tail);
+    g.bin_msg = nullptr;
+    g.bin_tail = nullptr;
+    g.bin_bytes = 0;
+  }
+  g_bins.erase(from, g_bins.end());
+  (void)hipGetLastError();  // the failed allocation's
+  return true;
+}
+
+hipError_t dev_malloc_bytes(void **p, size_t bytes) {
+  const hipError_t e = dev_malloc_spare_bytes(p, bytes);
+  return e == hipErrorOutOfMemory && release_bins() ? dev_malloc_spare_bytes(p, bytes) : e;
+}
+
+hipError_t dev_malloc_async_bytes(void **p, size_t bytes, hipStream_t s) {
+  const hipError_t e = malloc_async_once(p, bytes, s);
+  return e == hipErrorOutOfMemory && release_bins() ? malloc_async_once(p, bytes, s) : e;
 }
 
 // ----------------------------------------------------------- tuning cache --
@@ -239,6 +298,7 @@ void free_graph(Graph *g) {
   if (!g) return;
   (void)hipSetDevice(g->device);
   destroy_server(*g);
+  withdraw_bins(*g);
   if (g->del_ver) (void)dev_free(g->del_ver);
   if (g->pair_del_ver) (void)dev_free(g->pair_del_ver);
   for (auto &ev : g->events)
@@ -427,6 +487,7 @@ abcore_status pull_peel_pack(Graph &g, PeelKind kind, int32_t thrU, int32_t thrL
   rank = rank && fused && g.rcols != nullptr;
   // large frontiers pushed by binned rounds (the scan left its frontier in a
   // bitmap; no bitmap in LDS, which pulls faster than either)
+  BinHold hold(g);
   const int rounds = pull && fused && queue_f0 && !rank && kind == kGCC
                          ? bin_rounds(g, thrU, thrL, rest_part)
                          : 0;
@@ -503,7 +564,10 @@ abcore_status compute_core(Graph &g, hipStream_t s) {
     bool top_tried = false;
     int64_t live = g.n;
     for (; done < max_levels; done += batch) {
-      CHK(launch_kcore_levels(g, batch, bin_ready(g) && live * kBinLive >= g.n, s));
+      {
+        BinHold hold(g);
+        CHK(launch_kcore_levels(g, batch, bin_ready(g) && live * kBinLive >= g.n, s));
+      }
       TRY(read_state(g, s));
       if (g.h_state->done) break;
       // the deep levels by the h-index fixpoint once the live part (the
@@ -1067,7 +1131,10 @@ abcore_status abcore_graph_report(abcore_graph h, abcore_report *out) {
                          : 4 * n + 4 * n + 8 * (n + 1) + 4 * 2 * g->m_csr +
                                (g->rp_row != nullptr ? (4 + 8) * np + 4 * n : 0) +
                                (g->rdeg != nullptr ? 4 * ((int64_t)g->rdeg_mask + 1) : 0);
-  out->queue_bytes = 4 * (int64_t)kSub * g->qcap + g->bin_bytes;
+  {
+    BinHold hold(*g);
+    out->queue_bytes = 4 * (int64_t)kSub * g->qcap + g->bin_bytes;
+  }
   for (int i = 0; i < 4; ++i) out->core_top[i] = g->kcore_top_used ? g->top_stats[i] : 0;
   out->core_levels_ms = g->kcore_top_used ? g->top_ms[0] : 0.0;
   out->core_top_ms = g->kcore_top_used ? g->top_ms[1] : 0.0;
@@ -1470,9 +1537,8 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
     int64_t *part;
     int peel_mode;
     bool timing;
-    uint16_t *bin_msg;
     ~Swap() {
-      g.bin_msg = bin_msg;
+      g.bins_off = false;
       g.deg = deg;
       g.queue = queue;
       g.alive_bits = bits;
@@ -1481,8 +1547,7 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
       g.peel_mode = peel_mode;
       g.timing = timing;
     }
-  } restore{*g,      g->deg,       g->queue,  g->alive_bits, g->state,
-            g->part, g->peel_mode, g->timing, g->bin_msg};
+  } restore{*g, g->deg, g->queue, g->alive_bits, g->state, g->part, g->peel_mode, g->timing};
   g->queue = reinterpret_cast<int32_t *>(base + L.queue);
   g->deg = reinterpret_cast<int32_t *>(base + L.deg);
   g->alive_bits = reinterpret_cast<uint32_t *>(base + L.bits);
@@ -1490,7 +1555,7 @@ abcore_status abcore_compute_static(abcore_graph h, uint32_t alpha, uint32_t bet
   g->part = reinterpret_cast<int64_t *>(base + L.part);
   g->peel_mode = 3;     // the asynchronous worklist (no host reads)
   g->timing = false;    // event pairs would be created on demand
-  g->bin_msg = nullptr;  // the handle's, not in the scratch: no binned rounds
+  g->bins_off = true;   // their slots are the handle's, not in the scratch
   const int64_t nqueue = (int64_t)kSub * g->qcap;
   const int64_t nzero = (int64_t)((L.total - L.bits) / sizeof(uint32_t));
   static_fill_kernel<<<std::min(g->cu_count * 8, kMaxBlocks), 256, 0, s>>>(
@@ -1604,6 +1669,9 @@ abcore_status abcore_compute_batch(abcore_graph h, const uint32_t *h_alpha,
     CHK(hipStreamSynchronize(s));
     return ABCORE_OK;
   }
+  // (a captured graph names the message slots: they stay until it is launched,
+  // and one captured with them is not replayed once they were given back)
+  BinHold hold(*g);
   std::vector<int32_t> key;
   key.reserve(2 * (size_t)q + 8);
   key.insert(key.end(), tu.begin(), tu.end());
@@ -1614,6 +1682,7 @@ abcore_status abcore_compute_batch(abcore_graph h, const uint32_t *h_alpha,
   key.push_back(g->claim);
   key.push_back(g->rank_order ? 1 : 0);
   key.push_back(g->delta.count > 0 ? 1 : 0);
+  key.push_back(bin_ready(*g) ? 1 : 0);
   BatchCache &c = g->batch;
   if (!(c.exec && c.bits == d_bitmasks && c.version == g->version && c.key == key)) {
     drop_batch_cache(*g);

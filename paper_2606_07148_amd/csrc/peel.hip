@@ -2643,7 +2643,10 @@ __global__ __launch_bounds__(kBinBlock) void apply_kernel(PeelArgs a,
   }
 }
 
-bool bin_ready(const Graph &g) { return g.bin_msg != nullptr && g.peel_mode == 3; }
+// (under a BinHold: the slots may be given back at any other time)
+bool bin_ready(const Graph &g) {
+  return g.bin_msg != nullptr && !g.bins_off && g.peel_mode == 3;
+}
 
 // A pair of launches that find nothing to do takes 10 us, so they are left out
 // where the rows below the thresholds, by the degree distribution of the
@@ -2724,8 +2727,8 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
       bin_lds((int)count) + 1024 > g.lds_per_block)
     return ABCORE_OK;
   if (prepare_bin_kernels((int)count, shift) != hipSuccess ||
-      dev_malloc(&g.bin_tail, sizeof(uint32_t) * count) != hipSuccess ||
-      dev_malloc(&g.bin_msg, sizeof(uint16_t) * slots) != hipSuccess ||
+      dev_malloc_spare(&g.bin_tail, sizeof(uint32_t) * count) != hipSuccess ||
+      dev_malloc_spare(&g.bin_msg, sizeof(uint16_t) * slots) != hipSuccess ||
       hipMemsetAsync(g.bin_tail, 0, sizeof(uint32_t) * count, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess) {
     (void)hipGetLastError();
@@ -2738,6 +2741,7 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
   g.bin_shift = shift;
   g.bin_count = (int)count;
   g.bin_bytes = (int64_t)(sizeof(uint16_t) * slots + sizeof(uint32_t) * count);
+  offer_bins(g);
   return ABCORE_OK;
 }
 

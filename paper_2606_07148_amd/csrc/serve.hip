@@ -396,6 +396,7 @@ bool run_window(Graph &g, Server &S, const std::vector<Request> &win) {
     // finds it cheaper from the scan's sums (ABCORE_OPT_PULL 0), always (2)
     // or never (1)
     const bool pull = g.pull_mode != 1;
+    BinHold hold(g);
     const int rounds = pull ? bin_rounds(g, win[i].thrU, win[i].thrL, false) : 0;
     const bool bin = rounds > 0;
     PeelArgs ap = a;

@@ -1,9 +1,15 @@
-"""Device memory of builds: the temporaries are gone before the working set is
-allocated."""
+"""Device memory of builds and of the optional message slots of binned rounds
+(graphs of at least 2^22 vertices): a build's temporaries are gone before its
+working set is allocated, and the slots are given back, by any handle, when
+another allocation would not fit; results stay the oracle's."""
+import threading
+
+import numpy as np
 import pytest
 
 import bigraph_gen
-from tests.gpu_util import ensure_built, say, to_dev
+import oracle
+from tests.gpu_util import bits_np, ensure_built, say, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -21,6 +27,30 @@ def _setup():
     pkg = p
     yield
     p.abcore_set_memory_budget(0)
+
+
+@pytest.fixture(scope="module")
+def graph():
+    nU, nL = 2_500_001, 1_800_003
+    eu, ev = bigraph_gen.uniform(nU, nL, 12_000_000, 21)
+    return nU, nL, eu, ev, oracle.Graph(nU, nL, eu, ev)
+
+
+def _held():
+    return pkg.abcore_device_memory()[0]
+
+
+def _slots(g):
+    """Bytes of the sub-queues and the message slots: less once the slots are
+    given back."""
+    return pkg.abcore_graph_report(g)["queue_bytes"]
+
+
+def _check(g, ref, queries):
+    for a, b in queries:
+        want = oracle.pack(oracle.compute(ref, a, b))
+        got = bits_np(pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC))[: len(want)]
+        assert np.array_equal(got, want), (a, b)
 
 
 @pytest.mark.parametrize("nU,nL,m", [(3_000, 2_000, 12_000), (6_000_000, 6_000_000, 1_000_000)])
@@ -45,3 +75,105 @@ def test_build_peak(nU, nL, m):
         pkg.abcore_build_csr(nU, nL, deu, dev).destroy()
     finally:
         pkg.abcore_set_memory_budget(0)
+
+
+def test_slots_given_back_for_the_core_numbers(graph):
+    nU, nL, eu, ev, ref = graph
+    n = nU + nL
+    g = pkg.abcore_build_csr(nU, nL, to_dev(eu), to_dev(ev))
+    pkg.abcore_set_option(g, pkg.ABCORE_OPT_RANK_ORDER, 2)
+    alphas, betas = [3, 5, 5, 7], [2, 4, 7, 9]
+    want = oracle.batch(ref, alphas, betas)
+
+    def batch():
+        got = bits_np(pkg.abcore_compute_batch(g, alphas, betas))
+        assert np.array_equal(got[:, : want.shape[1]], want)
+
+    batch()
+    batch()  # replays the captured launches, binned rounds among them
+    with_slots = _slots(g)
+    # the arrays of a decomposition on levels alone: core numbers, two lists
+    # and the removed bitmap; half of the slots' bytes too little
+    arrays = 3 * 4 * n + 4 * ((n + 31) // 32) + 4096
+    pkg.abcore_set_option(g, pkg.ABCORE_OPT_KCORE_SWITCH, 1)
+    pkg.abcore_set_memory_budget(_held() + arrays - 2 * ref.m)
+    try:
+        say("core numbers where only the slots' bytes make room")
+        core, mx = pkg.abcore_core_numbers(g)
+        cores = oracle.core_numbers(ref)
+        assert np.array_equal(core.cpu().numpy(), cores) and mx == int(cores.max())
+        assert _slots(g) < with_slots - 2 * ref.m
+        for _ in range(3):
+            batch()
+            _check(g, ref, [(5, 7)])
+    finally:
+        pkg.abcore_set_memory_budget(0)
+        g.destroy()
+
+
+def test_slots_given_back_to_another_handle(graph):
+    nU, nL, eu, ev, ref = graph
+    small = bigraph_gen.uniform(300_000, 200_000, 1_000_000, 6)
+    sref = oracle.Graph(300_000, 200_000, *small)
+    sdev = [to_dev(a) for a in small]
+    h = pkg.abcore_build_csr(300_000, 200_000, *sdev)
+    h.destroy()
+    base, _ = pkg.abcore_device_memory(reset_peak=True)
+    h = pkg.abcore_build_csr(300_000, 200_000, *sdev)
+    need = pkg.abcore_device_memory()[1] - base
+    h.destroy()
+    g = pkg.abcore_build_csr(nU, nL, to_dev(eu), to_dev(ev))
+    pkg.abcore_set_option(g, pkg.ABCORE_OPT_RANK_ORDER, 2)
+    _check(g, ref, [(5, 7)])
+    with_slots = _slots(g)
+    assert 2 * 2 * ref.m > need // 2
+    pkg.abcore_set_memory_budget(_held() + need // 2)
+    try:
+        say("a build that only the other handle's slots make room for")
+        h = pkg.abcore_build_csr(300_000, 200_000, *sdev)
+        assert _slots(g) < with_slots
+        _check(h, sref, [(3, 4)])
+        _check(g, ref, [(5, 7), (9, 2)])
+        h.destroy()
+    finally:
+        pkg.abcore_set_memory_budget(0)
+        g.destroy()
+
+
+def test_slots_given_back_while_queries_run(graph):
+    """One thread queries its handle while another builds under a budget that
+    takes the first one's slots."""
+    nU, nL, eu, ev, ref = graph
+    import torch
+    small = [to_dev(a) for a in bigraph_gen.uniform(300_000, 200_000, 1_000_000, 6)]
+    want = oracle.pack(oracle.compute(ref, 5, 7))
+    for _ in range(2):
+        g = pkg.abcore_build_csr(nU, nL, to_dev(eu), to_dev(ev))
+        pkg.abcore_set_option(g, pkg.ABCORE_OPT_RANK_ORDER, 2)
+        wrong, failed = [], []
+
+        def query():
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                out = torch.zeros((nU + nL + 31) // 32, dtype=torch.int32, device="cuda")
+                for i in range(40):
+                    pkg.abcore_compute(g, 5, 7, pkg.ABCORE_GCC, out=out)
+                    if not np.array_equal(bits_np(out)[: len(want)], want):
+                        wrong.append(i)
+
+        t = threading.Thread(target=query)
+        pkg.abcore_set_memory_budget(_held() + 2 * MB)
+        t.start()
+        try:
+            for _ in range(4):
+                try:
+                    pkg.abcore_build_csr(300_000, 200_000, *small).destroy()
+                except pkg.AbcoreError as e:
+                    failed.append(e.name)  # the slots were in use just then
+            t.join()
+        finally:
+            pkg.abcore_set_memory_budget(0)
+        say("queries wrong:", wrong, "builds without memory:", failed)
+        assert not wrong
+        assert all(f == "ENOMEM" for f in failed)
+        g.destroy()

@@ -2373,12 +2373,13 @@ __global__ __launch_bounds__(kBinBlock) void bin_kernel(PeelArgs a, uint16_t *__
     if (x >= 0) {
       if (KIND == kKCore && a.kdead != nullptr)
         atomicOr(&a.kdead[x >> 5], 1u << (x & 31));  // removed from here on
-      // after a pull round a split row may be queued a second time (see
-      // peel_batch): the first consumer marks its degree
-      if (d > kPiece && a.fix_bits != nullptr &&
-          atomicExch(&a.deg[x], kClaimedDeg) <= kClaimedDeg / 2)
-        d = 0;
-      if (a.ins_head != nullptr) {
+      // a split row's first consumer marks its degree, and a second copy of it
+      // in the queue walks nothing, as in peel_batch (there is none today: ahead
+      // of these rounds queue_split_kernel queues each split row at most once)
+      const bool mine = d <= kPiece || a.fix_bits == nullptr ||
+                        atomicExch(&a.deg[x], kClaimedDeg) > kClaimedDeg / 2;
+      if (!mine) d = 0;
+      if (mine && a.ins_head != nullptr) {
         // inserted edges: few, decremented directly
         for (int e = a.ins_head[x], next; e >= 0; e = next) {
           int32_t w;

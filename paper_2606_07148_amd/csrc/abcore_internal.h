@@ -357,14 +357,18 @@ struct WindowRecord {
   int32_t pad[3];
 };
 
-// Peel flavours.
 // Where a scoped query's answer goes (PeelArgs::ans_out): pinned words, and
 // the two endpoints.
+constexpr int kAnsAborted = 3;  // the word of ans_out that says so
+static_assert(offsetof(PeelState, abort_flag) ==
+                  offsetof(PeelState, aux0) + kAnsAborted * sizeof(int32_t),
+              "the answer's words are the state's");
 struct Answer {
   int32_t *out = nullptr;
   int32_t x = -1, y = -1;
 };
 
+// Peel flavours.
 enum PeelKind : int { kGCC = 0, kGCCPlus = 1, kKCore = 2 };
 
 // Parameters of a peel, passed by value to kernels.
@@ -440,6 +444,7 @@ struct PeelArgs {
   // Scoped queries (nullable): the membership of ans_x (bit 0) and ans_y (bit
   // 1) after termination, and in ans_out[3] whether the peel aborted, written
   // to host-visible (pinned) words; nothing else has to be read back.
+  // (abcore_query hands it the words from aux0 of the pinned state on)
   int32_t *ans_out;
   int32_t ans_x, ans_y;
   // Sub-queue every append tries first (-1: the producer's own; a fixed one

@@ -1334,7 +1334,7 @@ __global__ __launch_bounds__(kPeelBlock) void peel_async_kernel(PeelArgs a) {
     const int32_t in = (ld_agent(&a.deg[a.ans_x]) >= (a.ans_x < a.nU ? a.thrU : a.thrL) ? 1 : 0) |
                        (ld_agent(&a.deg[a.ans_y]) >= (a.ans_y < a.nU ? a.thrU : a.thrL) ? 2 : 0);
     __hip_atomic_store(&a.ans_out[0], in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    __hip_atomic_store(&a.ans_out[3], aborted ? 1 : 0, __ATOMIC_RELAXED,
+    __hip_atomic_store(&a.ans_out[kAnsAborted], aborted ? 1 : 0, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
   }
   if (a.rs_next_st != nullptr && aborted) {

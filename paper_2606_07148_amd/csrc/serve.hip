@@ -184,7 +184,7 @@ bool reap(Server &S, bool wait) {
     if (e != hipSuccess) {
       r.status = ABCORE_EDEVICE;
       if (S.fail.empty()) S.fail = std::string("served query failed: ") + hipGetErrorString(e);
-    } else if (s.h_out[3] != 0) {
+    } else if (s.h_out[kAnsAborted] != 0) {
       r.status = ABCORE_EDEVICE;
       if (S.fail.empty()) S.fail = "a served peel exceeded its spin limit";
     } else {

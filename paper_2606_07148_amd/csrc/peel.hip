@@ -2673,18 +2673,21 @@ int bin_rounds(const Graph &g, int32_t thrU, int32_t thrL, bool nested) {
 // Slots per bucket for the workgroups' unused chunks.
 static uint32_t bin_slack(const Graph &g) { return (uint32_t)(g.cu_count + 1) * kBinChunk; }
 
-static hipError_t prepare_bin_kernels(int nbuckets, int shift) {
+// The kernels' largest dynamic LDS: the device's, never one handle's (the
+// attribute is the process's, and other handles use other bucket sizes).
+static hipError_t prepare_bin_kernels(const Graph &g) {
   hipError_t e = hipSuccess;
   for (const void *f : {reinterpret_cast<const void *>(&bin_kernel<kGCC, false>),
                         reinterpret_cast<const void *>(&bin_kernel<kGCC, true>),
                         reinterpret_cast<const void *>(&bin_kernel<kKCore, false>)})
     if (e == hipSuccess)
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)bin_lds(nbuckets));
+                              (int)g.lds_per_block - 1024);
   for (const void *f : {reinterpret_cast<const void *>(&apply_kernel<kGCC>),
                         reinterpret_cast<const void *>(&apply_kernel<kKCore>)})
     if (e == hipSuccess)
-      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 4 << shift);
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              4 << kBinMaxShift);
   return e;
 }
 
@@ -2727,7 +2730,7 @@ abcore_status build_bins(Graph &g, hipStream_t s) {
   if (count > kBinMaxBuckets || slots > (int64_t)UINT32_MAX ||
       bin_lds((int)count) + 1024 > g.lds_per_block)
     return ABCORE_OK;
-  if (prepare_bin_kernels((int)count, shift) != hipSuccess ||
+  if (prepare_bin_kernels(g) != hipSuccess ||
       dev_malloc_spare(&g.bin_tail, sizeof(uint32_t) * count) != hipSuccess ||
       dev_malloc_spare(&g.bin_msg, sizeof(uint16_t) * slots) != hipSuccess ||
       hipMemsetAsync(g.bin_tail, 0, sizeof(uint32_t) * count, s) != hipSuccess ||

@@ -102,3 +102,39 @@ def test_inserted_edges_at_split_rows():
             pkg.abcore_set_option(g, pkg.ABCORE_OPT_PULL, pull)
             assert _query(g, ref, a, b)[0] == 2 + 2 * ROUNDS
     g.destroy()
+
+
+def test_handles_of_different_bucket_sizes():
+    """A handle with large buckets stays usable while others with smaller ones
+    come and go (the kernels' LDS limits are the device's, not a handle's);
+    compared with the same queries pushed by atomics."""
+    import torch
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+
+    def build(nU, nL, m):
+        eu = torch.randint(0, nU, (m,), dtype=torch.int32, device="cuda", generator=gen)
+        ev = torch.randint(0, nL, (m,), dtype=torch.int32, device="cuda", generator=gen)
+        g = pkg.abcore_build_csr(nU, nL, eu, ev)
+        pkg.abcore_set_option(g, pkg.ABCORE_OPT_RANK_ORDER, 2)
+        pkg.abcore_set_option(g, pkg.ABCORE_OPT_TIMING, 1)
+        return g
+
+    def same(g, a, b):
+        pkg.abcore_set_option(g, pkg.ABCORE_OPT_PULL, 1)
+        want = bits_np(pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC)).copy()
+        pkg.abcore_set_option(g, pkg.ABCORE_OPT_PULL, 0)
+        pkg.abcore_kernel_timing(g, 1)
+        assert np.array_equal(bits_np(pkg.abcore_compute(g, a, b, pkg.ABCORE_GCC)), want)
+        assert pkg.abcore_kernel_timing(g, 1)[1] == 2 + 2 * ROUNDS
+
+    large = build(10_000_000, 7_000_000, 40_000_000)  # 32,768 vertices to a bucket
+    say("buckets: large alone")
+    same(large, 4, 5)
+    small = build(2_400_000, 1_900_000, 12_000_000)   # 8,192
+    say("buckets: both")
+    same(small, 4, 6)
+    same(large, 4, 5)
+    small.destroy()
+    same(large, 4, 5)
+    large.destroy()

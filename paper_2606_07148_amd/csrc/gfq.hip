@@ -210,6 +210,23 @@ __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
     if (key[i] >= 0) atomicMin(&parent[key[i]], low[i]);
 }
 
+// Every lower vertex unites with the first kSampleLinks entries of its row
+// (sparse_merges, below).
+template <class Scope>
+__global__ void uf_sample_link_kernel(const int64_t *__restrict__ off,
+                                      const int32_t *__restrict__ cols, Scope scope,
+                                      int32_t *parent, int64_t nU, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t x = nU + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
+    if (!scope.in(x)) continue;
+    const int64_t s = off[x], e = min(off[x + 1], s + kSampleLinks);
+    for (int64_t j = s; j < e; ++j) {
+      const int32_t w = cols[j];
+      if (scope.near(w)) uf_union(parent, (int32_t)x, w);
+    }
+  }
+}
+
 // The most frequent root among kRootSamples evenly spaced vertices into
 // *big (-1 when none of them is in scope): one workgroup, every thread
 // counting its own sample among all of them in LDS, so that the choice
@@ -837,9 +854,11 @@ int small_grid(const Graph &g, int64_t items) {
 // The forest of connected parts of a scope in g.parent: vertices of one part
 // have one root, the smallest id in it.  Stream-ordered; the root of the
 // largest tree sits in the partial-sum buffer (reset before every
-// computation).
+// computation).  merges (sparse graphs): that many launches of the merging
+// phase, the trees compressed after each, then unions of the lower vertices'
+// first entries; 0: as the merging phase describes.
 template <class Scope>
-static void launch_parts(Graph &g, Scope scope, hipStream_t s) {
+static void launch_parts(Graph &g, Scope scope, int merges, hipStream_t s) {
   const int32_t *head = g.delta.count > 0 ? g.delta.head : nullptr;
   int32_t *d_big = reinterpret_cast<int32_t *>(g.part);
   uf_hook_lower_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.off, g.cols, scope, g.parent, g.nU,
@@ -850,20 +869,43 @@ static void launch_parts(Graph &g, Scope scope, hipStream_t s) {
     return (int)std::max<int64_t>(
         1, std::min<int64_t>((items + kMergeBlock - 1) / kMergeBlock, g.cu_count));
   };
-  uf_merge_kernel<false><<<merge_grid(g.nU), kMergeBlock, 0, s>>>(g.off, g.cols, scope, g.parent,
-                                                                  g.nU);
-  uf_merge_kernel<true><<<merge_grid(g.nU / kMergeEvery + 1), kMergeBlock, 0, s>>>(
-      g.off, g.cols, scope, g.parent, g.nU);
+  for (int i = 0; i < std::max(merges, 1); ++i) {
+    uf_merge_kernel<false><<<merge_grid(g.nU), kMergeBlock, 0, s>>>(g.off, g.cols, scope,
+                                                                    g.parent, g.nU);
+    if (merges > 0) uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, scope, g.n);
+  }
+  if (merges > 0)
+    uf_sample_link_kernel<<<small_grid(g, g.nL), 256, 0, s>>>(g.off, g.cols, scope, g.parent,
+                                                              g.nU, g.n);
+  else
+    uf_merge_kernel<true><<<merge_grid(g.nU / kMergeEvery + 1), kMergeBlock, 0, s>>>(
+        g.off, g.cols, scope, g.parent, g.nU);
   uf_compress_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, scope, g.n);
   uf_big_root_kernel<<<1, kRootSamples, 0, s>>>(g.parent, scope, g.n, d_big);
   uf_rest_link_kernel<<<wide_grid(g), kBlock, 0, s>>>(g.off, g.cols, scope, g.parent, head,
                                                       g.delta.next, g.delta.other, g.n, d_big);
 }
 
+// Launches of the merging phase where few edges and no hubs leave the hooks
+// many small trees: their joining in the completion took longer than uniting
+// the first entries of every row had, 1 to 3 ms by the graph's seed.  Medians
+// over uniform graphs, united / hooked as on skewed graphs / merged so: 100,000
+// vertices with 95,000 edges 0.37 / 0.81 / 0.17 ms, 2 M with 2.1 M 3.5 / 2.8 /
+// 0.69, 5.5 M with 6.3 M 1.0 / 3.5 / 1.0; a random tree of 2 M 3.5 / 5.1 / 3.5, a
+// path of 200,000 0.38 / 0.49 / 0.44.  With fewer than half an edge a vertex (0.57
+// / 0.51 / 0.84 at 5.5 M and 0.4), more than 7/4 (1.2 / 0.42 / 0.44 at 2 M and
+// 2), long rows (1.6 / 0.32 / 0.27 at 1.5 M and 0.8) or more vertices (2.1 / 1.9
+// / 2.7 at 18 M and 1.1) the general merging is the faster, or the same.
+static int sparse_merges(const Graph &g) {
+  const int64_t n = g.n, m = g.m_csr;
+  if (g.nheavy > 0 || n > (8 << 20) || 2 * m <= n || 4 * m > 7 * n) return 0;
+  return 4 * m <= 3 * n ? 6 : 3;
+}
+
 // Component labels for the whole graph (label < 0) or re-labelling of the
 // vertices currently labelled `label` (deletion may split that component).
 hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
-  launch_parts(g, LabelScope{g.comp, label}, s);
+  launch_parts(g, LabelScope{g.comp, label}, sparse_merges(g), s);
   uf_label_kernel<<<small_grid(g, g.n), 256, 0, s>>>(g.parent, g.comp, label, g.n);
   return hipGetLastError();
 }
@@ -873,7 +915,7 @@ hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
 hipError_t launch_reached(Graph &g, const uint32_t *member, int32_t vx, int32_t vy,
                           uint32_t *bits, unsigned long long *count, hipStream_t s) {
   const int64_t nwords = (g.n + 31) / 32;
-  launch_parts(g, MemberScope{member}, s);
+  launch_parts(g, MemberScope{member}, 0, s);
   uf_reached_kernel<<<small_grid(g, g.n), kBlock, 0, s>>>(member, g.parent, vx, vy, g.n, bits,
                                                           nwords, count);
   return hipGetLastError();

@@ -33,7 +33,11 @@ __device__ int32_t uf_find(int32_t *parent, int32_t x) {
   }
 }
 
+// Ends also where both have one parent, without a look at the root: most calls
+// find both ends in the largest tree, and once its root's line has been written
+// in a launch, reads of it queue (2.7 ms of one relabelling of 5.5 M vertices).
 __device__ void uf_union(int32_t *parent, int32_t a, int32_t b) {
+  if (aload(&parent[a]) == aload(&parent[b])) return;
   while (true) {
     a = uf_find(parent, a);
     b = uf_find(parent, b);
@@ -897,19 +901,17 @@ static void launch_parts(Graph &g, Scope scope, int merges, hipStream_t s) {
 }
 
 // Launches of the merging phase where few edges and no hubs leave the hooks
-// many small trees: their joining in the completion took longer than uniting
-// the first entries of every row had, 1 to 3 ms by the graph's seed.  Medians
-// over uniform graphs, united / hooked as on skewed graphs / merged so: 100,000
-// vertices with 95,000 edges 0.37 / 0.81 / 0.17 ms, 2 M with 2.1 M 3.5 / 2.8 /
-// 0.69, 5.5 M with 6.3 M 1.0 / 3.5 / 1.0; a random tree of 2 M 3.5 / 5.1 / 3.5, a
-// path of 200,000 0.38 / 0.49 / 0.44.  With fewer than half an edge a vertex (0.57
-// / 0.51 / 0.84 at 5.5 M and 0.4), more than 7/4 (1.2 / 0.42 / 0.44 at 2 M and
-// 2), long rows (1.6 / 0.32 / 0.27 at 1.5 M and 0.8) or more vertices (2.1 / 1.9
-// / 2.7 at 18 M and 1.1) the general merging is the faster, or the same.
+// many small trees, whose joining in the completion is slow: medians over
+// uniform graphs, one merge and the strided one / three merges and the unions:
+// 100,000 vertices with 95,000 edges 0.49 / 0.17 ms, 2 M with 2.1 M 1.2 / 0.73,
+// 5.5 M with 6.3 M 1.3 / 1.0; a random tree of 2 M 3.8 / 2.7, a path of 2 M 3.6 /
+// 0.75, of 200,000 0.33 / 0.47.  With fewer than half an edge a vertex (0.46 / 0.66
+// at 5.5 M and 0.4), more than 7/4 (0.40 / 0.45 at 2 M and 2), long rows (0.28 for
+// both at 1.5 M and 0.8) or more vertices (1.9 / 2.6 at 18 M and 1.1) the general
+// merging is the faster, or the same.
 static int sparse_merges(const Graph &g) {
   const int64_t n = g.n, m = g.m_csr;
-  if (g.nheavy > 0 || n > (8 << 20) || 2 * m <= n || 4 * m > 7 * n) return 0;
-  return 4 * m <= 3 * n ? 6 : 3;
+  return g.nheavy == 0 && n <= (8 << 20) && 2 * m > n && 4 * m <= 7 * n ? 3 : 0;
 }
 
 // Component labels for the whole graph (label < 0) or re-labelling of the

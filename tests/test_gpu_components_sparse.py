@@ -64,11 +64,9 @@ def _block(nU, nL, eu, ev):
 GRAPHS = {
     "path": lambda: _path(4000),
     "tree": lambda: _tree(4000),
-    # of 3,500 vertices: half as many edges, 3/4 and 7/4 of them, and the next
+    # of 3,500 vertices: half as many edges, 7/4 of them, and the next
     "half": lambda: _uniform(2000, 1500, 1750),
     "past half": lambda: _uniform(2000, 1500, 1751),
-    "3/4": lambda: _uniform(2000, 1500, 2625),
-    "past 3/4": lambda: _uniform(2000, 1500, 2626),
     "7/4": lambda: _uniform(2000, 1500, 6125),
     "past 7/4": lambda: _uniform(2000, 1500, 6126),
     "rows of 64": lambda: _stars(64),

@@ -79,7 +79,7 @@ const char *abcore_last_error(void);
  * [0,n_lower)), read during the call and not retained.  Duplicate pairs are
  * removed (the edge set E is a set).  Builds one CSR over unified ids holding
  * both adjacencies, rows sorted ascending.  Requires n_upper, n_lower >= 0,
- * n_upper + n_lower < 2^31 and m < 2^31.  Synchronous.
+ * n_upper + n_lower < 2^30 - 1 and m < 2^31 - 1.  Synchronous.
  * out: receives the handle.  out_m_distinct (nullable): distinct edge count.
  * Errors: EINVAL (null pointer, negative size, id out of range), ENOMEM,
  * EDEVICE. */
@@ -384,6 +384,11 @@ abcore_status abcore_serve_stop(abcore_graph g, int64_t *counters);
  *                          GCC kernels; read with abcore_kernel_timing.
  *   ABCORE_OPT_PULL      : first GCC round in pull form: 0 = decided on the
  *                          device from the scan frontier, 1 = never, 2 = always.
+ *                          On graphs of at least 2^22 vertices large rounds
+ *                          that are not pulled are binned (sorted by id range
+ *                          and applied there) instead of pushed by atomics;
+ *                          with 1 none is.  Any value but 0 also keeps small
+ *                          graphs on the general path (see below).
  *   ABCORE_OPT_CLAIM     : queue slots a wave of the asynchronous peel takes
  *                          at a time, 1..64 (0 = 32).
  *   ABCORE_OPT_RANK_ORDER: 1 (default) = a GCC query whose first round is
@@ -440,6 +445,12 @@ abcore_status abcore_serve_stop(abcore_graph g, int64_t *counters);
  *                          j in 1..16 = every append tries sub-queue j-1
  *                          first, so that it fills and the rest overflow.
  *                          Results are identical either way.
+ *
+ * Small graphs (at most 81,920 adjacency entries that fit one workgroup's LDS,
+ * four times as many in batches of four queries and more) run a GCC query, or
+ * a GCC+ query between unequal thresholds, in a single workgroup, unless stats
+ * are asked for, edges were inserted, or PEEL_MODE, PULL, GRID, CLAIM,
+ * APPEND_SUBQUEUE or SPIN_LIMIT is set.  Results are identical either way.
  *
  * Aborts.  Every device-side wait is bounded.  A computation whose wait
  * exceeds its bound leaves an invalid result; a call that requested stats
@@ -498,9 +509,11 @@ abcore_status abcore_tuned(abcore_graph g, int32_t kind, int32_t *out_grid, int3
 abcore_status abcore_tune_cache(const char *path, int32_t mode);
 
 /* Kernel kinds timed while ABCORE_OPT_TIMING is on: the push peel
- * (Algorithm 1, peel phase), the pull-form first round, the scan phase, the
+ * (Algorithm 1, peel phase; a query in one workgroup counts here as a whole),
+ * the pull-form first round and, on large graphs, the binned rounds after it
+ * (2 + 2 launches a round where a query has any), the scan phase, the
  * bitmask pack and the pull round's completion (split rows below threshold
- * queued, round range advanced). */
+ * queued, round range advanced).  Batches in the default peel mode are not timed. */
 enum {
   ABCORE_KERNEL_PEEL = 0,
   ABCORE_KERNEL_PULL = 1,

@@ -13,15 +13,22 @@ namespace abc {
 // Bit x of `bits`: x lies in the component of vx or of vy (labels read from
 // comp, which the scoped scan used) and its final working degree reached its
 // threshold.  Every word is written; *count (nullable) gains the bits set.
+// connected: a component counts only if its vx or vy is such a vertex itself,
+// so that the search for the parts around vertices outside the core passes
+// over empty words.
 __global__ __launch_bounds__(kBlock) void pack_scope_kernel(const int32_t *__restrict__ deg,
                                                             const int32_t *__restrict__ comp,
                                                             int32_t vx, int32_t vy, int64_t n,
                                                             int32_t nU, int32_t thrU,
                                                             int32_t thrL,
                                                             uint32_t *__restrict__ bits,
-                                                            int64_t nwords,
+                                                            int64_t nwords, bool connected,
                                                             unsigned long long *count) {
-  const int32_t c1 = comp[vx], c2 = comp[vy];
+  auto label = [&](int32_t v) {
+    const int32_t c = comp[v], d = ld_agent(&deg[v]);
+    return connected && d < (v < nU ? thrU : thrL) ? -1 : c;  // (no vertex has label -1)
+  };
+  const int32_t c1 = label(vx), c2 = label(vy);
   const int64_t stride = (int64_t)gridDim.x * kBlock;
   unsigned long long total = 0;
   for (int64_t base = ((int64_t)blockIdx.x * kWavesPerBlock + wave_in_block()) * kWave;
@@ -103,7 +110,8 @@ abcore_status scoped_set(Graph &g, int32_t vx, int32_t vy, int32_t thrU, int32_t
   uint32_t *member = connected ? g.row_bits : d_bits;
   if (hipMemsetAsync(dc, 0, sizeof(unsigned long long), s) != hipSuccess) goto fail;
   pack_scope_kernel<<<grid_for(g, nwords * 32, kBlock), kBlock, 0, s>>>(
-      g.deg, g.comp, vx, vy, g.n, g.nU, thrU, thrL, member, nwords, connected ? nullptr : dc);
+      g.deg, g.comp, vx, vy, g.n, g.nU, thrU, thrL, member, nwords, connected,
+      connected ? nullptr : dc);
   if (hipGetLastError() != hipSuccess) goto fail;
   if (connected && launch_reached(g, member, vx, vy, d_bits, dc, s) != hipSuccess) goto fail;
   if (count != nullptr &&

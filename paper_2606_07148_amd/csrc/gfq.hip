@@ -56,11 +56,9 @@ __device__ void uf_union(int32_t *parent, int32_t a, int32_t b) {
 // The vertices a search for connected parts covers: those labelled `label`
 // (all when it is negative; a row's live entries stay inside), or the members
 // of a bitmap (a row's entries are tested too).
-// none(): nobody asks for the parts; every kernel then ends at once.
 struct LabelScope {
   const int32_t *comp;
   int32_t label;
-  __device__ __forceinline__ bool none() const { return false; }
   __device__ __forceinline__ bool in(int64_t x) const { return label < 0 || comp[x] == label; }
   __device__ __forceinline__ bool near(int32_t w) const { return w >= 0; }
   // a vertex at or after sample i of k, or -1
@@ -71,8 +69,6 @@ struct LabelScope {
 };
 struct MemberScope {
   const uint32_t *bits;
-  int32_t vx, vy;  // the parts asked for are theirs
-  __device__ __forceinline__ bool none() const { return !in(vx) && !in(vy); }
   __device__ __forceinline__ bool in(int64_t x) const { return (bits[x >> 5] >> (x & 31)) & 1u; }
   __device__ __forceinline__ bool near(int32_t w) const { return w >= 0 && in(w); }
   // (members may be few: the first one in the 64 words from the sample on)
@@ -105,7 +101,6 @@ template <class Scope>
 __global__ void uf_hook_lower_kernel(const int64_t *__restrict__ off,
                                      const int32_t *__restrict__ cols, Scope scope,
                                      int32_t *parent, int64_t nU, int64_t n) {
-  if (scope.none()) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride) {
     if (!scope.in(x)) continue;
@@ -128,7 +123,6 @@ template <class Scope>
 __global__ void uf_hook_upper_kernel(const int64_t *__restrict__ off,
                                      const int32_t *__restrict__ cols, Scope scope,
                                      int32_t *parent, int64_t nU) {
-  if (scope.none()) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < nU; x += stride) {
     if (!scope.in(x)) continue;
@@ -147,7 +141,6 @@ __global__ void uf_hook_upper_kernel(const int64_t *__restrict__ off,
 
 template <class Scope>
 __global__ void uf_compress_kernel(int32_t *parent, Scope scope, int64_t n) {
-  if (scope.none()) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride)
     if (scope.in(x)) astore(&parent[x], uf_find(parent, (int32_t)x));
@@ -178,7 +171,6 @@ template <bool kFind, class Scope>
 __global__ __launch_bounds__(kMergeBlock) void uf_merge_kernel(
     const int64_t *__restrict__ off, const int32_t *__restrict__ cols, Scope scope,
     int32_t *parent, int64_t nU) {
-  if (scope.none()) return;
   __shared__ int32_t key[kMergeSlots], low[kMergeSlots];
   for (int i = threadIdx.x; i < kMergeSlots; i += kMergeBlock) {
     key[i] = -1;
@@ -249,7 +241,6 @@ template <class Scope>
 __global__ __launch_bounds__(kRootSamples) void uf_big_root_kernel(const int32_t *parent,
                                                                    Scope scope, int64_t n,
                                                                    int32_t *big) {
-  if (scope.none()) return;
   __shared__ __align__(16) int32_t roots[kRootSamples];
   __shared__ unsigned long long best;
   const int i = threadIdx.x;
@@ -278,7 +269,6 @@ __global__ __launch_bounds__(kBlock) void uf_rest_link_kernel(
     const int64_t *__restrict__ off, const int32_t *__restrict__ cols, Scope scope,
     int32_t *parent, const int32_t *ins_head, const int32_t *ins_next,
     const int32_t *ins_other, int64_t n, const int32_t *big_root) {
-  if (scope.none()) return;
   const int32_t big = *big_root;
   const int gw = blockIdx.x * kWavesPerBlock + wave_in_block();
   const int nw = gridDim.x * kWavesPerBlock;
@@ -340,7 +330,7 @@ __global__ __launch_bounds__(kBlock) void uf_reached_kernel(const uint32_t *__re
                                                             uint32_t *__restrict__ bits,
                                                             int64_t nwords,
                                                             unsigned long long *count) {
-  const MemberScope scope{member, vx, vy};
+  const MemberScope scope{member};
   // (a root is the vertex itself or smaller: -1 is no member's root)
   const int32_t r1 = scope.in(vx) ? uf_find(parent, vx) : -1;
   const int32_t r2 = scope.in(vy) ? uf_find(parent, vy) : -1;
@@ -927,7 +917,7 @@ hipError_t launch_cc(Graph &g, int32_t label, hipStream_t s) {
 hipError_t launch_reached(Graph &g, const uint32_t *member, int32_t vx, int32_t vy,
                           uint32_t *bits, unsigned long long *count, hipStream_t s) {
   const int64_t nwords = (g.n + 31) / 32;
-  launch_parts(g, MemberScope{member, vx, vy}, 0, s);
+  launch_parts(g, MemberScope{member}, 0, s);
   uf_reached_kernel<<<small_grid(g, g.n), kBlock, 0, s>>>(member, g.parent, vx, vy, g.n, bits,
                                                           nwords, count);
   return hipGetLastError();
